@@ -1331,9 +1331,9 @@ def summarize_traffic(fetch_dir, write_dir, out_path, calib_bytes, workload):
     def graph_test(nm):
         nm = nm.replace("(anonymous namespace)::", "")
         return any(k in nm for k in ("validate_kernel(", "validate_reduce_kernel(", "canon_keys_kernel(",
-                                     "decode_packed_kernel(", "decode_split_kernel(", "tpos_kernel(",
-                                     "n_order_fix_kernel(", "offsets_kernel(")) or \
-            ("sort_pass_kernel<" in nm and "sort_pass_kernel<unsigned int, unsigned int," not in nm)
+                                     "decode_packed_kernel(", "decode_split_kernel(", "list_finish_kernel<",
+                                     "n_order_fix_kernel<", "offsets_kernel(")) or \
+            ("sort_pass_kernel<" in nm and "sort_pass_kernel<unsigned int, unsigned int, SortNone" not in nm)
     builds = sum(len(vs) for nm, vs in fk.items() if "validate_kernel(" in nm.replace("(anonymous namespace)::", ""))
     if builds:
         fb = sum(x for nm, vs in fk.items() if graph_test(nm) for x in vs) * 1024 * f_scale / builds

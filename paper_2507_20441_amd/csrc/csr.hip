@@ -144,28 +144,74 @@ __global__ void decode_split_kernel(const u64* tsorted, const u64* uv, int64_t m
     if (e > 0 && uv[e - 1] == k && tsorted[e - 1] == t) atomicOr(flags, kDup);
 }
 
-// By eid: the edge's position in a T order (the inverse of leid).
-__global__ void tpos_kernel(const int32_t* leid, int64_t m, int32_t* pos) {
+// out[from .. to) = v for every lane of the wave (an empty range writes
+// nothing): short ranges lane by lane, long ones by the whole wave.  Every
+// lane of the wave calls it.
+__device__ __forceinline__ void wave_fill(int32_t* out, int64_t from, int64_t to, int32_t v) {
+    const bool big = to - from > 64;
+    if (!big)
+        for (int64_t i = from; i < to; ++i) out[i] = v;
+    for (u64 todo = __ballot(big); todo; todo &= todo - 1) {
+        const int src = __ffsll(todo) - 1;
+        const int64_t f = __shfl((long long)from, src, 64), t = __shfl((long long)to, src, 64);
+        const int32_t w = __shfl(v, src, 64);
+        for (int64_t i = f + (threadIdx.x & 63); i < t; i += 64) out[i] = w;
+    }
+}
+
+// Search guide of one list order (see DevGraph): position p writes the
+// entries after the previous position's slice up to its own, the last
+// position also those after it.  own: the list owners in order, key(p) the
+// time or neighbour at p.
+template <typename F>
+__device__ __forceinline__ void guide_fill(const uint32_t* own, const int32_t* off, int64_t m, int32_t n, int64_t p,
+                                           const F& key, int bits, uint32_t mul, int32_t* guide) {
+    int64_t from = 0, to = 0, end = 0;
+    if (p < m) {
+        auto entry = [&](int64_t i) -> int64_t {
+            // (clamped owners: a broken order must not write outside the guide)
+            const int32_t g = own[i] < (uint32_t)n ? (int32_t)own[i] : n - 1;
+            const int32_t a = off[g], b = off[g + 1];
+            return guide_first(g, a) + slice_of(slice_frac(key(i), bits, mul), guide_slices(a, b));
+        };
+        to = entry(p) + 1;
+        from = p == 0 ? 0 : entry(p - 1) + 1;
+        if (p == m - 1) end = guide_first(n, (int32_t)m) + 1;
+    }
+    wave_fill(guide, from, to, (int32_t)p);
+    wave_fill(guide, to, end, (int32_t)m);
+}
+
+// What follows a T-order sort, in one pass over the positions: by eid the
+// edge's position (the inverse of leid), the (neighbour, time) records of
+// 32-bit lists, and the guide by time.
+template <typename TT>
+__global__ void __launch_bounds__(kBlock)
+list_finish_kernel(const uint32_t* own, const int32_t* leid, const uint32_t* nbr, const TT* t, const int32_t* off,
+                   int64_t m, int32_t n, int bt, uint32_t tmul, int32_t* pos, uint2* nt, int32_t* guide) {
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (p < m && (uint32_t)leid[p] < (uint64_t)m) pos[leid[p]] = (int32_t)p;
+    if (p < m) {
+        if ((uint32_t)leid[p] < (uint64_t)m) pos[leid[p]] = (int32_t)p;
+        if (nt) nt[p] = make_uint2(nbr[p], (uint32_t)t[p]);
+    }
+    if (guide) guide_fill(own, off, m, n, p, [&](int64_t i) { return (u64)t[i]; }, bt, tmul, guide);
 }
 
 // N order: the packed key from the carried neighbour and time (ntime: the
-// carried times, which may be nkey itself), and each entry's position in
-// this direction's T order.
+// carried times, which may be nkey itself), each entry's position in this
+// direction's T order, and the guide by neighbour.  own: the owners, the
+// same sequence in both orders.
 template <typename TT>
-__global__ void n_order_fix_kernel(const uint32_t* nbr, const TT* ntime, const int32_t* neid, const int32_t* tpos,
-                                   int64_t m, int bt, u64* nkey, int32_t* nxref) {
+__global__ void __launch_bounds__(kBlock)
+n_order_fix_kernel(const uint32_t* nbr, const TT* ntime, const int32_t* neid, const int32_t* tpos, const uint32_t* own,
+                   const int32_t* off, int64_t m, int32_t n, int bt, int bn, uint32_t nmul, u64* nkey, int32_t* nxref,
+                   int32_t* guide) {
     const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (q >= m) return;
-    nkey[q] = ((u64)nbr[q] << bt) | (u64)ntime[q];
-    nxref[q] = (uint32_t)neid[q] < (uint64_t)m ? tpos[neid[q]] : -1;
-}
-
-// (neighbour, time) records of a T order with 32-bit times.
-__global__ void pack_nt_kernel(const uint32_t* nbr, const uint32_t* t, int64_t m, uint2* nt) {
-    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (p < m) nt[p] = make_uint2(nbr[p], t[p]);
+    if (q < m) {
+        nkey[q] = ((u64)nbr[q] << bt) | (u64)ntime[q];
+        nxref[q] = (uint32_t)neid[q] < (uint64_t)m ? tpos[neid[q]] : -1;
+    }
+    if (guide) guide_fill(own, off, m, n, q, [&](int64_t i) { return (u64)nbr[i]; }, bn, nmul, guide);
 }
 
 // List offsets from the owner-sorted keys: off[v] is the first position whose
@@ -173,14 +219,18 @@ __global__ void pack_nt_kernel(const uint32_t* nbr, const uint32_t* t, int64_t m
 // (key[p-1], key[p]]; the last position also closes the owners after it.
 __global__ void offsets_kernel(const uint32_t* key, int64_t m, int32_t n, int32_t* off) {
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (p >= m) return;
-    // (owners are below n; the clamps keep a broken order from writing
-    // outside off)
-    const int64_t cur = key[p] < (uint32_t)n ? (int64_t)key[p] : (int64_t)n - 1;
-    const int64_t prev = p == 0 ? -1 : (key[p - 1] < (uint32_t)n ? (int64_t)key[p - 1] : (int64_t)n - 1);
-    for (int64_t v = prev + 1; v <= cur; ++v) off[v] = (int32_t)p;
-    if (p == m - 1)
-        for (int64_t v = cur + 1; v <= n; ++v) off[v] = (int32_t)m;
+    int64_t from = 0, to = 0, end = 0;
+    if (p < m) {
+        // (owners are below n; the clamps keep a broken order from writing
+        // outside off)
+        const int64_t cur = key[p] < (uint32_t)n ? (int64_t)key[p] : (int64_t)n - 1;
+        const int64_t prev = p == 0 ? -1 : (key[p - 1] < (uint32_t)n ? (int64_t)key[p - 1] : (int64_t)n - 1);
+        from = prev + 1;
+        to = cur + 1;
+        if (p == m - 1) end = (int64_t)n + 1;
+    }
+    wave_fill(off, from, to, (int32_t)p);
+    wave_fill(off, to, end, (int32_t)m);
 }
 
 int bits_for(u64 x) {
@@ -255,6 +305,9 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     const int bn = bits_for((u64)(n > 0 ? n - 1 : 0));
     D.bt = bits_for((u64)g->T);
     if (D.bt == 0) D.bt = 1;
+    D.bn = bn;
+    D.tmul = slice_scale((u64)g->T, D.bt);
+    D.nmul = slice_scale((u64)(n - 1), bn);
     if (bn + D.bt > 64)
         return bail(tm_fail(TM_ERANGE, "graph: %d vertex-id bits + %d time bits exceed 64", bn, D.bt));
 
@@ -377,6 +430,11 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         int32_t* tpos[2] = {nullptr, nullptr};
         TT* ltab[2] = {nullptr, nullptr};
         uint32_t* lnbr_of[2] = {nullptr, nullptr};  // each T order's neighbours (the N-order sorts' keys)
+        // guides pay from lists of a few entries on; with fewer edges than
+        // vertices the lists are shorter than that and the guides' entry per
+        // vertex would outweigh the edges
+        const bool guides = n <= m;
+        const size_t guide_len = (size_t)guide_first(n, (int32_t)m) + 1;
         for (int dir = 0; dir < 2; ++dir) {
             TT* lt = nullptr;
             int32_t *leid = nullptr, *lnbr = nullptr, *lown = nullptr, *off = nullptr;
@@ -405,18 +463,19 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             TM_TRY(sort_into(in, out, tmp, m, 0, bn, 2 /* eids: 0, 1, ... */, flags + 1, st));
             hipLaunchKernelGGL(offsets_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const uint32_t*)own[dir],
                                m, n, off);
-            hipLaunchKernelGGL(tpos_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const int32_t*)leid, m,
-                               tpos[dir]);
+            uint2* nt = nullptr;
+            int32_t* tguide = nullptr;
+            if constexpr (sizeof(TT) == 4) TM_TRY(arena_alloc(g->arena, &nt, m));
+            if (guides) TM_TRY(arena_alloc(g->arena, &tguide, guide_len));
+            hipLaunchKernelGGL((list_finish_kernel<TT>), dim3(grid_for(m)), dim3(kBlock), 0, st,
+                               (const uint32_t*)own[dir], (const int32_t*)leid, (const uint32_t*)lnbr, (const TT*)lt,
+                               (const int32_t*)off, m, n, D.bt, D.tmul, tpos[dir], nt, tguide);
             if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: list launch");
             D.off[dir] = off;
             D.tpos[dir] = tpos[dir];
+            D.tguide[dir] = tguide;
             ltab[dir] = lt;
             if constexpr (sizeof(TT) == 4) {
-                uint2* nt = nullptr;
-                TM_TRY(arena_alloc(g->arena, &nt, m));
-                hipLaunchKernelGGL(pack_nt_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st,
-                                   (const uint32_t*)lnbr, (const uint32_t*)lt, m, nt);
-                if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: list launch");
                 D.lt32[dir] = reinterpret_cast<const uint32_t*>(lt);
                 D.lt[dir] = nullptr;
                 D.lnt[dir] = nt;
@@ -441,6 +500,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             TM_TRY(arena_alloc(g->arena, &nkey, m));
             TM_TRY(arena_alloc(g->arena, &nxref, m));
             TM_TRY(arena_alloc(g->arena, &neid, m));
+            int32_t* nguide = nullptr;
+            if (guides) TM_TRY(arena_alloc(g->arena, &nguide, guide_len));
             L in, out;
             in.k = lnbr_of[other];
             in.v0 = reinterpret_cast<V*>(ltab[other]);
@@ -453,11 +514,13 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             TM_TRY(sort_into(in, out, tmp, m, 0, bn, 0, flags + 1, st));
             hipLaunchKernelGGL((n_order_fix_kernel<V>), dim3(grid_for(m)), dim3(kBlock), 0, st,
                                (const uint32_t*)nbr_carried, (const V*)out.v0, (const int32_t*)neid,
-                               (const int32_t*)tpos[dir], m, D.bt, nkey, nxref);
+                               (const int32_t*)tpos[dir], (const uint32_t*)own[dir], D.off[dir], m, n, D.bt, bn,
+                               D.nmul, nkey, nxref, nguide);
             if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: list launch");
             D.nkey[dir] = nkey;
             D.nxref[dir] = nxref;
             D.neid[dir] = neid;
+            D.nguide[dir] = nguide;
         }
         return TM_OK;
     };

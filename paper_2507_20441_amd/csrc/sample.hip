@@ -144,26 +144,47 @@ struct Bounds {
 };
 
 // The four searches of window_bounds in lockstep over a T order of time
-// type TT (wlo <= whi inside [0, T], which TT holds).
+// type TT (wlo <= whi inside [0, T], which TT holds) and the N order of the
+// same list [r.a, r.b) of vertex g (not empty), each inside its guide slice
+// when there are guides (see DevGraph).
 template <typename TT>
-__device__ __forceinline__ void window_search(const TT* lt, const u64* nk, int32_t a, int32_t b, TT wlo, TT whi,
-                                              u64 klo, u64 khi, Bounds& r) {
-    int32_t b0 = a, b1 = a, b2 = a, b3 = a;
-    int32_t n = b - a;
-    while (n > 1) {
-        const int32_t h = n >> 1;
-        const TT x0 = lt[b0 + h], x1 = lt[b1 + h];
-        const u64 x2 = nk[b2 + h], x3 = nk[b3 + h];
-        b0 = x0 < wlo ? b0 + h : b0;
-        b1 = x1 <= whi ? b1 + h : b1;
-        b2 = x2 < klo ? b2 + h : b2;
-        b3 = x3 <= khi ? b3 + h : b3;
-        n -= h;
+__device__ __forceinline__ void window_search(const DevGraph& G, int dir, int32_t g, int32_t o, const TT* lt,
+                                              const u64* nk, TT wlo, TT whi, u64 klo, u64 khi, Bounds& r) {
+    int32_t b0 = r.a, b1 = r.a, b2 = r.a, n0 = r.b - r.a, n1 = n0, n2 = n0;
+    if (G.tguide[dir]) {
+        const int64_t first = guide_first(g, r.a);
+        const int32_t ns = guide_slices(r.a, r.b);
+        const int32_t* e0 = G.tguide[dir] + first + slice_of(time_frac<TT>(wlo, G.bt, G.tmul), ns);
+        const int32_t* e1 = G.tguide[dir] + first + slice_of(time_frac<TT>(whi, G.bt, G.tmul), ns);
+        const int32_t* e2 = G.nguide[dir] + first + slice_of(slice_frac((u64)(uint32_t)o, G.bn, G.nmul), ns);
+        b0 = e0[0];
+        n0 = e0[1] - b0;
+        b1 = e1[0];
+        n1 = e1[1] - b1;
+        b2 = e2[0];
+        n2 = e2[1] - b2;
     }
-    r.p0 = b0 + (lt[b0] < wlo ? 1 : 0);
-    r.p1 = b1 + (lt[b1] <= whi ? 1 : 0);
-    r.q0 = b2 + (nk[b2] < klo ? 1 : 0);
-    r.q1 = b3 + (nk[b3] <= khi ? 1 : 0);
+    int32_t b3 = b2, n3 = n2;
+    // a finished search (n = 0) probes the list's first entry and ignores it
+    while ((n0 | n1 | n2 | n3) > 0) {
+        const int32_t h0 = n0 >> 1, h1 = n1 >> 1, h2 = n2 >> 1, h3 = n3 >> 1;
+        const TT x0 = lt[n0 > 0 ? b0 + h0 : r.a], x1 = lt[n1 > 0 ? b1 + h1 : r.a];
+        const u64 x2 = nk[n2 > 0 ? b2 + h2 : r.a], x3 = nk[n3 > 0 ? b3 + h3 : r.a];
+        const bool u0 = n0 > 0 && x0 < wlo, u1 = n1 > 0 && x1 <= whi;
+        const bool u2 = n2 > 0 && x2 < klo, u3 = n3 > 0 && x3 <= khi;
+        b0 = u0 ? b0 + h0 + 1 : b0;
+        n0 = u0 ? n0 - h0 - 1 : h0;
+        b1 = u1 ? b1 + h1 + 1 : b1;
+        n1 = u1 ? n1 - h1 - 1 : h1;
+        b2 = u2 ? b2 + h2 + 1 : b2;
+        n2 = u2 ? n2 - h2 - 1 : h2;
+        b3 = u3 ? b3 + h3 + 1 : b3;
+        n3 = u3 ? n3 - h3 - 1 : h3;
+    }
+    r.p0 = b0;
+    r.p1 = b1;
+    r.q0 = b2;
+    r.q1 = b3;
 }
 
 // The child window of Claim "matching-edges-set" in list dir of vertex g with
@@ -183,9 +204,9 @@ __device__ __forceinline__ Bounds window_bounds(const DevGraph& G, int dir, int3
     const u64 base = (u64)o << G.bt;
     const u64 klo = base | (u64)wlo, khi = base | (u64)whi;
     if (G.lt32[dir])
-        window_search<uint32_t>(G.lt32[dir], nk, r.a, r.b, (uint32_t)wlo, (uint32_t)whi, klo, khi, r);
+        window_search<uint32_t>(G, dir, g, o, G.lt32[dir], nk, (uint32_t)wlo, (uint32_t)whi, klo, khi, r);
     else
-        window_search<int64_t>(G.lt[dir], nk, r.a, r.b, wlo, whi, klo, khi, r);
+        window_search<int64_t>(G, dir, g, o, G.lt[dir], nk, wlo, whi, klo, khi, r);
     return r;
 }
 
@@ -211,22 +232,32 @@ __device__ __forceinline__ void el_run_dir(const DevGraph& G, int dir, int32_t x
     const u64* nk = G.nkey[dir];
     const u64 base = (u64)(dir ? x : y) << G.bt;
     const u64 klo = base | (u64)lo, khi = base | (u64)hi;
-    int32_t b0 = la;
-    int32_t n = lb - la;
-    while (n > 1) {
-        const int32_t h = n >> 1;
-        b0 = nk[b0 + h] < klo ? b0 + h : b0;
-        n -= h;
+    // the slice of the list's guide that holds the far endpoint's run (the
+    // whole list without guides)
+    int32_t b0 = la, n = lb - la;
+    const int32_t* gd = G.nguide[dir];
+    if (gd) {
+        const int32_t* e = gd + guide_first(dir ? y : x, la) +
+                           slice_of(slice_frac((u64)(uint32_t)(dir ? x : y), G.bn, G.nmul), guide_slices(la, lb));
+        b0 = e[0];
+        n = e[1] - b0;
         if (np) ++*np;
     }
-    ra = b0 + (nk[b0] < klo ? 1 : 0);
-    if (np) ++*np;
+    const int32_t end = b0 + n;
+    while (n > 0) {
+        const int32_t h = n >> 1;
+        const bool up = nk[b0 + h] < klo;
+        b0 = up ? b0 + h + 1 : b0;
+        n = up ? n - h - 1 : h;
+        if (np) ++*np;
+    }
+    ra = b0;
     // every key before ra is below klo <= khi: rb is the first position at
     // or after ra whose key exceeds khi; [g0, g1] holds it
-    int32_t g0 = ra, g1 = lb, p = ra - 1;
+    int32_t g0 = ra, g1 = end, p = ra - 1;
     for (int32_t step = 1;; step <<= 1) {
         const int32_t q = p + step;
-        if (q >= lb) break;
+        if (q >= end) break;
         if (np) ++*np;
         if (nk[q] > khi) {
             g1 = q;

@@ -135,39 +135,78 @@ __device__ __forceinline__ constexpr int bound_rank(int k) {
                                                                      : (k == 0 ? 1 : (k == 1 ? 0 : (k == 2 ? 3 : 2))));
 }
 
-// The first positions in [a, b) of a T order whose time is >= x[j], for NB
-// bounds in lockstep (independent loads per step).  x[j] lies in [0, T + 1],
-// which the time type TT holds.  With kN, the same halving steps also find
-// q, the bound of (kq, leq) in the N order over the same range: its probe
-// is one more independent load per step instead of a second chain of
-// dependent ones after the first.
+// The first positions in [a, b) (not empty) of a T order whose time is >= x[j],
+// for NB bounds in lockstep (independent loads per step).  x[j] lies in
+// [0, T + 1], which the time type TT holds.  With kN, the same halving steps
+// also find q, the bound of (kq, leq) in the N order over the same range, kq's
+// neighbour being o: its probe is one more independent load per step instead
+// of a second chain of dependent ones after the first.
+//
+// Each search looks only at the entries of its guide slice (see DevGraph), a
+// few of them whatever the list's length: the kernel's time is its probes
+// (the address path is busy 95-99%), and over whole lists each of the four
+// searches took one per doubling of the list.
 template <typename TT, int NB, bool kN>
-__device__ __forceinline__ void lockstep_lower(const TT* lt, int32_t a, int32_t b, const int64_t (&x)[NB],
-                                               int32_t (&p)[NB], const u64* nk, u64 kq, bool leq, int32_t& q) {
+__device__ __forceinline__ void lockstep_lower(const DevGraph& G, const TT* lt, int dir, int32_t g, int32_t a,
+                                               int32_t b, const int64_t (&x)[NB], int32_t (&p)[NB], const u64* nk,
+                                               u64 kq, bool leq, int32_t o, int32_t& q) {
     TT xk[NB];
-    int32_t c[NB];
+    int32_t c[NB], n[NB];
+    int32_t cq = a, nq = kN ? b - a : 0;
+    const int32_t* tg = sel2(G.tguide, dir);
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         xk[j] = (TT)x[j];
         c[j] = a;
+        n[j] = b - a;
     }
-    int32_t cq = a;
-    int32_t n = b - a;
-    while (n > 1) {
-        const int32_t h = n >> 1;
+    if (tg) {
+        const int64_t first = guide_first(g, a);
+        const int32_t ns = guide_slices(a, b);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            // (x = T + 1 lies past every time: the last slice holds its bound)
+            const TT y = x[j] > G.T ? (TT)G.T : xk[j];
+            const int32_t* e = tg + first + slice_of(time_frac<TT>(y, G.bt, G.tmul), ns);
+            c[j] = e[0];
+            n[j] = e[1] - c[j];
+        }
+        if constexpr (kN) {
+            const int32_t* e = sel2(G.nguide, dir) + first + slice_of(slice_frac((u64)(uint32_t)o, G.bn, G.nmul), ns);
+            cq = e[0];
+            nq = e[1] - cq;
+        }
+    }
+    auto left = [&]() {
+        int32_t l = nq;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) l |= n[j];
+        return l;
+    };
+    // a finished search (n = 0) probes the list's first entry and ignores it
+    while (left() > 0) {
         TT y[NB];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) y[j] = lt[c[j] + h];
+        for (int j = 0; j < NB; ++j) y[j] = lt[n[j] > 0 ? c[j] + (n[j] >> 1) : a];
         u64 z = 0;
-        if constexpr (kN) z = nk[cq + h];
+        if constexpr (kN) z = nk[nq > 0 ? cq + (nq >> 1) : a];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) c[j] = y[j] < xk[j] ? c[j] + h : c[j];
-        if constexpr (kN) cq = key_before(z, kq, leq) ? cq + h : cq;
-        n -= h;
+        for (int j = 0; j < NB; ++j) {
+            const int32_t h = n[j] >> 1;
+            const bool up = n[j] > 0 && y[j] < xk[j];
+            c[j] = up ? c[j] + h + 1 : c[j];
+            n[j] = up ? n[j] - h - 1 : h;
+        }
+        if constexpr (kN) {
+            const int32_t h = nq >> 1;
+            const bool up = nq > 0 && key_before(z, kq, leq);
+            cq = up ? cq + h + 1 : cq;
+            nq = up ? nq - h - 1 : h;
+        }
     }
 #pragma unroll
-    for (int j = 0; j < NB; ++j) p[j] = a == b ? a : c[j] + (lt[c[j]] < xk[j] ? 1 : 0);
-    if constexpr (kN) q = a == b ? a : cq + (key_before(nk[cq], kq, leq) ? 1 : 0);
+    for (int j = 0; j < NB; ++j) p[j] = c[j];
+    if constexpr (kN) q = cq;
 }
 
 template <int NB, int Kind>
@@ -181,13 +220,18 @@ __device__ __forceinline__ BoundsN<NB> level_bounds(const DevGraph& G, int dir, 
     BoundsN<NB> r;
     r.len = b - a;
     const uint32_t* lt32 = sel2(G.lt32, dir);
-    if (!exclude || a == b) {
+    if (a == b) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) r.p[j] = r.q[j] = a;
+        return r;
+    }
+    if (!exclude) {
         // T order only: no excluded run
         int32_t unused = a;
         if (lt32)
-            lockstep_lower<uint32_t, NB, false>(lt32, a, b, x, r.p, nk, 0, false, unused);
+            lockstep_lower<uint32_t, NB, false>(G, lt32, dir, g, a, b, x, r.p, nk, 0, false, o, unused);
         else
-            lockstep_lower<int64_t, NB, false>(sel2(G.lt, dir), a, b, x, r.p, nk, 0, false, unused);
+            lockstep_lower<int64_t, NB, false>(G, sel2(G.lt, dir), dir, g, a, b, x, r.p, nk, 0, false, o, unused);
 #pragma unroll
         for (int j = 0; j < NB; ++j) r.q[j] = a;
         return r;
@@ -206,9 +250,9 @@ __device__ __forceinline__ BoundsN<NB> level_bounds(const DevGraph& G, int dir, 
     constexpr int j0 = bound_rank<Kind>(0);
     int32_t q0 = a;
     if (lt32)
-        lockstep_lower<uint32_t, NB, true>(lt32, a, b, x, r.p, nk, kx[j0], le[j0], q0);
+        lockstep_lower<uint32_t, NB, true>(G, lt32, dir, g, a, b, x, r.p, nk, kx[j0], le[j0], o, q0);
     else
-        lockstep_lower<int64_t, NB, true>(sel2(G.lt, dir), a, b, x, r.p, nk, kx[j0], le[j0], q0);
+        lockstep_lower<int64_t, NB, true>(G, sel2(G.lt, dir), dir, g, a, b, x, r.p, nk, kx[j0], le[j0], o, q0);
     r.q[j0] = q0;
     sfor<1, NB>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
