@@ -214,6 +214,55 @@ n_order_fix_kernel(const uint32_t* nbr, const TT* ntime, const int32_t* neid, co
     if (guide) guide_fill(own, off, m, n, q, [&](int64_t i) { return (u64)nbr[i]; }, bn, nmul, guide);
 }
 
+// The pair ranks of both lists (see DevGraph), in one launch: thread i < m
+// takes position i of the out-lists' N order, the next m those of the
+// in-lists.  Both lists of a vertex are in (neighbour, time) order, so
+// consecutive lanes search the other list at nearby keys (their probes fall
+// on lines the wave shares); the write to the edge's T position, one record
+// inside one line, is the scattered part.  opos: per N position, the edge's T
+// position in the other list.
+__global__ void __launch_bounds__(kBlock)
+pair_rank_kernel(DevGraph G, const uint32_t* own0, const uint32_t* own1, const uint32_t* opos0, const uint32_t* opos1,
+                 uint4* rank0, uint4* rank1) {
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t m = G.m;
+    if (i >= 2 * m) return;
+    const int w = i >= m ? 1 : 0;
+    const int64_t q = w ? i - m : i;
+    const u64* nk = w ? G.nkey[1] : G.nkey[0];
+    const u64* ok = w ? G.nkey[0] : G.nkey[1];
+    const uint32_t own = w ? own1[q] : own0[q];
+    const int32_t g = own < (uint32_t)G.n ? (int32_t)own : G.n - 1;  // (a broken order must not read outside)
+    const int32_t* off = w ? G.off[1] : G.off[0];
+    const int32_t* ooff = w ? G.off[0] : G.off[1];
+    const int32_t a = ooff[g], b = ooff[g + 1];
+    const u64 key = nk[q];
+    const u64 o = key >> G.bt;
+    // two keys of one neighbour differ by their times
+    uint32_t sp = kGapNone, sn = kGapNone, rp = kGapNone, rn = kGapNone;
+    if (q > off[g] && (nk[q - 1] >> G.bt) == o) sp = gap_code(key - nk[q - 1]);
+    if (q + 1 < off[g + 1] && (nk[q + 1] >> G.bt) == o) sn = gap_code(nk[q + 1] - key);
+    int32_t c = a, n = b - a;
+    const int32_t* gd = w ? G.nguide[0] : G.nguide[1];
+    if (gd) {
+        const int32_t* e = gd + guide_first(g, a) + slice_of(slice_frac(o, G.bn, G.nmul), guide_slices(a, b));
+        c = e[0];
+        n = e[1] - c;
+    }
+    while (n > 0) {
+        const int32_t h = n >> 1;
+        const bool up = ok[c + h] < key;
+        c = up ? c + h + 1 : c;
+        n = up ? n - h - 1 : h;
+    }
+    if (c > a && (ok[c - 1] >> G.bt) == o) rp = gap_code(key - ok[c - 1]);
+    if (c < b && (ok[c] >> G.bt) == o) rn = gap_code(ok[c] - key + 1);
+    const uint32_t at = (uint32_t)(w ? G.nxref[1] : G.nxref[0])[q];
+    if (at < (u64)m)
+        (w ? rank1 : rank0)[at] = make_uint4((uint32_t)q, (uint32_t)c, (w ? opos1 : opos0)[q],
+                                             sp | (sn << 8) | (rp << 16) | (rn << 24));
+}
+
 // List offsets from the owner-sorted keys: off[v] is the first position whose
 // owner is >= v.  Position p writes the offsets of the owners in
 // (key[p-1], key[p]]; the last position also closes the owners after it.
@@ -232,6 +281,13 @@ __global__ void offsets_kernel(const uint32_t* key, int64_t m, int32_t n, int32_
     wave_fill(off, from, to, (int32_t)p);
     wave_fill(off, to, end, (int32_t)m);
 }
+
+// Graphs that keep pair ranks (32 B per edge).  They cost a graph build 25 us
+// at 1e5 edges, 35 us at 5e5 and 9 ms at 1e8, and take 2, 22-28 us and 3-4 ms
+// off every weight build with two to four levels: below 2^19 edges a graph
+// would have to meet many motifs to earn them.  Above 2^28 edges their memory
+// goes to weight sets, as that of the owners.
+bool pair_ranks_kept(int64_t m) { return m >= ((int64_t)1 << 19) && m <= ((int64_t)1 << 28); }
 
 int bits_for(u64 x) {
     int b = 0;
@@ -320,6 +376,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     // 2^32 - 1; t32e: those times by eid, the list sorts' input.
     const bool narrow = g->T < (int64_t)0xFFFFFFFFll;
     uint32_t* t32e = nullptr;
+    uint32_t* opos[3] = {nullptr, nullptr, nullptr};  // N orders: the carried other T positions, and their sort buffer
     uint32_t* nbr32[2] = {nullptr, nullptr};  // 32-bit times: the T orders' neighbours until packed
     auto release = [&]() {
         for (uint32_t*& b : nbr32) {
@@ -332,6 +389,10 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         }
         if (nbr_tmp) (void)dev_free(nbr_tmp, st);
         nbr_tmp = nullptr;
+        for (uint32_t*& b : opos) {
+            if (b) (void)dev_free(b, st);
+            b = nullptr;
+        }
         if (t32e) (void)dev_free(t32e, st);
         t32e = nullptr;
     };
@@ -434,6 +495,10 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         // vertices the lists are shorter than that and the guides' entry per
         // vertex would outweigh the edges
         const bool guides = n <= m;
+        const bool ranks = pair_ranks_kept(m);
+        for (int x = 0; x < 3 && ranks; ++x)
+            if (dev_alloc((void**)&opos[x], (size_t)m * sizeof(uint32_t), st) != hipSuccess)
+                return tm_fail(TM_ENOMEM, "graph: work arrays");
         const size_t guide_len = (size_t)guide_first(n, (int32_t)m) + 1;
         for (int dir = 0; dir < 2; ++dir) {
             TT* lt = nullptr;
@@ -502,18 +567,34 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             TM_TRY(arena_alloc(g->arena, &neid, m));
             int32_t* nguide = nullptr;
             if (guides) TM_TRY(arena_alloc(g->arena, &nguide, guide_len));
-            L in, out;
-            in.k = lnbr_of[other];
-            in.v0 = reinterpret_cast<V*>(ltab[other]);
-            in.v1 = reinterpret_cast<uint32_t*>(const_cast<int32_t*>(D.leid[other]));
-            in.v2 = own[other];
-            out.k = nkeys_out;
-            out.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(ntime32) : reinterpret_cast<V*>(nkey);
-            out.v1 = reinterpret_cast<uint32_t*>(neid);
-            out.v2 = nbr_carried;
-            TM_TRY(sort_into(in, out, tmp, m, 0, bn, 0, flags + 1, st));
+            auto sort_n = [&](auto set) -> int {
+                using S = decltype(set);
+                S in, out, buf;
+                in.k = lnbr_of[other];
+                in.v0 = reinterpret_cast<V*>(ltab[other]);
+                in.v1 = reinterpret_cast<uint32_t*>(const_cast<int32_t*>(D.leid[other]));
+                in.v2 = own[other];
+                out.k = nkeys_out;
+                out.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(ntime32) : reinterpret_cast<V*>(nkey);
+                out.v1 = reinterpret_cast<uint32_t*>(neid);
+                out.v2 = nbr_carried;
+                buf.k = tmp.k;
+                buf.v0 = tmp.v0;
+                buf.v1 = tmp.v1;
+                buf.v2 = tmp.v2;
+                int iota = 0;
+                if constexpr (!std::is_same<decltype(in.v3), SortNone*>::value) {
+                    out.v3 = opos[dir];
+                    buf.v3 = opos[2];
+                    iota = 8;  // the other list's positions: 0, 1, ...
+                }
+                return sort_into(in, out, buf, m, 0, bn, iota, flags + 1, st);
+            };
+            if (ranks) TM_TRY(sort_n(SortSet<uint32_t, V, uint32_t, uint32_t, uint32_t>{}));
+            else TM_TRY(sort_n(L{}));
+            const V* nt_sorted = sizeof(TT) == 4 ? reinterpret_cast<V*>(ntime32) : reinterpret_cast<V*>(nkey);
             hipLaunchKernelGGL((n_order_fix_kernel<V>), dim3(grid_for(m)), dim3(kBlock), 0, st,
-                               (const uint32_t*)nbr_carried, (const V*)out.v0, (const int32_t*)neid,
+                               (const uint32_t*)nbr_carried, nt_sorted, (const int32_t*)neid,
                                (const int32_t*)tpos[dir], (const uint32_t*)own[dir], D.off[dir], m, n, D.bt, bn,
                                D.nmul, nkey, nxref, nguide);
             if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: list launch");
@@ -521,6 +602,15 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             D.nxref[dir] = nxref;
             D.neid[dir] = neid;
             D.nguide[dir] = nguide;
+        }
+        if (ranks) {
+            uint4* rank[2] = {nullptr, nullptr};
+            for (uint4*& r : rank) TM_TRY(arena_alloc(g->arena, &r, m));
+            hipLaunchKernelGGL(pair_rank_kernel, dim3(grid_for(2 * m)), dim3(kBlock), 0, st, D,
+                               (const uint32_t*)own[0], (const uint32_t*)own[1], (const uint32_t*)opos[0],
+                               (const uint32_t*)opos[1], rank[0], rank[1]);
+            if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: rank launch");
+            for (int dir = 0; dir < 2; ++dir) D.nrank[dir] = rank[dir];
         }
         return TM_OK;
     };

@@ -51,7 +51,8 @@ struct SampleArgs {
     // position x is win[s][par][2 x] (the parities interleave), x the
     // parent's position in the T order of the list slot s attaches to
     // (side[s]); win_from[s]: the list the parent is drawn from, so that
-    // when the two differ the parent's position is looked up (leid, tpos)
+    // when the two differ the parent's position is looked up (nrank, or
+    // leid and tpos)
     const int4* win[kMaxSlots][2];
     int win_from[kMaxSlots];
     int has_win;
@@ -857,10 +858,16 @@ __device__ __forceinline__ void sample_positions(const SampleArgs& a, const Samp
                 int32_t wx = pick(posv, a.parent[s]);
                 if (a.win_from[s] != a.side[s]) {
                     // the parent was drawn from its other list: its position
-                    // in the list the windows follow, through its eid
-                    const int32_t pe = G.leid[a.win_from[s]][wx];
-                    wx = G.tpos[a.side[s]][pe];
-                    if constexpr (kCount) nb += 8;
+                    // in the list the windows follow (without the pair ranks
+                    // through its eid, two dependent reads)
+                    if (G.nrank[0]) {
+                        wx = (int32_t)G.nrank[a.win_from[s]][wx].z;
+                        if constexpr (kCount) nb += 4;
+                    } else {
+                        const int32_t pe = G.leid[a.win_from[s]][wx];
+                        wx = G.tpos[a.side[s]][pe];
+                        if constexpr (kCount) nb += 8;
+                    }
                 }
                 const int4 b = a.win[s][par][2 * (int64_t)wx];
                 w.p0 = b.x;

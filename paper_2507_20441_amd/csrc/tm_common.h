@@ -62,6 +62,13 @@ struct DevGraph {
     const int32_t* tpos[2];    // by eid: the edge's position in the T order
     const int32_t* tguide[2];  // T order: guide by time (null: graphs with more vertices than edges)
     const int32_t* nguide[2];  // N order: guide by neighbour (null likewise)
+    // By T position of list w (vertex g, neighbour o, time t): the edge's
+    // place in its lists' other orders -- x: its own position in the N order
+    // of list w; y: the first position in the N order of g's list 1 - w whose
+    // key is >= (o, t); z: its T position in list 1 - w; w: how far in time
+    // the nearest entries of o around those two N positions are (PairGaps).
+    // Null outside the sizes pair_ranks_kept names.
+    const uint4* nrank[2];
     int bn;                    // bits of a vertex id
     uint32_t tmul, nmul;       // slice scale of times and of neighbours (slice_scale)
 };
@@ -91,6 +98,25 @@ template <typename TT>
 __device__ __forceinline__ uint32_t time_frac(TT x, int bt, uint32_t mul) {
     if constexpr (sizeof(TT) == 4) return (uint32_t)(((u64)((uint32_t)x << (32 - bt)) * mul) >> 31);
     else return slice_frac((u64)x, bt, mul);
+}
+
+// Gaps in time from an edge to its pair's neighbouring edges, as lower bounds
+// in eight bits each (exponent and two bits below the leading one; kGapNone:
+// no such edge).  Byte 0, 1: the entries of the same pair before and after the
+// edge in its own list; byte 2, 3: those of the pair in the vertex's other
+// list before t and at or after t (that gap plus one, as it may be zero).
+constexpr uint32_t kGapNone = 255;
+TM_HD uint32_t gap_code(u64 gap) {  // gap >= 1
+    const int e = 63 - __builtin_clzll(gap);
+    const uint32_t frac = (uint32_t)(e >= 2 ? (gap >> (e - 2)) & 3 : (gap << (2 - e)) & 3);
+    const uint32_t c = (uint32_t)e * 4 + frac;
+    return c < kGapNone ? c : kGapNone - 1;
+}
+// The smallest gap with that code; above 2^62 for kGapNone.
+TM_HD int64_t gap_floor(uint32_t code) {
+    const int e = (int)(code >> 2) < 62 ? (int)(code >> 2) : 62;
+    const u64 v = (u64)(4 + (code & 3));
+    return (int64_t)(e >= 2 ? v << (e - 2) : v >> (2 - e));
 }
 
 // ---------------------------------------------------------------------------

@@ -322,7 +322,7 @@ __device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t* ws
 }
 
 // ---------------------------------------------------------------------------
-// Stable LSD radix sort of keys that carry up to three value arrays
+// Stable LSD radix sort of keys that carry up to four value arrays
 // (structure of arrays), one kernel per digit of up to 8 bits:
 //  * sort_hist_kernel counts the digits of every pass in one read of the
 //    keys, and sort_base_kernel turns those counts into each digit's first
@@ -386,8 +386,8 @@ struct SortSize<SortNone> {
 };
 
 struct SortIO {
-    const void* in[4];  // keys, then the value arrays
-    void* out[4];
+    const void* in[5];  // keys, then the value arrays
+    void* out[5];
 };
 
 template <typename K>
@@ -450,12 +450,12 @@ __device__ __forceinline__ void sort_move_values(const void* vin, void* vout, bo
     }
 }
 
-template <typename K, typename V0, typename V1, typename V2>
+template <typename K, typename V0, typename V1, typename V2, typename V3>
 __global__ void __launch_bounds__(kBlock)
 sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int iota, const uint32_t* __restrict__ starts,
                  uint32_t* __restrict__ ticket, u64* __restrict__ status, int* __restrict__ err) {
     constexpr size_t kElt = std::max(std::max(sizeof(K), SortSize<V0>::value),
-                                     std::max(SortSize<V1>::value, SortSize<V2>::value));
+                                     std::max(std::max(SortSize<V1>::value, SortSize<V2>::value), SortSize<V3>::value));
     __shared__ __align__(16) unsigned char sbuf[kElt * kSortTile];
     __shared__ uint8_t sdig[kSortTile];
     // per wave and digit: counts, then tile-local starts, at most kSortTile
@@ -599,15 +599,17 @@ sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int io
     sort_move_values<V0>(io.in[1], io.out[1], iota & 1, wbase, lane, n, lp, sbuf, sdig, gofs, tn);
     sort_move_values<V1>(io.in[2], io.out[2], iota & 2, wbase, lane, n, lp, sbuf, sdig, gofs, tn);
     sort_move_values<V2>(io.in[3], io.out[3], iota & 4, wbase, lane, n, lp, sbuf, sdig, gofs, tn);
+    sort_move_values<V3>(io.in[4], io.out[4], iota & 8, wbase, lane, n, lp, sbuf, sdig, gofs, tn);
 }
 
-// A key array and up to three value arrays (null where a value is absent).
-template <typename K, typename V0 = SortNone, typename V1 = SortNone, typename V2 = SortNone>
+// A key array and up to four value arrays (null where a value is absent).
+template <typename K, typename V0 = SortNone, typename V1 = SortNone, typename V2 = SortNone, typename V3 = SortNone>
 struct SortSet {
     K* k = nullptr;
     V0* v0 = nullptr;
     V1* v1 = nullptr;
     V2* v2 = nullptr;
+    V3* v3 = nullptr;
 };
 
 // Runs the plan's passes: pass p reads `in` (p = 0) or the previous pass's
@@ -616,8 +618,8 @@ struct SortSet {
 // index of the buffer that holds the result.  iota: bit j set, value array j
 // holds nothing yet and stands for 0, 1, ..., n - 1.  scratch: at least
 // sort_scratch_bytes(n) bytes, or null to allocate it here.
-template <typename K, typename V0, typename V1, typename V2>
-int sort_run(const SortSet<K, V0, V1, V2>& in, const SortSet<K, V0, V1, V2> (&bufs)[2], int64_t n,
+template <typename K, typename V0, typename V1, typename V2, typename V3>
+int sort_run(const SortSet<K, V0, V1, V2, V3>& in, const SortSet<K, V0, V1, V2, V3> (&bufs)[2], int64_t n,
              const SortPlan& P, int iota, int* err, hipStream_t st, void* scratch, int* result) {
     *result = (P.npass - 1) & 1;
     if (n <= 0 || P.npass <= 0) return TM_OK;
@@ -640,10 +642,10 @@ int sort_run(const SortSet<K, V0, V1, V2>& in, const SortSet<K, V0, V1, V2> (&bu
         if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "sort: digit start launch");
     }
     for (int p = 0; p < P.npass && rc == TM_OK; ++p) {
-        const SortSet<K, V0, V1, V2>& src = p == 0 ? in : bufs[(p - 1) & 1];
-        const SortSet<K, V0, V1, V2>& dst = bufs[p & 1];
-        SortIO io{{src.k, src.v0, src.v1, src.v2}, {dst.k, dst.v0, dst.v1, dst.v2}};
-        hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2>), dim3((unsigned)ntiles), dim3(kBlock), 0, st, io, n,
+        const SortSet<K, V0, V1, V2, V3>& src = p == 0 ? in : bufs[(p - 1) & 1];
+        const SortSet<K, V0, V1, V2, V3>& dst = bufs[p & 1];
+        SortIO io{{src.k, src.v0, src.v1, src.v2, src.v3}, {dst.k, dst.v0, dst.v1, dst.v2, dst.v3}};
+        hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, V3>), dim3((unsigned)ntiles), dim3(kBlock), 0, st, io, n,
                            P.shift[p], P.bits[p], (uint32_t)(p + 1), p == 0 ? iota : 0,
                            (const uint32_t*)(ghist + p * kSortDigits), tickets + p, status, err);
         if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "sort: pass launch");
@@ -659,9 +661,9 @@ int sort_run(const SortSet<K, V0, V1, V2>& in, const SortSet<K, V0, V1, V2> (&bu
 // `tmp` as the other buffer of the passes (`in` is left as it was unless
 // tmp is `in`, which is allowed only when an odd number of passes runs).  At
 // least one pass runs: a stable copy when no bit is sorted.
-template <typename K, typename V0, typename V1, typename V2>
-int sort_into(const SortSet<K, V0, V1, V2>& in, const SortSet<K, V0, V1, V2>& out,
-              const SortSet<K, V0, V1, V2>& tmp, int64_t n, int lo_bit, int nbits, int iota, int* err,
+template <typename K, typename V0, typename V1, typename V2, typename V3>
+int sort_into(const SortSet<K, V0, V1, V2, V3>& in, const SortSet<K, V0, V1, V2, V3>& out,
+              const SortSet<K, V0, V1, V2, V3>& tmp, int64_t n, int lo_bit, int nbits, int iota, int* err,
               hipStream_t st) {
     SortPlan P = sort_plan(lo_bit, nbits);
     if (P.npass == 0) {
@@ -669,7 +671,7 @@ int sort_into(const SortSet<K, V0, V1, V2>& in, const SortSet<K, V0, V1, V2>& ou
         P.shift[0] = 0;
         P.bits[0] = 0;
     }
-    const SortSet<K, V0, V1, V2> bufs[2] = {(P.npass & 1) ? out : tmp, (P.npass & 1) ? tmp : out};
+    const SortSet<K, V0, V1, V2, V3> bufs[2] = {(P.npass & 1) ? out : tmp, (P.npass & 1) ? tmp : out};
     int res = 0;
     return sort_run(in, bufs, n, P, iota, err, st, nullptr, &res);
 }

@@ -36,6 +36,12 @@ struct ChildDesc {
     const void* qn[2];
 };
 
+// An edge's products of both interval parities.
+template <typename W>
+struct alignas(2 * sizeof(W) > 16 ? 16 : 2 * sizeof(W)) Products {
+    W v[2];
+};
+
 struct LevelArgs {
     DevGraph G;
     int64_t delta;
@@ -45,9 +51,9 @@ struct LevelArgs {
     ChildDesc c[kMaxSlots];
     int walk;          // -1: eid order; 0 / 1: the T order of the out- / in-lists
     int4* win[kMaxSlots][2];  // per child and parity: its windows, stride 2, by walk position (null: not kept)
-    void* out[2];      // per parity (interleaved, stride 2): by eid, or by T position in list out_pos_dir
+    void* out;         // Products records: by eid, or by T position in list out_pos_dir
     int out_pos_dir;   // first of two passes: its own walk (consecutive writes), else -1
-    const void* in[2]; // second of two passes: the first pass's products ...
+    const void* in;    // second of two passes: the first pass's products ...
     int in_pos_dir;    // ... by T position in this list
     int* ovf;
     unsigned long long* nbytes;  // counting variant: access-model bytes of the launch
@@ -125,6 +131,30 @@ __device__ __forceinline__ int32_t key_gallop(const u64* nk, int32_t s, int32_t 
         n -= h;
     }
     return lo + 1;
+}
+
+// The same going back: the first position in [a, s] with no entry from it to
+// s before kx; every position from s on is at or past kx.
+__device__ __forceinline__ int32_t key_gallop_back(const u64* nk, int32_t a, int32_t s, u64 kx) {
+    if (s <= a || nk[s - 1] < kx) return s;
+    int32_t hi = s - 1, lo, step = 1;
+    while (true) {
+        lo = hi - step;
+        if (lo < a) {
+            lo = a - 1;
+            break;
+        }
+        if (nk[lo] < kx) break;
+        hi = lo;
+        step <<= 1;
+    }
+    // lo is before kx (or a - 1), hi is not
+    while (hi - lo > 1) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (nk[mid] < kx) lo = mid;
+        else hi = mid;
+    }
+    return hi;
 }
 
 // The indices of a child's bounds in nondecreasing order of x (Kind 0: a
@@ -209,9 +239,20 @@ __device__ __forceinline__ void lockstep_lower(const DevGraph& G, const TT* lt, 
     if constexpr (kN) q = cq;
 }
 
+// rank: where the walked edge's (o, t) falls in the N order of list dir, and
+// gaps: the least gaps in time to o's entries around it (DevGraph::nrank, two
+// bytes; own: list dir is the walked list, which holds the edge itself); not
+// ranked: searched for.  A pair's entries are mostly further apart than
+// delta: the bounds then follow from the rank with no probe, and the others
+// lie a few entries from it.  (Searching o's run put each lane on lines of
+// its own.  With the T position in the other list read from the same record
+// instead of through the eid -- 4 bytes of a random line per edge -- the seven
+// level launches of the 1e8-edge workload went from 64.6 to 45.1 ms, the nine
+// of a tree choice at 2e6 edges from 1.06 to 0.79 ms.)
 template <int NB, int Kind>
-__device__ __forceinline__ BoundsN<NB> level_bounds(const DevGraph& G, int dir, int32_t g, int32_t o,
-                                                    const int64_t (&xs)[NB], bool exclude) {
+__device__ __forceinline__ BoundsN<NB> level_bounds(const DevGraph& G, int dir, int32_t g, int32_t o, int64_t t,
+                                                    const int64_t (&xs)[NB], bool exclude, bool ranked, int32_t rank,
+                                                    uint32_t gaps, bool own) {
     const int32_t a = sel2(G.off, dir)[g], b = sel2(G.off, dir)[g + 1];
     const u64* nk = sel2(G.nkey, dir);
     int64_t x[NB];
@@ -225,8 +266,8 @@ __device__ __forceinline__ BoundsN<NB> level_bounds(const DevGraph& G, int dir, 
         for (int j = 0; j < NB; ++j) r.p[j] = r.q[j] = a;
         return r;
     }
-    if (!exclude) {
-        // T order only: no excluded run
+    if (!exclude || ranked) {
+        // T order only: no excluded run, or its bounds come from the rank
         int32_t unused = a;
         if (lt32)
             lockstep_lower<uint32_t, NB, false>(G, lt32, dir, g, a, b, x, r.p, nk, 0, false, o, unused);
@@ -234,6 +275,26 @@ __device__ __forceinline__ BoundsN<NB> level_bounds(const DevGraph& G, int dir, 
             lockstep_lower<int64_t, NB, false>(G, sel2(G.lt, dir), dir, g, a, b, x, r.p, nk, 0, false, o, unused);
 #pragma unroll
         for (int j = 0; j < NB; ++j) r.q[j] = a;
+        if (!exclude) return r;
+        // bounds at or before t back from the rank, the later ones on from it
+        constexpr int nback = Kind == 1 ? 1 : 2;  // (kind 1: the first bound is t itself)
+        const u64 base = (u64)o << G.bt;
+        const int64_t prev = gap_floor(gaps & 255u), next = gap_floor((gaps >> 8) & 255u) - (own ? 0 : 1);
+        int32_t s = rank;
+        sfor<0, nback>([&](auto kc) {
+            constexpr int j = bound_rank<Kind>(nback - 1 - decltype(kc)::value);
+            // (t - x <= prev - 1: the entry before lies before x)
+            if constexpr (Kind != 1)
+                if (t - x[j] >= prev) s = key_gallop_back(nk, a, s, base + (u64)x[j]);
+            r.q[j] = s;
+        });
+        s = rank + (own ? 1 : 0);
+        sfor<nback, NB>([&](auto kc) {
+            constexpr int j = bound_rank<Kind>(decltype(kc)::value);
+            // (x - t <= next: the entry after lies at x or later)
+            if (x[j] - t > next) s = key_gallop(nk, s, b, base + (u64)(x[j] > G.T ? G.T : x[j]), x[j] > G.T);
+            r.q[j] = s;
+        });
         return r;
     }
     // N order: all of the lane's keys share the excluded neighbour o; the
@@ -317,11 +378,20 @@ __device__ __forceinline__ u64 level_edge(const LevelArgs& a, int64_t p) {
     const int64_t blk = t / a.ilen;
     const bool hasB = blk >= 1;
     const int parA = (int)(blk & 1), parB = parA ^ 1;
+    // where the excluded neighbour's runs lie (pairs of the walked edge)
+    const uint4* nrank = a.walk < 0 ? nullptr : sel2(G.nrank, a.walk);
+    const bool ranked = nrank != nullptr;
+    const uint4 rk = ranked ? nrank[p] : make_uint4(0, 0, 0, 0);
+    // the edge's T position in list dir
+    auto pos_in = [&](int dir) -> int64_t {
+        return dir == a.walk ? p : (ranked ? (int64_t)rk.z : (int64_t)sel2(G.tpos, dir)[e]);
+    };
     W prodA = 1, prodB = hasB ? (W)1 : (W)0;
-    if (a.in[0]) {
-        const int64_t ip = a.in_pos_dir == a.walk ? p : (int64_t)sel2(G.tpos, a.in_pos_dir)[e];
-        prodA = static_cast<const W*>(sel2(a.in, parA))[2 * ip];
-        prodB = hasB ? static_cast<const W*>(sel2(a.in, parB))[2 * ip] : (W)0;
+    if (a.in) {
+        const int64_t ip = pos_in(a.in_pos_dir);
+        const Products<W> in = static_cast<const Products<W>*>(a.in)[ip];
+        prodA = parA ? in.v[1] : in.v[0];
+        prodB = hasB ? (parA ? in.v[0] : in.v[1]) : (W)0;
         if constexpr (kCount) nb += (a.in_pos_dir == a.walk ? 0 : 4) + sizeof(W) * (hasB ? 2 : 1);
     }
     bool ovf = false;
@@ -344,7 +414,9 @@ __device__ __forceinline__ u64 level_edge(const LevelArgs& a, int64_t p) {
             xs[1] = lo > (blk - 1) * a.ilen ? lo : (blk - 1) * a.ilen;
             xs[2] = (hi < (blk + 2) * a.ilen - 1 ? hi : (blk + 2) * a.ilen - 1) + 1;
             xs[3] = (hi < (blk + 1) * a.ilen - 1 ? hi : (blk + 1) * a.ilen - 1) + 1;
-            r = level_bounds<4, 2>(G, d.dir, g, o, xs, a.exclude != 0);
+            const bool own = d.dir == a.walk;
+            r = level_bounds<4, 2>(G, d.dir, g, o, t, xs, a.exclude != 0, ranked, (int32_t)(own ? rk.x : rk.y),
+                                   own ? rk.w : rk.w >> 16, own);
             if constexpr (kCount) {
                 int it = 0;
                 for (int32_t n = r.len; n > 1; n -= n >> 1) ++it;
@@ -366,8 +438,12 @@ __device__ __forceinline__ u64 level_edge(const LevelArgs& a, int64_t p) {
                 xs[1] = (hi < (blk + 2) * a.ilen - 1 ? hi : (blk + 2) * a.ilen - 1) + 1;
                 xs[2] = (hi < (blk + 1) * a.ilen - 1 ? hi : (blk + 1) * a.ilen - 1) + 1;
             }
-            const BoundsN<3> r3 = d.beta < 0 ? level_bounds<3, 0>(G, d.dir, g, o, xs, a.exclude != 0)
-                                             : level_bounds<3, 1>(G, d.dir, g, o, xs, a.exclude != 0);
+            const bool own = d.dir == a.walk;
+            const int32_t rank = (int32_t)(own ? rk.x : rk.y);
+            const uint32_t gaps = own ? rk.w : rk.w >> 16;
+            const BoundsN<3> r3 =
+                d.beta < 0 ? level_bounds<3, 0>(G, d.dir, g, o, t, xs, a.exclude != 0, ranked, rank, gaps, own)
+                           : level_bounds<3, 1>(G, d.dir, g, o, t, xs, a.exclude != 0, ranked, rank, gaps, own);
             // before: (p0, p1, p2, p2); after: (p0, p0, p1, p2)
             const bool bef = d.beta < 0;
             r.p[0] = r3.p[0];
@@ -407,9 +483,13 @@ __device__ __forceinline__ u64 level_edge(const LevelArgs& a, int64_t p) {
             if (!mul_ok(prodB, xb, &prodB)) ovf = true;
         }
     });
-    const int64_t at = a.out_pos_dir < 0 ? (int64_t)e : (a.out_pos_dir == a.walk ? p : (int64_t)sel2(G.tpos, a.out_pos_dir)[e]);
-    static_cast<W*>(sel2(a.out, parA))[2 * at] = prodA;
-    static_cast<W*>(sel2(a.out, parB))[2 * at] = hasB ? prodB : (W)0;
+    const int64_t at = a.out_pos_dir < 0 ? (int64_t)e : pos_in(a.out_pos_dir);
+    // (one store of the whole record: the position may be scattered)
+    if (!hasB) prodB = 0;
+    Products<W> out;
+    out.v[0] = parA ? prodB : prodA;
+    out.v[1] = parA ? prodA : prodB;
+    static_cast<Products<W>*>(a.out)[at] = out;
     if constexpr (kCount) nb += 2 * sizeof(W) + (a.out_pos_dir < 0 || a.out_pos_dir == a.walk ? 0 : 4);
     if (ovf) atomicOr(a.ovf, 4);
     return nb;
@@ -726,13 +806,11 @@ int build_typed(tm_weights* w, hipStream_t st, int* ovf, int* ovf_c, bool check_
                 // neighbouring lanes search one list (the center's root list
                 // is that list too when all its children attach at one end);
                 // the kept windows are written in that walk order, and the
-                // sampler finds a parent's walk position through tpos when it
+                // sampler finds a parent's walk position by a lookup when it
                 // drew the parent from the other list
                 a.walk = a.nc == 0 ? -1 : side;
-                for (int par = 0; par < 2; ++par) {
-                    a.out[par] = ((two && pass == 0) ? tmp : static_cast<W*>(w->vals[s][0])) + par;
-                    a.in[par] = (two && pass == 1) ? (const void*)(tmp + par) : nullptr;
-                }
+                a.out = (two && pass == 0) ? (void*)tmp : w->vals[s][0];
+                a.in = (two && pass == 1) ? (const void*)tmp : nullptr;
                 // the first of two passes leaves its products in its own walk
                 // order; the second gathers them
                 // a non-center slot's values land at its T-order position in
