@@ -166,140 +166,266 @@ int device_exclusive_scan(F f, int64_t n, T* out, int* ovf, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// Two exclusive scans in one pass: f(i) returns the i-th value of both
-// sequences (a Pair2), so a record holding both is read once.  Same outputs
-// and flags as two device_exclusive_scan calls.
+// Pairs of exclusive scans: a job scans two sequences at once, f(i) giving the
+// i-th value of both (a Pair2), so a record holding both is read once; the
+// jobs of a call (same length) share their launches.  Sums run in T, whose
+// wrapping leaves the low bits of the exact sums; a sum that does not fit T
+// sets bit 2 (64-bit) or bit 1 (128-bit) of *ovf.
+//
+// Two launches up to kScanSelfTiles tiles: the tile sums, then the tiles, each
+// block adding up the sums before its own.  (Four launches, with a launch of
+// one block per sequence between them, spent more on the gaps than on the
+// values: a slot's two scans and its coarse entries at 1e6 edges, 60 us busy in
+// ten launches, take 25 us in two.)  Above that, one more launch scans the
+// tile sums in groups and a block adds up the groups before its own.
 // ---------------------------------------------------------------------------
 template <typename V>
 struct Pair2 {
     V a, b;
 };
 
-template <typename F>
-__global__ void __launch_bounds__(kBlock) scan2_tiles_kernel(F f, int64_t n, u128* part0, u128* part1, int* ovf) {
+constexpr int kScanJobs = 2;
+constexpr int64_t kScanSelfTiles = 2048;
+
+template <typename T, typename F>
+struct Scan2Job {
+    F f;
+    T* out0;  // [n + 1] each
+    T* out1;
+    T* c0;    // every 2^kCoarseBits-th entry of out0 and out1, or null
+    T* c1;
+};
+
+template <typename T, typename F>
+struct Scan2Args {
+    Scan2Job<T, F> job[kScanJobs];
+    T* part;  // per job and sequence, len entries: the tile sums; unless self,
+              // scanned in groups, and after them the groups' sums
+    int64_t n, nb, len;
+    int self;
+    int* ovf;
+};
+
+// Of two kernel arguments, as a select between the two loaded values: an index
+// into the kernel's arguments has the compiler copy them to scratch, and so
+// does a plain select, which the optimiser may turn back into a select of the
+// two addresses.  The empty asm statement pins both in scalar registers first
+// (arguments are uniform across the wave).
+template <typename P>
+__device__ __forceinline__ P pick_arg(P x0, P x1, int i) {
+    asm("" : "+s"(x0), "+s"(x1));
+    return i ? x1 : x0;
+}
+
+// The block's job (blockIdx.y); F::pick selects between two functors.
+template <typename T, typename F>
+__device__ __forceinline__ Scan2Job<T, F> scan2_job(const Scan2Args<T, F>& a) {
+    static_assert(kScanJobs == 2, "one select");
+    const int y = blockIdx.y;
+    return {F::pick(a.job[0].f, a.job[1].f, y), pick_arg(a.job[0].out0, a.job[1].out0, y),
+            pick_arg(a.job[0].out1, a.job[1].out1, y), pick_arg(a.job[0].c0, a.job[1].c0, y),
+            pick_arg(a.job[0].c1, a.job[1].c1, y)};
+}
+
+template <typename T>
+__device__ __forceinline__ T add_carry(T x, T y, bool& carry) {
+    const T s = x + y;
+    carry = carry || s < x;
+    return s;
+}
+
+template <typename T>
+__device__ __forceinline__ T shfl_up_word(T v, int d) {
+    if constexpr (sizeof(T) == 16) return shfl_up_u128(v, d);
+    else return __shfl_up(v, d, 64);
+}
+
+// Exclusive scan of v over the lanes of a block of kW waves; *total the sum.
+template <typename T, int kW = kWaves>
+__device__ __forceinline__ T block_exclusive_t(T v, T* total, bool& carry) {
+    __shared__ T wsum[kW];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    T inc = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const T o = shfl_up_word<T>(inc, d);
+        if (lane >= d) inc = add_carry(inc, o, carry);
+    }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    T before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < kW; ++w) {
+        const T x = wsum[w];
+        if (w < wave) before += x;
+        all = add_carry(all, x, carry);
+    }
+    __syncthreads();
+    *total = all;
+    return before + inc - v;
+}
+
+template <typename T, typename F>
+__global__ void __launch_bounds__(kBlock) scan2_tiles_kernel(Scan2Args<T, F> args) {
+    const Scan2Job<T, F> job = scan2_job(args);
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    u128 s0 = 0, s1 = 0;
+    T s0 = 0, s1 = 0;
     bool carry = false;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         const int64_t i = base + (int64_t)k * kBlock + threadIdx.x;
-        if (i < n) {
-            const auto x = f(i);
-            const u128 y0 = s0 + to_u128(x.a), y1 = s1 + to_u128(x.b);
-            if (y0 < s0 || y1 < s1) carry = true;
-            s0 = y0;
-            s1 = y1;
+        if (i < args.n) {
+            const auto x = job.f(i);
+            s0 = add_carry<T>(s0, x.a, carry);
+            s1 = add_carry<T>(s1, x.b, carry);
         }
     }
-    u128 tot0, tot1;
-    block_exclusive(s0, &tot0, &carry);
-    block_exclusive(s1, &tot1, &carry);
+    T tot0, tot1;
+    block_exclusive_t<T>(s0, &tot0, carry);
+    block_exclusive_t<T>(s1, &tot1, carry);
     if (threadIdx.x == 0) {
-        part0[blockIdx.x] = tot0;
-        part1[blockIdx.x] = tot1;
+        T* part = args.part + 2 * (int64_t)blockIdx.y * args.len;
+        part[blockIdx.x] = tot0;
+        part[args.len + blockIdx.x] = tot1;
     }
-    if (carry) atomicOr(ovf, 1);
+    if (carry) atomicOr(args.ovf, sizeof(T) == 8 ? 2 : 1);
+}
+
+// Tile sums in groups of kBlock: each group into exclusive prefixes, in place,
+// and its sum after the sequence's tile sums.
+template <typename T>
+__global__ void __launch_bounds__(kBlock) scan2_parts_kernel(T* parts, int64_t nb, int64_t len, int* ovf) {
+    T* part = parts + (int64_t)blockIdx.y * len;
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    bool carry = false;
+    T total;
+    const T at = block_exclusive_t<T>(i < nb ? part[i] : (T)0, &total, carry);
+    if (i < nb) part[i] = at;
+    if (threadIdx.x == 0) part[nb + blockIdx.x] = total;
+    if (carry) atomicOr(ovf, sizeof(T) == 8 ? 2 : 1);
 }
 
 template <typename T, typename F>
-__global__ void __launch_bounds__(kBlock)
-scan2_apply_kernel(F f, int64_t n, const u128* part0, const u128* part1, T* out0, T* out1, int* ovf) {
-    using V = decltype(f(0).a);
+__global__ void __launch_bounds__(kBlock) scan2_apply_kernel(Scan2Args<T, F> args) {
+    const Scan2Job<T, F> job = scan2_job(args);
     // Values come in and results go out in rounds of kBlock consecutive
     // entries (coalesced), through LDS; in between each lane scans a run of
     // kScanItems consecutive entries.  Entry j of the tile sits at LDS
     // position j + j / kScanItems, so that the lanes reading their runs do
     // not all fall on the same banks.
     constexpr int kPad = kScanTile + kScanTile / kScanItems;
-    constexpr size_t kElt = sizeof(V) > sizeof(T) ? sizeof(V) : sizeof(T);
-    __shared__ __align__(16) unsigned char sbuf[2 * kPad * kElt];
+    __shared__ __align__(16) unsigned char sbuf[2 * kPad * sizeof(T)];
     const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    V* lv0 = reinterpret_cast<V*>(sbuf);
-    V* lv1 = lv0 + kPad;
+    const int64_t n = args.n;
+    T* l0 = reinterpret_cast<T*>(sbuf);
+    T* l1 = l0 + kPad;
+    const T* part0 = args.part + 2 * (int64_t)blockIdx.y * args.len;
+    const T* part1 = part0 + args.len;
+    bool carry = false;
+    T before0 = 0, before1 = 0;
+    // the sums of the tiles before this one, or of the groups before its own
+    const int64_t pfirst = args.self ? 0 : args.nb;
+    const int64_t pcount = args.self ? (int64_t)blockIdx.x : (int64_t)blockIdx.x / kBlock;
+    for (int64_t i = threadIdx.x; i < pcount; i += kBlock) {
+        before0 = add_carry<T>(before0, part0[pfirst + i], carry);
+        before1 = add_carry<T>(before1, part1[pfirst + i], carry);
+    }
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         const int j = k * kBlock + (int)threadIdx.x;
         const int64_t i = base + j;
-        V a = 0, b = 0;
+        T a = 0, b = 0;
         if (i < n) {
-            const auto x = f(i);
+            const auto x = job.f(i);
             a = x.a;
             b = x.b;
         }
-        lv0[j + j / kScanItems] = a;
-        lv1[j + j / kScanItems] = b;
+        l0[j + j / kScanItems] = a;
+        l1[j + j / kScanItems] = b;
+    }
+    {
+        T t0, t1;
+        block_exclusive_t<T>(before0, &t0, carry);
+        block_exclusive_t<T>(before1, &t1, carry);
+        before0 = t0;
+        before1 = t1;
+    }
+    if (!args.self) {
+        before0 = add_carry<T>(before0, part0[blockIdx.x], carry);
+        before1 = add_carry<T>(before1, part1[blockIdx.x], carry);
     }
     __syncthreads();
-    u128 v0[kScanItems], v1[kScanItems];
-    u128 s0 = 0, s1 = 0;
-    bool carry = false;
+    // (a lane's run stays its own until the last round: the values are read
+    // again rather than held, for registers)
+    const int lane0 = (int)threadIdx.x * (kScanItems + 1);
+    T s0 = 0, s1 = 0;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
-        const int j = (int)threadIdx.x * kScanItems + k;
-        v0[k] = to_u128(lv0[j + j / kScanItems]);
-        v1[k] = to_u128(lv1[j + j / kScanItems]);
-        const u128 y0 = s0 + v0[k], y1 = s1 + v1[k];
-        if (y0 < s0 || y1 < s1) carry = true;
-        s0 = y0;
-        s1 = y1;
+        s0 += l0[lane0 + k];
+        s1 += l1[lane0 + k];
     }
-    u128 tot0, tot1;
-    u128 run0 = part0[blockIdx.x] + block_exclusive(s0, &tot0, &carry);
-    u128 run1 = part1[blockIdx.x] + block_exclusive(s1, &tot1, &carry);
-    __syncthreads();  // every lane has read its values: the buffer takes the results
-    T* lo0 = reinterpret_cast<T*>(sbuf);
-    T* lo1 = lo0 + kPad;
+    T tot0, tot1;
+    T run0 = before0 + block_exclusive_t<T>(s0, &tot0, carry);
+    T run1 = before1 + block_exclusive_t<T>(s1, &tot1, carry);
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
-        const int j = (int)threadIdx.x * kScanItems + k;
-        lo0[j + j / kScanItems] = (T)run0;
-        lo1[j + j / kScanItems] = (T)run1;
-        const u128 y0 = run0 + v0[k], y1 = run1 + v1[k];
-        if (y0 < run0 || y1 < run1) carry = true;
-        run0 = y0;
-        run1 = y1;
+        const T x = l0[lane0 + k], y = l1[lane0 + k];
+        l0[lane0 + k] = run0;
+        l1[lane0 + k] = run1;
+        run0 += x;
+        run1 += y;
     }
     __syncthreads();
+    constexpr int64_t kCoarse = (int64_t)1 << kCoarseBits;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         const int j = k * kBlock + (int)threadIdx.x;
         const int64_t i = base + j;
         if (i < n) {
-            out0[i] = lo0[j + j / kScanItems];
-            out1[i] = lo1[j + j / kScanItems];
+            const T x = l0[j + j / kScanItems], y = l1[j + j / kScanItems];
+            job.out0[i] = x;
+            job.out1[i] = y;
+            if (job.c0 && (i & (kCoarse - 1)) == 0) {
+                job.c0[i >> kCoarseBits] = x;
+                job.c1[i >> kCoarseBits] = y;
+            }
         }
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        const u128 t0 = part0[gridDim.x], t1 = part1[gridDim.x];
-        out0[n] = (T)t0;
-        out1[n] = (T)t1;
-        if ((u128)(T)t0 != t0 || (u128)(T)t1 != t1) atomicOr(ovf, 2);  // a total does not fit T
+        // (the tile sums' wraps are flagged where they are added up)
+        const T t0 = add_carry<T>(before0, tot0, carry), t1 = add_carry<T>(before1, tot1, carry);
+        job.out0[n] = t0;
+        job.out1[n] = t1;
+        if (job.c0 && (n & (kCoarse - 1)) == 0) {
+            job.c0[n >> kCoarseBits] = t0;
+            job.c1[n >> kCoarseBits] = t1;
+        }
     }
-    if (carry) atomicOr(ovf, 1);
+    if (carry) atomicOr(args.ovf, sizeof(T) == 8 ? 2 : 1);
 }
 
 template <typename T, typename F>
-int device_exclusive_scan2(F f, int64_t n, T* out0, T* out1, int* ovf, hipStream_t st) {
-    if (n == 0) {
-        static_assert(sizeof(T) % 4 == 0, "scan outputs are whole words");
-        TM_TRY(fill_u32(out0, sizeof(T) / 4, 0u, st));
-        return fill_u32(out1, sizeof(T) / 4, 0u, st);
-    }
-    const int64_t nb = (n + kScanTile - 1) / kScanTile;
-    u128* part = nullptr;
-    TM_HIP(dev_alloc((void**)&part, 2 * (nb + 1) * sizeof(u128), st));
-    u128* part1 = part + nb + 1;
-    hipLaunchKernelGGL((scan2_tiles_kernel<F>), dim3((unsigned)nb), dim3(kBlock), 0, st, f, n, part, part1, ovf);
-    TM_HIP(hipGetLastError());
-    int rc = scan_parts(part, nb, ovf, st);
-    if (rc == TM_OK) rc = scan_parts(part1, nb, ovf, st);
-    if (rc == TM_OK) {
-        hipLaunchKernelGGL((scan2_apply_kernel<T, F>), dim3((unsigned)nb), dim3(kBlock), 0, st, f, n,
-                           (const u128*)part, (const u128*)part1, out0, out1, ovf);
-        TM_HIP(hipGetLastError());
-    }
-    TM_HIP(dev_free(part, st));
-    return rc;
+int device_exclusive_scan2(const Scan2Job<T, F>* jobs, int njobs, int64_t n, int* ovf, hipStream_t st) {
+    if (njobs <= 0 || njobs > kScanJobs || n <= 0) return tm_fail(TM_EDEVICE, "scan: %d jobs", njobs);
+    Scan2Args<T, F> a;
+    for (int j = 0; j < kScanJobs; ++j) a.job[j] = jobs[j < njobs ? j : 0];
+    a.n = n;
+    a.nb = (n + kScanTile - 1) / kScanTile;
+    a.self = a.nb <= kScanSelfTiles ? 1 : 0;
+    a.ovf = ovf;
+    const int64_t groups = (a.nb + kBlock - 1) / kBlock;
+    a.len = a.nb + groups;
+    TM_HIP(dev_alloc((void**)&a.part, (size_t)(2 * njobs) * a.len * sizeof(T), st));
+    const dim3 grid((unsigned)a.nb, (unsigned)njobs);
+    hipLaunchKernelGGL((scan2_tiles_kernel<T, F>), grid, dim3(kBlock), 0, st, a);
+    if (!a.self)
+        hipLaunchKernelGGL((scan2_parts_kernel<T>), dim3((unsigned)groups, 2 * (unsigned)njobs), dim3(kBlock), 0, st,
+                           a.part, a.nb, a.len, ovf);
+    hipLaunchKernelGGL((scan2_apply_kernel<T, F>), grid, dim3(kBlock), 0, st, a);
+    const hipError_t e = hipGetLastError();
+    TM_HIP(dev_free(a.part, st));
+    TM_HIP(e);
+    return TM_OK;
 }
 
 // Exclusive scan of v over the block's 256 threads (thread t holds entry t):

@@ -59,17 +59,10 @@ struct LevelArgs {
     unsigned long long* nbytes;  // counting variant: access-model bytes of the launch
 };
 
-// Element i (0 or 1) of a two-entry argument array, as a select between the
-// two loaded values: indexing the kernel's argument arrays at run time had
-// the compiler copy all of its arguments to scratch, and so did a plain
-// select, which the optimiser may turn back into a select of the two
-// addresses.  The empty asm statement pins both values in scalar registers
-// first (the arrays are kernel arguments: uniform across the wave).
+// Element i (0 or 1) of a two-entry argument array (see pick_arg).
 template <typename T>
 __device__ __forceinline__ T sel2(const T (&arr)[2], int i) {
-    T x0 = arr[0], x1 = arr[1];
-    asm("" : "+s"(x0), "+s"(x1));
-    return i ? x1 : x0;
+    return pick_arg(arr[0], arr[1], i);
 }
 
 template <int B, int E, typename F>
@@ -515,38 +508,51 @@ __global__ void __launch_bounds__(kBlock) level_kernel(LevelArgs a) {
     }
 }
 
-// Values of one parity held in a list's T order, read in that list's N
-// order (through the N-to-T cross index, which stays inside each vertex's
-// list).
-// (Level values interleave their two parities, one record per position:
-// both parities' scans run together and read each record once.)
+// The products of both parities, at their own positions or (at not null) in
+// another order: a list's T-order values in its N order go through the N-to-T
+// cross index, which stays inside each vertex's list.
 template <typename W>
-struct ListGather {
-    const W* val;
+struct Values {
+    const Products<W>* val;
     const int32_t* at;
     __device__ Pair2<W> operator()(int64_t p) const {
-        const W* r = val + 2 * (int64_t)at[p];
-        return {r[0], r[1]};
+        const Products<W> r = val[at ? (int64_t)at[p] : p];
+        return {r.v[0], r.v[1]};
+    }
+    static __device__ __forceinline__ Values pick(const Values& x, const Values& y, int i) {
+        return {pick_arg(x.val, y.val, i), pick_arg(x.at, y.at, i)};
     }
 };
 
-template <typename W>
-struct Plain {
-    const W* val;
-    __device__ Pair2<W> operator()(int64_t p) const {
-        const W* r = val + 2 * p;
-        return {r[0], r[1]};
+// Interval bounds: I_i = [i delta, (i+2) delta) holds eids [lo_i, hi_i).  The
+// bound of i delta is the low end of I_i and the high end of I_{i-2}; one wave
+// finds it, 64 probes a step, as the few intervals of a large delta leave the
+// chip idle and the search's dependent reads are its time (2e6 edges, up to
+// 4000 intervals: 15-21 us with two binary searches per lane, 5 us).
+__global__ void __launch_bounds__(kBlock)
+interval_wave_kernel(const int64_t* t, int64_t m, int64_t q, int64_t delta, int32_t* lo, int32_t* hi) {
+    const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
+    const int lane = threadIdx.x & 63;
+    if (i >= q + 2) return;
+    const u64 x = (u64)i * (u64)delta;  // below 2^64: i delta <= T + 2 delta
+    int64_t a = 0, n = m;               // the bound lies in [a, a + n]
+    while (n > 64) {
+        const int64_t p = a + (n * (lane + 1)) / 65;
+        const int c = __popcll(__ballot((u64)t[p] < x));  // the first c pivots lie before the bound
+        const int64_t b = c < 64 ? a + (n * (c + 1)) / 65 : a + n;
+        const int64_t s = c > 0 ? a + (n * c) / 65 + 1 : a;
+        a = s;
+        n = b - s;
     }
-};
-
-// Every 2^kCoarseBits-th entry of a prefix table.
-template <typename W>
-__global__ void coarse_kernel(const W* q, int64_t nc, W* c) {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < nc) c[i] = q[i << kCoarseBits];
+    const int64_t e = a + __popcll(__ballot(lane < n && (u64)t[a + (lane < n ? lane : 0)] < x));
+    if (lane == 0) {
+        if (i < q) lo[i] = (int32_t)e;
+        if (i >= 2) hi[i - 2] = (int32_t)e;
+    }
 }
 
-// Interval bounds: I_i = [i delta, (i+2) delta) holds eids [lo_i, hi_i).
+// The same with one lane per interval, for more intervals than the chip has
+// waves to search with.
 __global__ void interval_kernel(const int64_t* t, int64_t m, int64_t q, int64_t delta, int32_t* lo,
                                 int32_t* hi) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -637,6 +643,43 @@ guide_fill_kernel(const W* cum, const void* qc0, const void* qc1, const int32_t*
     guide[b].key = (u64)((uint32_t)tpos0[e] * 2u + (uint32_t)(i & 1));
 }
 
+// One block, for few intervals: the prefix cum of the W_i and the offsets
+// ioff (below) in one launch instead of four.  The four take 18 us for up to
+// 2000 intervals and 24 us at 8000, their gaps not counted; this takes 5.5 us
+// at 100, 9.5 at 2000, 15 at 4000 and 30 at 8000.
+constexpr int kCumBlock = 1024;
+constexpr int kCumItems = 4;
+constexpr int64_t kCumOneBlock = kCumBlock * kCumItems;
+
+template <typename W>
+__global__ void __launch_bounds__(kCumBlock) cum_kernel(IntervalWeight<W> f, int64_t q, W* cum, W* ioff, int* ovf) {
+    W before = 0;
+    bool carry = false;
+    for (int64_t base = 0; base < q; base += kCumBlock * kCumItems) {
+        const int64_t first = base + (int64_t)threadIdx.x * kCumItems;
+        W v[kCumItems], s = 0;
+#pragma unroll
+        for (int k = 0; k < kCumItems; ++k) {
+            v[k] = first + k < q ? f(first + k) : (W)0;
+            s = add_carry<W>(s, v[k], carry);
+        }
+        W tot;
+        W run = before + block_exclusive_t<W, kCumBlock / 64>(s, &tot, carry);
+        before = add_carry<W>(before, tot, carry);
+#pragma unroll
+        for (int k = 0; k < kCumItems; ++k) {
+            const int64_t i = first + k;
+            if (i < q) {
+                cum[i] = run;
+                ioff[i] = run - ((i & 1) ? f.qc1 : f.qc0)[f.lo[i]];
+                run += v[k];
+            }
+        }
+    }
+    if (threadIdx.x == 0) cum[q] = before;
+    if (carry) atomicOr(ovf, sizeof(W) == 8 ? 2 : 1);
+}
+
 // ioff[i] = cum[i] - qc_{i mod 2}[lo_i], modulo the word size.
 template <typename W>
 __global__ void __launch_bounds__(kBlock)
@@ -658,7 +701,14 @@ struct WrappedDiff {
     __device__ Pair2<u128> operator()(int64_t p) const {
         return {(u128)(u64)(q0[p + 1] - q0[p]), (u128)(u64)(q1[p + 1] - q1[p])};
     }
+    static __device__ __forceinline__ WrappedDiff pick(const WrappedDiff& x, const WrappedDiff& y, int i) {
+        return {pick_arg(x.q0, y.q0, i), pick_arg(x.q1, y.q1, i)};
+    }
 };
+
+// Interval searches by waves up to this many intervals (at 2e6 edges 9 us for
+// 16000 against 15 by lanes; 18 against 16 for 40000).
+constexpr int64_t kIntervalWaves = (int64_t)1 << 14;
 
 // The center's prefix arrays in eid order from src (its values, both parities
 // in one pass), then the interval bounds, the prefix of W_i, the per-interval
@@ -673,25 +723,32 @@ int finish_tables(tm_weights* w, hipStream_t st, int* ovf, const R& src) {
         TM_TRY(arena_alloc(w->arena, &qc[par], (size_t)m + 1));
         w->qc[par] = qc[par];
     }
-    TM_TRY(device_exclusive_scan2<W>(src, m, qc[0], qc[1], ovf, st));
+    const Scan2Job<W, R> job{src, qc[0], qc[1], nullptr, nullptr};
+    TM_TRY(device_exclusive_scan2(&job, 1, m, ovf, st));
     // intervals and their weights
     TM_TRY(arena_alloc(w->arena, &w->ilo, (size_t)w->q));
     TM_TRY(arena_alloc(w->arena, &w->ihi, (size_t)w->q));
-    hipLaunchKernelGGL(interval_kernel, dim3(grid_for(w->q)), dim3(kBlock), 0, st, g->d.t, m, w->q,
-                       w->ilen, w->ilo, w->ihi);
+    if (w->q <= kIntervalWaves)
+        hipLaunchKernelGGL(interval_wave_kernel, dim3(grid_for(64 * (w->q + 2))), dim3(kBlock), 0, st, g->d.t, m, w->q,
+                           w->ilen, w->ilo, w->ihi);
+    else
+        hipLaunchKernelGGL(interval_kernel, dim3(grid_for(w->q)), dim3(kBlock), 0, st, g->d.t, m, w->q,
+                           w->ilen, w->ilo, w->ihi);
     TM_HIP(hipGetLastError());
     W* cum;
     TM_TRY(arena_alloc(w->arena, &cum, (size_t)w->q + 1));
-    TM_TRY(device_exclusive_scan<W>(
-        IntervalWeight<W>{static_cast<const W*>(w->qc[0]), static_cast<const W*>(w->qc[1]), w->ilo,
-                          w->ihi},
-        w->q, cum, ovf, st));
     w->cumW = cum;
     // per-interval offsets and the root guide
     W* ioff;
     TM_TRY(arena_alloc(w->arena, &ioff, (size_t)w->q));
-    hipLaunchKernelGGL((ioff_kernel<W>), dim3(grid_for(w->q)), dim3(kBlock), 0, st, (const W*)cum,
-                       (const W*)w->qc[0], (const W*)w->qc[1], (const int32_t*)w->ilo, w->q, ioff);
+    const IntervalWeight<W> iw{qc[0], qc[1], w->ilo, w->ihi};
+    if (w->q <= kCumOneBlock) {
+        hipLaunchKernelGGL((cum_kernel<W>), dim3(1), dim3(kCumBlock), 0, st, iw, w->q, cum, ioff, ovf);
+    } else {
+        TM_TRY(device_exclusive_scan<W>(iw, w->q, cum, ovf, st));
+        hipLaunchKernelGGL((ioff_kernel<W>), dim3(grid_for(w->q)), dim3(kBlock), 0, st, (const W*)cum,
+                           (const W*)qc[0], (const W*)qc[1], (const int32_t*)w->ilo, w->q, ioff);
+    }
     TM_HIP(hipGetLastError());
     w->ioff = ioff;
     w->guide_bits = guide_bits_for(m, w->lean);
@@ -862,19 +919,17 @@ int build_typed(tm_weights* w, hipStream_t st, int* ovf, int* ovf_c, bool check_
                     w->qt[s][par] = qt[par];
                     w->qn[s][par] = qn[par];
                 }
-                const W* vp = static_cast<const W*>(w->vals[s][0]);
-                TM_TRY(device_exclusive_scan2<W>(Plain<W>{vp}, m, qt[0], qt[1], ovf, st));
-                TM_TRY(device_exclusive_scan2<W>(ListGather<W>{vp, g->d.nxref[dir]}, m, qn[0], qn[1], ovf, st));
+                const Products<W>* vp = static_cast<const Products<W>*>(w->vals[s][0]);
                 // lean sets (memory over speed) search the full tables
                 const int64_t nc = (m >> kCoarseBits) + 1;
+                W* c[2] = {nullptr, nullptr};
                 for (int par = 0; par < 2 && !w->lean; ++par) {
-                    W* c;
-                    TM_TRY(arena_alloc(w->arena, &c, (size_t)nc));
-                    hipLaunchKernelGGL((coarse_kernel<W>), dim3(grid_for(nc)), dim3(kBlock), 0, st,
-                                       (const W*)qt[par], nc, c);
-                    TM_HIP(hipGetLastError());
-                    w->qtc[s][par] = c;
+                    TM_TRY(arena_alloc(w->arena, &c[par], (size_t)nc));
+                    w->qtc[s][par] = c[par];
                 }
+                const Scan2Job<W, Values<W>> jobs[2] = {{{vp, nullptr}, qt[0], qt[1], c[0], c[1]},
+                                                        {{vp, g->d.nxref[dir]}, qn[0], qn[1], nullptr, nullptr}};
+                TM_TRY(device_exclusive_scan2(jobs, 2, m, ovf, st));
                 TM_HIP(dev_free(w->vals[s][0], st));
                 w->vals[s][0] = nullptr;
             }
@@ -883,7 +938,7 @@ int build_typed(tm_weights* w, hipStream_t st, int* ovf, int* ovf_c, bool check_
     // the center: prefix sums in eid order (slot 0 is the center), then the
     // interval tables
     {
-        TM_TRY(finish_tables<W>(w, st, ovf_c, Plain<W>{static_cast<const W*>(w->vals[0][0])}));
+        TM_TRY(finish_tables<W>(w, st, ovf_c, Values<W>{static_cast<const Products<W>*>(w->vals[0][0]), nullptr}));
     }
     TM_HIP(dev_free(w->vals[0][0], st));
     w->vals[0][0] = nullptr;
