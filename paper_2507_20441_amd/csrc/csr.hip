@@ -376,6 +376,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     // 2^32 - 1; t32e: those times by eid, the list sorts' input.
     const bool narrow = g->T < (int64_t)0xFFFFFFFFll;
     uint32_t* t32e = nullptr;
+    unsigned char* scr = nullptr;  // the sorts' scratch
     uint32_t* opos[3] = {nullptr, nullptr, nullptr};  // N orders: the carried other T positions, and their sort buffer
     uint32_t* nbr32[2] = {nullptr, nullptr};  // 32-bit times: the T orders' neighbours until packed
     auto release = [&]() {
@@ -389,6 +390,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         }
         if (nbr_tmp) (void)dev_free(nbr_tmp, st);
         nbr_tmp = nullptr;
+        if (scr) (void)dev_free(scr, st);
+        scr = nullptr;
         for (uint32_t*& b : opos) {
             if (b) (void)dev_free(b, st);
             b = nullptr;
@@ -419,17 +422,40 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     }
     // A sort between two buffer sets: the result lands in `spare` after an
     // odd number of passes, else back in `in`.
-    auto sort_two = [&](const auto& in, const auto& spare, int nbits, auto* res) -> int {
+    // One block, cleared by one launch, holds every sort's scratch: the digit
+    // counts and tickets of the canonical sorts (0, 1) and of the lists' by
+    // source and by destination (2, 3), tickets of the N orders (4, 5; they
+    // sort the same owners as the T order of their direction, so its counts
+    // serve them), and the status words all of them share.  (At 20,000 edges
+    // clearing, counting and starting five sorts one by one was a fifth of the
+    // build.)
+    constexpr int kHeads = 6;
+    const size_t scr_bytes = kHeads * kSortHeadBytes + sort_status_bytes(m);
+    uint32_t tag = 0;
+    auto scratch_of = [&](int tickets, int counts) {
+        SortScratch x = sort_scratch_at(scr + (size_t)tickets * kSortHeadBytes);
+        x.counts = reinterpret_cast<uint32_t*>(scr + (size_t)counts * kSortHeadBytes);
+        x.status = reinterpret_cast<u64*>(scr + kHeads * kSortHeadBytes);
+        x.counted = tickets >= 2;
+        x.tag0 = tag;
+        tag += kSortMaxPasses;
+        return x;
+    };
+    if (rc == TM_OK && dev_alloc((void**)&scr, scr_bytes, st) != hipSuccess)
+        rc = tm_fail(TM_ENOMEM, "graph: sort scratch");
+    if (rc == TM_OK) rc = fill_u32(scr, (int64_t)(scr_bytes / sizeof(uint32_t)), 0u, st);
+    auto sort_two = [&](const auto& in, const auto& spare, int nbits, int which, auto* res) -> int {
         const bool odd = (std::max(1, radix_passes(nbits)) & 1) != 0;
         *res = odd ? spare : in;
-        return sort_into(in, odd ? spare : in, odd ? in : spare, m, 0, nbits, 0, flags + 1, st);
+        return sort_into(in, odd ? spare : in, odd ? in : spare, m, 0, nbits, 0, flags + 1, st,
+                         scratch_of(which, which));
     };
     if (rc == TM_OK && one_key) {
         using S = SortSet<u64>;
         S in, spare, res;
         in.k = work[0];
         spare.k = work[2];
-        rc = sort_two(in, spare, 2 * bn + D.bt, &res);
+        rc = sort_two(in, spare, 2 * bn + D.bt, 0, &res);
         if (rc == TM_OK)
             hipLaunchKernelGGL(decode_packed_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)res.k, m,
                                bn, esrc, edst, et, t32e, flags);
@@ -441,7 +467,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         x.v0 = work[1];
         y.k = work[2];
         y.v0 = work[3];
-        rc = sort_two(x, y, 2 * bn, &r1);
+        rc = sort_two(x, y, 2 * bn, 0, &r1);
         if (rc == TM_OK) {
             const S& o1 = r1.k == x.k ? y : x;
             S in2, spare2;
@@ -449,7 +475,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             in2.v0 = r1.k;
             spare2.k = o1.k;
             spare2.v0 = o1.v0;
-            rc = sort_two(in2, spare2, D.bt, &r2);
+            rc = sort_two(in2, spare2, D.bt, 1, &r2);
         }
         if (rc == TM_OK)
             hipLaunchKernelGGL(decode_split_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)r2.k,
@@ -500,6 +526,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             if (dev_alloc((void**)&opos[x], (size_t)m * sizeof(uint32_t), st) != hipSuccess)
                 return tm_fail(TM_ENOMEM, "graph: work arrays");
         const size_t guide_len = (size_t)guide_first(n, (int32_t)m) + 1;
+        TM_TRY(sort_count<uint32_t>(reinterpret_cast<uint32_t*>(esrc), reinterpret_cast<uint32_t*>(edst), 2, m,
+                                    sort_plan_copy(0, bn), scratch_of(2, 2).counts, scratch_of(3, 3).counts, st));
         for (int dir = 0; dir < 2; ++dir) {
             TT* lt = nullptr;
             int32_t *leid = nullptr, *lnbr = nullptr, *lown = nullptr, *off = nullptr;
@@ -525,7 +553,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             out.v0 = reinterpret_cast<V*>(lt);
             out.v1 = reinterpret_cast<uint32_t*>(leid);
             out.v2 = reinterpret_cast<uint32_t*>(lnbr);
-            TM_TRY(sort_into(in, out, tmp, m, 0, bn, 2 /* eids: 0, 1, ... */, flags + 1, st));
+            TM_TRY(sort_into(in, out, tmp, m, 0, bn, 2 /* eids: 0, 1, ... */, flags + 1, st,
+                             scratch_of(2 + dir, 2 + dir)));
             hipLaunchKernelGGL(offsets_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const uint32_t*)own[dir],
                                m, n, off);
             uint2* nt = nullptr;
@@ -588,7 +617,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
                     buf.v3 = opos[2];
                     iota = 8;  // the other list's positions: 0, 1, ...
                 }
-                return sort_into(in, out, buf, m, 0, bn, iota, flags + 1, st);
+                return sort_into(in, out, buf, m, 0, bn, iota, flags + 1, st, scratch_of(4 + dir, 2 + dir));
             };
             if (ranks) TM_TRY(sort_n(SortSet<uint32_t, V, uint32_t, uint32_t, uint32_t>{}));
             else TM_TRY(sort_n(L{}));

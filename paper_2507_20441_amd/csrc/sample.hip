@@ -1560,9 +1560,12 @@ int sample_run(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, hipStrea
     int* ovf = nullptr;
     uint32_t *k0 = nullptr, *v0 = nullptr, *k1 = nullptr, *v1 = nullptr;
     TM_HIP(dev_alloc((void**)&parts, (size_t)(blocks + 1) * sizeof(Partial), st));
-    TM_HIP(dev_alloc((void**)&ovf, sizeof(int), st));
-    TM_TRY(fill_u32(ovf, 1, 0u, st));
+    // the flag word and the sort's scratch in one block, cleared together
+    const size_t flag_bytes = 256 + (sorted ? sort_scratch_bytes((int64_t)chunk) : 0);
+    TM_HIP(dev_alloc((void**)&ovf, flag_bytes, st));
+    SortScratch sort;
     if (sorted) {
+        sort = sort_scratch_at(reinterpret_cast<unsigned char*>(ovf) + 256);
         TM_HIP(dev_alloc((void**)&k0, chunk * sizeof(uint32_t), st));
         TM_HIP(dev_alloc((void**)&v0, chunk * sizeof(uint32_t), st));
         TM_HIP(dev_alloc((void**)&k1, chunk * sizeof(uint32_t), st));
@@ -1588,6 +1591,7 @@ int sample_run(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, hipStrea
         // the root draws keep a wider grid (more draws in flight)
         const dim3 rgrid((unsigned)std::min<u64>((n + kBlock - 1) / kBlock, 8192));
         StageTimer t_roots, t_sample, t_reduce;
+        TM_TRY(fill_u32(ovf, (int64_t)(flag_bytes / sizeof(uint32_t)), 0u, st));
         if (sorted) {
             if (!model_bytes) t_roots.start(TM_STAGE_ROOTS, st);
             if (w->wide)
@@ -1597,7 +1601,7 @@ int sample_run(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, hipStrea
             TM_HIP(hipGetLastError());
             uint32_t *ks, *vs;
             TM_TRY(radix_sort_pairs<uint32_t>(k0, v0, k1, v1, (int64_t)n, root_sort_lo_bit(key_bits), key_bits, &ks,
-                                              &vs, ovf, st, true));
+                                              &vs, ovf, st, true, sort));
             a.skey = ks;
             a.sval = vs;
             t_roots.stop();
@@ -2378,8 +2382,9 @@ int sample_run_noalloc(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, 
         kb[x] = reinterpret_cast<uint32_t*>(at);
         at += align256(kNoAllocKeys);
     }
-    uint32_t* hist = reinterpret_cast<uint32_t*>(at);
+    const SortScratch sort = sort_scratch_at(at);
     TM_TRY(fill_u32(ovf, 1, 0u, st));  // a fill kernel: the last call's flag is stale
+    if (sorted) TM_TRY(fill_u32(at, (int64_t)(sort_scratch_bytes((int64_t)count) / sizeof(uint32_t)), 0u, st));
     a.parts = parts;
     a.ovf = ovf;
     a.j0 = j0;
@@ -2396,7 +2401,7 @@ int sample_run_noalloc(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, 
         TM_HIP(hipGetLastError());
         uint32_t *ks, *vs;
         TM_TRY(radix_sort_pairs<uint32_t>(kb[0], kb[1], kb[2], kb[3], (int64_t)count, root_sort_lo_bit(key_bits),
-                                          key_bits, &ks, &vs, ovf, st, true, hist));
+                                          key_bits, &ks, &vs, ovf, st, true, sort));
         a.skey = ks;
         a.sval = vs;
     }

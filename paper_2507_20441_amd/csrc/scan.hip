@@ -1,5 +1,5 @@
-// Scan of tile sums for the device-wide exclusive scan, and the digit starts
-// of the radix sort (tm_primitives.h).
+// Scan of tile sums for the device-wide exclusive scan (tm_primitives.h), and
+// the fill kernels.
 #include <algorithm>
 
 #include "tm_primitives.h"
@@ -68,13 +68,4 @@ int scan_parts(u128* part, int64_t nb, int* ovf, hipStream_t st) {
         return TM_OK;
     }
     return device_exclusive_scan<u128>(ArrayReader128{part}, nb, part, ovf, st);
-}
-
-__global__ void __launch_bounds__(kBlock) sort_base_kernel(uint32_t* ghist, int npass) {
-    __shared__ uint32_t wsum[kWaves];
-    for (int p = 0; p < npass; ++p) {
-        uint32_t* h = ghist + p * kSortDigits;
-        const uint32_t v = h[threadIdx.x];
-        h[threadIdx.x] = block_excl_scan_256(v, wsum);
-    }
 }

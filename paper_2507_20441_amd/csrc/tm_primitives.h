@@ -12,8 +12,19 @@ constexpr int kScanItems = 8;                      // values per lane in a scan 
 constexpr int kScanTile = kBlock * kScanItems;     // 2048
 constexpr int kSortBits = 8;                       // sort digits: up to 8 bits, one per lane
 constexpr int kSortDigits = 1 << kSortBits;        // 256
-constexpr int kSortItems = 16;                     // keys per lane in a sort tile
-constexpr int kSortTile = kBlock * kSortItems;     // 4096
+// Keys per lane in a sort tile.  A pass over many tiles wants large ones (each
+// digit's run of a tile goes out to consecutive addresses; 4096 keys); a pass
+// over few tiles is one tile's serial work -- ranking key by key, one array
+// after another through LDS -- and is left after a quarter of the keys (1024,
+// whose values also fit in registers from the start).  A graph build of 2^14
+// edges takes 198 us with the small tiles and 301 with the large, 2^18 edges
+// 351 and 412, 2^19 506 and 494, 2^21 1475 and 1020; sampling 2^16 roots 88
+// and 95 us, 2^18 112 and 116, 2^19 152 and 148.
+constexpr int kSortItems = 16;
+constexpr int kSortItemsSmall = 4;
+constexpr int64_t kSortSmall = (int64_t)1 << 18;
+constexpr int sort_items(int64_t n) { return n <= kSortSmall ? kSortItemsSmall : kSortItems; }
+constexpr int64_t sort_tiles(int64_t n) { return (n + kBlock * sort_items(n) - 1) / (kBlock * sort_items(n)); }
 constexpr int kSortMaxPasses = 8;
 static_assert(kSortDigits == kBlock, "one digit per lane of a block");
 
@@ -451,8 +462,7 @@ __device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t* ws
 // Stable LSD radix sort of keys that carry up to four value arrays
 // (structure of arrays), one kernel per digit of up to 8 bits:
 //  * sort_hist_kernel counts the digits of every pass in one read of the
-//    keys, and sort_base_kernel turns those counts into each digit's first
-//    position;
+//    keys (each pass turns its counts into the digits' first positions);
 //  * sort_pass_kernel, once per pass: a block takes the next tile by ticket
 //    (so a tile only ever waits on tiles that are already running), ranks
 //    its keys by digit with wave ballots, publishes its digit counts, and
@@ -462,8 +472,8 @@ __device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t* ws
 //    through LDS, each digit's run of the tile to consecutive addresses.
 // A status word holds a value (bits 0-31), a flag (bits 32-33: 1 the tile's
 // own count, 2 the total through the tile) and the pass's tag (bits 40-47).
-// The words are cleared once per sort, so a word left by an earlier pass
-// reads as not yet published.  Waits are bounded: a lane that has polled
+// The words are cleared once, and sorts that share them use tags of their own,
+// so a word left by an earlier pass reads as not yet published.  Waits are bounded: a lane that has polled
 // kSortMaxSpins times sets kSortStall in the caller's error word and goes on
 // (the order is then wrong, and the caller reports the error).
 // ---------------------------------------------------------------------------
@@ -477,8 +487,29 @@ constexpr size_t kSortHeadBytes =
 
 // Scratch of a sort of n keys: per-pass digit counts and tickets, then one
 // status word per tile and digit.
-constexpr size_t sort_scratch_bytes(int64_t n) {
-    return kSortHeadBytes + (size_t)(n > 0 ? (n + kSortTile - 1) / kSortTile : 0) * kSortDigits * sizeof(u64);
+constexpr size_t sort_status_bytes(int64_t n) {
+    return (size_t)(n > 0 ? sort_tiles(n) : 0) * kSortDigits * sizeof(u64);
+}
+constexpr size_t sort_scratch_bytes(int64_t n) { return kSortHeadBytes + sort_status_bytes(n); }
+
+// Where a sort finds its scratch when the caller cleared it: digit counts
+// (made by the sort unless counted) and tickets of its own, and the status
+// words, which sorts of one stream may share, each with tags above the others'.
+struct SortScratch {
+    uint32_t* counts = nullptr;   // [kSortMaxPasses][kSortDigits]
+    uint32_t* tickets = nullptr;  // [kSortMaxPasses]
+    u64* status = nullptr;
+    uint32_t tag0 = 0;
+    bool counted = false;
+};
+
+// The layout of sort_scratch_bytes.
+inline SortScratch sort_scratch_at(void* base) {
+    SortScratch s;
+    s.counts = static_cast<uint32_t*>(base);
+    s.tickets = s.counts + kSortMaxPasses * kSortDigits;
+    s.status = reinterpret_cast<u64*>(static_cast<unsigned char*>(base) + kSortHeadBytes);
+    return s;
 }
 
 struct SortPlan {
@@ -502,6 +533,17 @@ inline SortPlan sort_plan(int lo_bit, int nbits) {
     return P;
 }
 
+// The plan with at least one pass: a stable copy when no bit is sorted.
+inline SortPlan sort_plan_copy(int lo_bit, int nbits) {
+    SortPlan P = sort_plan(lo_bit, nbits);
+    if (P.npass == 0) {
+        P.npass = 1;
+        P.shift[0] = 0;
+        P.bits[0] = 0;
+    }
+    return P;
+}
+
 template <typename V>
 struct SortSize {
     static constexpr size_t value = sizeof(V);
@@ -516,10 +558,13 @@ struct SortIO {
     void* out[5];
 };
 
+// (two key arrays of one length: blockIdx.y picks)
 template <typename K>
 __global__ void __launch_bounds__(kBlock)
-sort_hist_kernel(const K* __restrict__ keys, int64_t n, SortPlan P, uint32_t* __restrict__ ghist) {
+sort_hist_kernel(const K* keys0, const K* keys1, int64_t n, SortPlan P, uint32_t* ghist0, uint32_t* ghist1) {
     __shared__ uint32_t h[kSortMaxPasses][kSortDigits];
+    const K* keys = pick_arg(keys0, keys1, blockIdx.y);
+    uint32_t* ghist = pick_arg(ghist0, ghist1, blockIdx.y);
 #pragma unroll
     for (int p = 0; p < kSortMaxPasses; ++p) h[p][threadIdx.x] = 0;
     __syncthreads();
@@ -536,35 +581,59 @@ sort_hist_kernel(const K* __restrict__ keys, int64_t n, SortPlan P, uint32_t* __
     }
 }
 
-// Each pass's digit counts, in place, into exclusive digit starts.
-__global__ void __launch_bounds__(kBlock) sort_base_kernel(uint32_t* ghist, int npass);
+template <typename K>
+int sort_count(const K* keys0, const K* keys1, int narrays, int64_t n, const SortPlan& P, uint32_t* counts0,
+               uint32_t* counts1, hipStream_t st) {
+    if (n <= 0 || P.npass <= 0) return TM_OK;
+    const unsigned hb = (unsigned)std::min<int64_t>((n + kBlock * kSortItems - 1) / (kBlock * kSortItems), 1024);
+    hipLaunchKernelGGL((sort_hist_kernel<K>), dim3(hb, (unsigned)narrays), dim3(kBlock), 0, st, keys0, keys1, n, P,
+                       counts0, counts1);
+    TM_HIP(hipGetLastError());
+    return TM_OK;
+}
 
-// One value array of a tile through LDS to the positions of its keys.
-template <typename V>
-__device__ __forceinline__ void sort_move_values(const void* vin, void* vout, bool iota, int64_t wbase, int lane,
-                                                 int64_t n, const uint32_t (&lp)[kSortItems], unsigned char* sbuf,
-                                                 const uint8_t* sdig, const uint32_t* gofs, int tn) {
+// One value array of a tile: its loads (before the ranking where registers
+// allow, small tiles: kPre), and its way through LDS to the positions of its
+// keys.
+template <typename V, int kItems>
+__device__ __forceinline__ void sort_load_values(const void* vin, bool iota, int64_t wbase, int lane, int64_t n,
+                                                 V (&x)[kItems]) {
     if constexpr (!std::is_same<V, SortNone>::value) {
-        V* sv = reinterpret_cast<V*>(sbuf);
         const V* in = static_cast<const V*>(vin);
-        V* out = static_cast<V*>(vout);
-        V x[kSortItems];
-        const int64_t tbase = wbase - (int64_t)(threadIdx.x >> 6) * 64 * kSortItems;
-        if (!iota && tbase + kSortTile <= n) {
+        const int64_t tbase = wbase - (int64_t)(threadIdx.x >> 6) * 64 * kItems;
+        if (!iota && tbase + kBlock * kItems <= n) {
             // a whole tile: one base address, the items at fixed offsets
             const V* vp = in + wbase + lane;
 #pragma unroll
-            for (int k = 0; k < kSortItems; ++k) x[k] = vp[k * 64];
+            for (int k = 0; k < kItems; ++k) x[k] = vp[k * 64];
         } else {
 #pragma unroll
-            for (int k = 0; k < kSortItems; ++k) {
+            for (int k = 0; k < kItems; ++k) {
                 const int64_t i = wbase + (int64_t)k * 64 + lane;
                 x[k] = i < n ? (iota ? (V)i : in[i]) : (V)0;
             }
         }
+    }
+}
+
+template <typename V, int kItems, bool kPre>
+__device__ __forceinline__ void sort_move_values(const void* vin, void* vout, bool iota, int64_t wbase, int lane,
+                                                 int64_t n, const uint32_t (&lp)[kItems],
+                                                 const V (&pre)[kPre ? kItems : 1],
+                                                 unsigned char* sbuf, const uint8_t* sdig, const uint32_t* gofs, int tn) {
+    if constexpr (!std::is_same<V, SortNone>::value) {
+        V* sv = reinterpret_cast<V*>(sbuf);
+        V* out = static_cast<V*>(vout);
+        V x[kItems];
+        if constexpr (kPre) {
+#pragma unroll
+            for (int k = 0; k < kItems; ++k) x[k] = pre[k];
+        } else {
+            sort_load_values(vin, iota, wbase, lane, n, x);
+        }
         __syncthreads();  // the buffer's previous contents have gone out
 #pragma unroll
-        for (int k = 0; k < kSortItems; ++k) {
+        for (int k = 0; k < kItems; ++k) {
             const int64_t i = wbase + (int64_t)k * 64 + lane;
             if (i < n) sv[lp[k]] = x[k];
         }
@@ -576,15 +645,17 @@ __device__ __forceinline__ void sort_move_values(const void* vin, void* vout, bo
     }
 }
 
-template <typename K, typename V0, typename V1, typename V2, typename V3>
+template <typename K, typename V0, typename V1, typename V2, typename V3, int kItems>
 __global__ void __launch_bounds__(kBlock)
-sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int iota, const uint32_t* __restrict__ starts,
+sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int iota, const uint32_t* __restrict__ counts,
                  uint32_t* __restrict__ ticket, u64* __restrict__ status, int* __restrict__ err) {
     constexpr size_t kElt = std::max(std::max(sizeof(K), SortSize<V0>::value),
                                      std::max(std::max(SortSize<V1>::value, SortSize<V2>::value), SortSize<V3>::value));
-    __shared__ __align__(16) unsigned char sbuf[kElt * kSortTile];
-    __shared__ uint8_t sdig[kSortTile];
-    // per wave and digit: counts, then tile-local starts, at most kSortTile
+    constexpr int kTile = kBlock * kItems;
+    constexpr bool kPre = kItems <= kSortItemsSmall;
+    __shared__ __align__(16) unsigned char sbuf[kElt * kTile];
+    __shared__ uint8_t sdig[kTile];
+    // per wave and digit: counts, then tile-local starts, at most kTile
     // (16 bits keep a 64-bit-key pass within four workgroups' LDS per CU)
     __shared__ uint16_t cnt[kWaves][kSortDigits];
     __shared__ uint32_t gofs[kSortDigits];  // per digit: its global position minus its tile-local one
@@ -592,51 +663,62 @@ sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int io
     __shared__ uint32_t s_tile;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (threadIdx.x == 0) s_tile = atomicAdd(ticket, 1u);
+    const uint32_t mask = (1u << bits) - 1u;
+    const uint32_t d = threadIdx.x;
+    const uint32_t gcount = d <= mask ? counts[d] : 0u;  // the digit over all keys
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) cnt[w][threadIdx.x] = 0;
     __syncthreads();
     const uint32_t tile = s_tile;
-    const int64_t tbase = (int64_t)tile * kSortTile;
-    // wave w owns tile positions [w 64 kSortItems, (w + 1) 64 kSortItems), in
+    const int64_t tbase = (int64_t)tile * kTile;
+    // wave w owns tile positions [w 64 kItems, (w + 1) 64 kItems), in
     // rounds of 64 consecutive keys: the wave ranks its keys in input order
-    const int64_t wbase = tbase + (int64_t)wave * 64 * kSortItems;
-    const uint32_t mask = (1u << bits) - 1u;
+    const int64_t wbase = tbase + (int64_t)wave * 64 * kItems;
     const u64 lt_mask = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const K* keys = static_cast<const K*>(io.in[0]);
-    K key[kSortItems];
-    uint32_t lp[kSortItems];  // (the digits are recomputed from the keys: fewer registers)
-    if (tbase + kSortTile <= n) {
+    K key[kItems];
+    V0 x0[kPre ? kItems : 1];
+    V1 x1[kPre ? kItems : 1];
+    V2 x2[kPre ? kItems : 1];
+    V3 x3[kPre ? kItems : 1];
+    uint32_t lp[kItems];  // (the digits are recomputed from the keys: fewer registers)
+    if (tbase + kTile <= n) {
         // a whole tile: one base address, the items at fixed offsets
         const K* kp = keys + wbase + lane;
 #pragma unroll
-        for (int k = 0; k < kSortItems; ++k) key[k] = kp[k * 64];
+        for (int k = 0; k < kItems; ++k) key[k] = kp[k * 64];
     } else {
 #pragma unroll
-        for (int k = 0; k < kSortItems; ++k) {
+        for (int k = 0; k < kItems; ++k) {
             const int64_t i = wbase + (int64_t)k * 64 + lane;
             key[k] = i < n ? keys[i] : (K)0;
         }
     }
+    if constexpr (kPre) {
+        sort_load_values(io.in[1], iota & 1, wbase, lane, n, x0);
+        sort_load_values(io.in[2], iota & 2, wbase, lane, n, x1);
+        sort_load_values(io.in[3], iota & 4, wbase, lane, n, x2);
+        sort_load_values(io.in[4], iota & 8, wbase, lane, n, x3);
+    }
 #pragma unroll
-    for (int k = 0; k < kSortItems; ++k) {
+    for (int k = 0; k < kItems; ++k) {
         const int64_t i = wbase + (int64_t)k * 64 + lane;
         const bool ok = i < n;
-        const uint32_t d = ok ? ((uint32_t)(key[k] >> shift) & mask) : 0u;
+        const uint32_t dk = ok ? ((uint32_t)(key[k] >> shift) & mask) : 0u;
         u64 peers = __ballot(ok);
         for (int b = 0; b < bits; ++b) {
-            const u64 bal = __ballot((d >> b) & 1u);
-            peers &= ((d >> b) & 1u) ? bal : ~bal;
+            const u64 bal = __ballot((dk >> b) & 1u);
+            peers &= ((dk >> b) & 1u) ? bal : ~bal;
         }
-        const uint32_t before = cnt[wave][d];
+        const uint32_t before = cnt[wave][dk];
         lp[k] = before + (uint32_t)__popcll(peers & lt_mask);
         // the lowest lane of each digit group advances the wave's counter
-        if (ok && (peers & lt_mask) == 0) cnt[wave][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
+        if (ok && (peers & lt_mask) == 0) cnt[wave][dk] = (uint16_t)(before + (uint32_t)__popcll(peers));
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     // lane d: the tile's count of digit d, published at once (the first tile
     // publishes it as its inclusive total)
-    const uint32_t d = threadIdx.x;
     uint32_t tcount = 0;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) tcount += cnt[w][d];
@@ -647,6 +729,7 @@ sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int io
                            __HIP_MEMORY_SCOPE_AGENT);
     // tile-local starts: of each digit, and of each wave's keys inside it
     const uint32_t dstart = block_excl_scan_256(tcount, wsum);
+    const uint32_t start = block_excl_scan_256(gcount, wsum);  // the digit's first position
     {
         uint32_t run = dstart;
 #pragma unroll
@@ -659,7 +742,7 @@ sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int io
     __syncthreads();
     K* skey = reinterpret_cast<K*>(sbuf);
 #pragma unroll
-    for (int k = 0; k < kSortItems; ++k) {
+    for (int k = 0; k < kItems; ++k) {
         const int64_t i = wbase + (int64_t)k * 64 + lane;
         if (i < n) {
             const uint32_t dk = (uint32_t)(key[k] >> shift) & mask;  // the digit again
@@ -711,10 +794,10 @@ sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int io
             __hip_atomic_store(my, tagw | ((u64)2 << 32) | (u64)(excl + tcount), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         }
-        gofs[d] = starts[d] + excl - dstart;
+        gofs[d] = start + excl - dstart;
     }
     __syncthreads();
-    const int tn = (int)(n - tbase < kSortTile ? n - tbase : kSortTile);
+    const int tn = (int)(n - tbase < kTile ? n - tbase : kTile);
     K* okeys = static_cast<K*>(io.out[0]);
     // (positions are below n whenever the digit counts hold; the test keeps
     // a broken invariant from writing outside the output)
@@ -722,10 +805,14 @@ sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int io
         const uint32_t g = gofs[sdig[p]] + (uint32_t)p;
         if ((int64_t)g < n) okeys[g] = skey[p];
     }
-    sort_move_values<V0>(io.in[1], io.out[1], iota & 1, wbase, lane, n, lp, sbuf, sdig, gofs, tn);
-    sort_move_values<V1>(io.in[2], io.out[2], iota & 2, wbase, lane, n, lp, sbuf, sdig, gofs, tn);
-    sort_move_values<V2>(io.in[3], io.out[3], iota & 4, wbase, lane, n, lp, sbuf, sdig, gofs, tn);
-    sort_move_values<V3>(io.in[4], io.out[4], iota & 8, wbase, lane, n, lp, sbuf, sdig, gofs, tn);
+    sort_move_values<V0, kItems, kPre>(io.in[1], io.out[1], iota & 1, wbase, lane, n, lp, x0, sbuf, sdig, gofs,
+                                       tn);
+    sort_move_values<V1, kItems, kPre>(io.in[2], io.out[2], iota & 2, wbase, lane, n, lp, x1, sbuf, sdig, gofs,
+                                       tn);
+    sort_move_values<V2, kItems, kPre>(io.in[3], io.out[3], iota & 4, wbase, lane, n, lp, x2, sbuf, sdig, gofs,
+                                       tn);
+    sort_move_values<V3, kItems, kPre>(io.in[4], io.out[4], iota & 8, wbase, lane, n, lp, x3, sbuf, sdig, gofs,
+                                       tn);
 }
 
 // A key array and up to four value arrays (null where a value is absent).
@@ -742,42 +829,42 @@ struct SortSet {
 // output, and writes bufs[p & 1]; bufs[0] must not be `in` (bufs[1] may be:
 // the first pass has consumed it before the second writes).  Returns the
 // index of the buffer that holds the result.  iota: bit j set, value array j
-// holds nothing yet and stands for 0, 1, ..., n - 1.  scratch: at least
-// sort_scratch_bytes(n) bytes, or null to allocate it here.
+// holds nothing yet and stands for 0, 1, ..., n - 1.  scratch: cleared by the
+// caller, or with null counts allocated and
+// cleared here.
 template <typename K, typename V0, typename V1, typename V2, typename V3>
 int sort_run(const SortSet<K, V0, V1, V2, V3>& in, const SortSet<K, V0, V1, V2, V3> (&bufs)[2], int64_t n,
-             const SortPlan& P, int iota, int* err, hipStream_t st, void* scratch, int* result) {
+             const SortPlan& P, int iota, int* err, hipStream_t st, SortScratch scratch, int* result) {
     *result = (P.npass - 1) & 1;
     if (n <= 0 || P.npass <= 0) return TM_OK;
     if (bufs[0].k == in.k) return tm_fail(TM_EDEVICE, "sort: the first pass would overwrite its input");
-    const size_t bytes = sort_scratch_bytes(n);
-    unsigned char* scr = static_cast<unsigned char*>(scratch);
-    if (!scr) TM_HIP(dev_alloc((void**)&scr, bytes, st));
-    uint32_t* ghist = reinterpret_cast<uint32_t*>(scr);
-    uint32_t* tickets = ghist + kSortMaxPasses * kSortDigits;
-    u64* status = reinterpret_cast<u64*>(scr + kSortHeadBytes);
-    const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
-    int rc = fill_u32(scr, (int64_t)(bytes / sizeof(uint32_t)), 0u, st);
-    if (rc == TM_OK) {
-        const unsigned hb = (unsigned)std::min<int64_t>(ntiles, 1024);
-        hipLaunchKernelGGL((sort_hist_kernel<K>), dim3(hb), dim3(kBlock), 0, st, (const K*)in.k, n, P, ghist);
-        if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "sort: histogram launch");
+    unsigned char* own = nullptr;
+    int rc = TM_OK;
+    if (!scratch.counts) {
+        const size_t bytes = sort_scratch_bytes(n);
+        TM_HIP(dev_alloc((void**)&own, bytes, st));
+        scratch = sort_scratch_at(own);
+        rc = fill_u32(own, (int64_t)(bytes / sizeof(uint32_t)), 0u, st);
     }
-    if (rc == TM_OK) {
-        hipLaunchKernelGGL(sort_base_kernel, dim3(1), dim3(kBlock), 0, st, ghist, P.npass);
-        if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "sort: digit start launch");
-    }
+    if (rc == TM_OK && !scratch.counted) rc = sort_count<K>(in.k, in.k, 1, n, P, scratch.counts, scratch.counts, st);
+    const int items = sort_items(n);
+    const dim3 grid((unsigned)sort_tiles(n));
     for (int p = 0; p < P.npass && rc == TM_OK; ++p) {
         const SortSet<K, V0, V1, V2, V3>& src = p == 0 ? in : bufs[(p - 1) & 1];
         const SortSet<K, V0, V1, V2, V3>& dst = bufs[p & 1];
         SortIO io{{src.k, src.v0, src.v1, src.v2, src.v3}, {dst.k, dst.v0, dst.v1, dst.v2, dst.v3}};
-        hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, V3>), dim3((unsigned)ntiles), dim3(kBlock), 0, st, io, n,
-                           P.shift[p], P.bits[p], (uint32_t)(p + 1), p == 0 ? iota : 0,
-                           (const uint32_t*)(ghist + p * kSortDigits), tickets + p, status, err);
+        const uint32_t tag = scratch.tag0 + (uint32_t)p + 1;
+        const uint32_t* cp = scratch.counts + p * kSortDigits;
+        if (items == kSortItems)
+            hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, V3, kSortItems>), grid, dim3(kBlock), 0, st, io, n,
+                               P.shift[p], P.bits[p], tag, p == 0 ? iota : 0, cp, scratch.tickets + p, scratch.status, err);
+        else
+            hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, V3, kSortItemsSmall>), grid, dim3(kBlock), 0, st, io, n,
+                               P.shift[p], P.bits[p], tag, p == 0 ? iota : 0, cp, scratch.tickets + p, scratch.status, err);
         if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "sort: pass launch");
     }
-    if (!scratch) {
-        const hipError_t e = dev_free(scr, st);
+    if (own) {
+        const hipError_t e = dev_free(own, st);
         if (rc == TM_OK && e != hipSuccess) rc = tm_fail(TM_EDEVICE, "sort: free");
     }
     return rc;
@@ -790,28 +877,23 @@ int sort_run(const SortSet<K, V0, V1, V2, V3>& in, const SortSet<K, V0, V1, V2, 
 template <typename K, typename V0, typename V1, typename V2, typename V3>
 int sort_into(const SortSet<K, V0, V1, V2, V3>& in, const SortSet<K, V0, V1, V2, V3>& out,
               const SortSet<K, V0, V1, V2, V3>& tmp, int64_t n, int lo_bit, int nbits, int iota, int* err,
-              hipStream_t st) {
-    SortPlan P = sort_plan(lo_bit, nbits);
-    if (P.npass == 0) {
-        P.npass = 1;
-        P.shift[0] = 0;
-        P.bits[0] = 0;
-    }
+              hipStream_t st, const SortScratch& scratch = {}) {
+    const SortPlan P = sort_plan_copy(lo_bit, nbits);
     const SortSet<K, V0, V1, V2, V3> bufs[2] = {(P.npass & 1) ? out : tmp, (P.npass & 1) ? tmp : out};
     int res = 0;
-    return sort_run(in, bufs, n, P, iota, err, st, nullptr, &res);
+    return sort_run(in, bufs, n, P, iota, err, st, scratch, &res);
 }
 
 // Sorts (keys, vals) by bits [lo_bit, nbits) of the key, stably.  Buffers
 // ping-pong between (keys, vals) and (tkeys, tvals); on return *k_out /
 // *v_out point to whichever pair holds the result (the tkeys pair after an
 // odd number of passes).  iota_vals: vals holds nothing yet and stands for
-// 0 .. n-1.  scratch_ext: sort_scratch_bytes(n) bytes from the caller, or
-// null.  err: bit kSortStall is set if a look-back wait ran out.
+// 0 .. n-1.  scratch: as for sort_run.  err: bit kSortStall is set if a
+// look-back wait ran out.
 template <typename K>
 int radix_sort_pairs(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64_t n, int lo_bit, int nbits,
                      K** k_out, uint32_t** v_out, int* err, hipStream_t st, bool iota_vals = false,
-                     void* scratch_ext = nullptr) {
+                     const SortScratch& scratch = {}) {
     *k_out = keys;
     *v_out = vals;
     if (n > 1 && nbits > lo_bit) {
@@ -825,7 +907,7 @@ int radix_sort_pairs(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64_t
         const S bufs[2] = {b0, b1};
         const SortPlan P = sort_plan(lo_bit, nbits);
         int res = 0;
-        TM_TRY(sort_run(in, bufs, n, P, iota_vals ? 1 : 0, err, st, scratch_ext, &res));
+        TM_TRY(sort_run(in, bufs, n, P, iota_vals ? 1 : 0, err, st, scratch, &res));
         *k_out = bufs[res].k;
         *v_out = bufs[res].v0;
     } else if (iota_vals) {
