@@ -195,30 +195,51 @@ void host_stage_release(void* p) {
     g_stage_free.push_back(p);
 }
 
-hipError_t read_back(const HostRead* r, int n, hipStream_t st) {
+bool HostStage::stage(const HostRead* r, int n) {
+    if (n > kStageReads) return false;
     size_t total = 0;
-    for (int i = 0; i < n; ++i) total += (r[i].bytes + 15) & ~(size_t)15;
-    unsigned char* stage = total <= kHostStageBytes ? static_cast<unsigned char*>(host_stage_acquire()) : nullptr;
-    hipError_t e = hipSuccess;
+    for (int i = 0; i < n; ++i) {
+        if (r[i].bytes % sizeof(uint32_t)) return false;
+        total += (r[i].bytes + 15) & ~(size_t)15;
+    }
+    if (total > kHostStageBytes) return false;
+    if (!block_) block_ = host_stage_acquire();
+    if (!block_) return false;
+    list = StageList{};
     size_t off = 0;
-    for (int i = 0; i < n && e == hipSuccess; ++i) {
-        if (r[i].bytes == 0) continue;
-        e = hipMemcpyAsync(stage ? stage + off : r[i].host, r[i].dev, r[i].bytes, hipMemcpyDeviceToHost, st);
+    for (int i = 0; i < n; ++i) {
+        r_[i] = r[i];
+        list.dst[i] = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(block_) + off);
+        list.src[i] = static_cast<const uint32_t*>(r[i].dev);
+        list.words[i] = (uint32_t)(r[i].bytes / sizeof(uint32_t));
         off += (r[i].bytes + 15) & ~(size_t)15;
     }
-    // the stream is waited for also after a failed enqueue: no copy into the
-    // staging block may still be in flight when it goes back to the list
-    const hipError_t es = sync_stream(st);
-    if (e == hipSuccess) e = es;
-    if (stage) {
-        off = 0;
-        for (int i = 0; i < n && e == hipSuccess; ++i) {
-            if (r[i].bytes) std::memcpy(r[i].host, stage + off, r[i].bytes);
-            off += (r[i].bytes + 15) & ~(size_t)15;
-        }
-        host_stage_release(stage);
-    }
+    n_ = n;
+    return true;
+}
+
+hipError_t HostStage::finish(hipStream_t st) {
+    const hipError_t e = sync_stream(st);
+    for (int i = 0; i < n_ && e == hipSuccess; ++i)
+        if (r_[i].bytes) std::memcpy(r_[i].host, list.dst[i], r_[i].bytes);
+    n_ = 0;
     return e;
+}
+
+hipError_t read_back(const HostRead* r, int n, hipStream_t st) {
+    HostStage hs;
+    if (hs.stage(r, n)) {
+        const hipError_t e = stage_launch(hs.list, st);
+        // the stream is waited for also after a failed launch: nothing may
+        // still be writing the block when it goes back to the list
+        const hipError_t es = hs.finish(st);
+        return e != hipSuccess ? e : es;
+    }
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < n && e == hipSuccess; ++i)
+        if (r[i].bytes) e = hipMemcpyAsync(r[i].host, r[i].dev, r[i].bytes, hipMemcpyDeviceToHost, st);
+    const hipError_t es = sync_stream(st);
+    return e == hipSuccess ? es : e;
 }
 
 hipEvent_t timing_event_acquire(int* dev) {

@@ -101,7 +101,8 @@ struct LaneAcc {
 struct Partial {
     u128 acc2, acc2_sq;
     u64 n_valid, n_vertex, n_delta, n_order, n_nonzero;
-    u64 flags;  // bit 0: acc2 wrapped, bit 1: acc2_sq saturated
+    u64 flags;  // bit 0: acc2 wrapped, bit 1: acc2_sq saturated, bit 2: a
+                // completion count overflowed, bit 3: inconsistent tables
     u64 bytes;  // access-model bytes (counting pass only)
 };
 
@@ -661,10 +662,10 @@ __device__ __forceinline__ bool draw_root(const SampleArgs& a, const W* cum, W W
 // Inconsistent tables give a harmless key and set bad.
 template <typename W>
 __device__ __forceinline__ uint32_t root_key(const SampleArgs& a, const W* cum, W Wtot, const X128& X,
-                                             const RootGuide& g0, const RootGuide& g1, bool& bad) {
+                                             const RootGuide& g0, const RootGuide& g1, bool& bad, u64* nb = nullptr) {
     int32_t i, e0;
     uint32_t key = ~0u;  // set by a one-pair guide bucket
-    if (!draw_root_from<W>(a, cum, Wtot, X, g0, g1, i, e0, nullptr, &key)) {
+    if (!draw_root_from<W>(a, cum, Wtot, X, g0, g1, i, e0, nb, &key)) {
         bad = true;
         return 0u;
     }
@@ -770,8 +771,8 @@ __device__ __forceinline__ u128 completions(const SampleArgs& a, const SampleArg
     return m_phi;
 }
 
-// kWin (root-sorted only): each child's window is read from the kept table
-// at its parent's list position instead of searched for.
+// kWin: each child's window is read from the kept table at its parent's list
+// position instead of searched for.
 // kSmall: trees of at most four edges and motifs of at most five vertices,
 // so that fewer register slots are live (more waves per SIMD).
 // kNarrow (W = u128 only): a widened set whose list tables stayed 64-bit;
@@ -782,7 +783,6 @@ template <typename W, bool kCount, bool kGeneral, bool kSorted, bool kWin = fals
           bool kNarrow = false>
 __device__ __forceinline__ void sample_positions(const SampleArgs& a, const SampleArgs& ga, const W* cum, u64 x0,
                                                  u64 xend, u64 stride, LaneAcc& L) {
-    static_assert(kSorted || !kWin, "windows are read by list position");
     static_assert(!kNarrow || sizeof(W) == 16, "only a 128-bit set has narrower list tables");
     using WC = typename std::conditional<kNarrow, u64, W>::type;  // child-pick arithmetic
     constexpr int NT = kSmall ? 4 : kMaxSlots - 1;  // register slots; a.nt of them are used
@@ -800,10 +800,21 @@ __device__ __forceinline__ void sample_positions(const SampleArgs& a, const Samp
         sfor<0, K>([&](auto xx) { img[decltype(xx)::value] = -1 - decltype(xx)::value; });
         u64 r;
         int32_t i, e0, u0, v0;
-        if constexpr (kSorted) {
-            // the root was drawn by root_kernel; lanes follow the sorted order
-            const uint32_t key = a.skey[x] - a.key_base;
-            r = a.sval[x];
+        if constexpr (kSorted || kWin) {
+            // the root by its T position: drawn by root_kernel (lanes follow
+            // the sorted order), or here (few samples, in their own order)
+            uint32_t key;
+            if constexpr (kSorted) {
+                key = a.skey[x] - a.key_base;
+                r = a.sval[x];
+            } else {
+                r = x;
+                const X128 X = draw_block(a.seed, a.j0 + r, 0);
+                RootGuide g0, g1;
+                guide_pair(a, X, g0, g1);
+                key = root_key<W>(a, cum, job_W<W>(a), X, g0, g1, bad, kCount ? &nb : nullptr);
+                if (bad) break;
+            }
             const int32_t pos = (int32_t)(key >> 1);
             if constexpr (kWin) posv[0] = pos;
             const int rd = a.root_dir;
@@ -815,7 +826,7 @@ __device__ __forceinline__ void sample_positions(const SampleArgs& a, const Samp
             v0 = rd ? own0 : nbr0;
             const int64_t blk = te[0] / a.ilen;
             i = (int32_t)(((blk & 1) == (int64_t)(key & 1)) ? blk : blk - 1);
-            if constexpr (kCount) nb += 8 + 12 + (G.lt32[0] ? 4 : 8);
+            if constexpr (kCount) nb += (kSorted ? 8 : 0) + 12 + (G.lt32[0] ? 4 : 8);
         } else {
             // draw 0: interval, then center edge
             r = x;
@@ -1038,8 +1049,10 @@ __device__ __forceinline__ LaneAcc lane_zero() {
     return L;
 }
 
-// Block-wide sum of the lanes' partials into *out; flags into *ovf.
-__device__ __forceinline__ void lanes_reduce(const LaneAcc& L, Partial* out, int* ovf) {
+constexpr u64 kPartOverflow = 4, kPartBad = 8;
+
+// Block-wide sum of the lanes' partials into *out.
+__device__ __forceinline__ void lanes_reduce(const LaneAcc& L, Partial* out) {
     Partial acc;
     acc.acc2 = L.acc2;
     acc.acc2_sq = L.acc2_sq;
@@ -1048,11 +1061,9 @@ __device__ __forceinline__ void lanes_reduce(const LaneAcc& L, Partial* out, int
     acc.n_delta = L.n_delta;
     acc.n_order = L.n_order;
     acc.n_nonzero = L.n_nonzero;
-    acc.flags = L.flags;
+    acc.flags = L.flags | (L.ovf ? kPartOverflow : 0) | (L.bad ? kPartBad : 0);
     acc.bytes = L.nb;
     block_reduce_write(acc, out);
-    if (L.ovf) atomicOr(ovf, 1);
-    if (L.bad) atomicOr(ovf, 2);
 }
 
 template <typename W, bool kCount, bool kGeneral, bool kSorted, bool kWin, bool kSmall = false, bool kNarrow = false>
@@ -1068,7 +1079,7 @@ __global__ void __launch_bounds__(kBlock) sample_kernel(SampleArgs a) {
     const W* cum = a.cum_in_lds ? cumL : cumG;
     LaneAcc L = lane_zero();
     if (job_skipped<W>(a, job_W<W>(a))) {
-        lanes_reduce(L, &a.parts[blockIdx.x], a.ovf);  // nothing drawn
+        lanes_reduce(L, &a.parts[blockIdx.x]);  // nothing drawn
         return;
     }
     if constexpr (kGeneral) {
@@ -1084,11 +1095,14 @@ __global__ void __launch_bounds__(kBlock) sample_kernel(SampleArgs a) {
         sample_positions<W, kCount, kGeneral, kSorted, kWin, kSmall, kNarrow>(
             a, a, cum, (u64)blockIdx.x * kBlock + threadIdx.x, a.count, (u64)gridDim.x * kBlock, L);
     }
-    lanes_reduce(L, &a.parts[blockIdx.x], a.ovf);
+    lanes_reduce(L, &a.parts[blockIdx.x]);
 }
 
-// Sum of the block partials (integers: the order does not matter).
-__global__ void __launch_bounds__(kBlock) reduce_kernel(const Partial* parts, int n, Partial* out) {
+// Sum of the block partials (integers: the order does not matter) into *out,
+// which may be a pinned block of the host, and the call's other results with
+// it (list).
+__global__ void __launch_bounds__(kBlock) reduce_kernel(const Partial* parts, int n, Partial* out, StageList list) {
+    stage_copy(list);
     Partial acc;
     acc.acc2 = 0;
     acc.acc2_sq = 0;
@@ -1115,17 +1129,15 @@ using SampleKernel = void (*)(SampleArgs);
 
 template <typename W, bool kCount, bool kSorted>
 SampleKernel sample_variant(const SampleArgs& a) {
-    if constexpr (kSorted) {
-        if (a.has_win && !a.general_runs && a.nt <= 4 && a.k <= 5)
-            return sample_kernel<W, kCount, false, true, true, true>;
-        if constexpr (sizeof(W) == 16) {
-            if (a.has_win && !a.general_runs && !a.list_wide)
-                return sample_kernel<W, kCount, false, true, true, false, true>;
-        }
-        if (a.has_win)
-            return a.general_runs ? sample_kernel<W, kCount, true, true, true>
-                                  : sample_kernel<W, kCount, false, true, true>;
+    if (a.has_win && !a.general_runs && a.nt <= 4 && a.k <= 5)
+        return sample_kernel<W, kCount, false, kSorted, true, true>;
+    if constexpr (sizeof(W) == 16) {
+        if (a.has_win && !a.general_runs && !a.list_wide)
+            return sample_kernel<W, kCount, false, kSorted, true, false, true>;
     }
+    if (a.has_win)
+        return a.general_runs ? sample_kernel<W, kCount, true, kSorted, true>
+                              : sample_kernel<W, kCount, false, kSorted, true>;
     return a.general_runs ? sample_kernel<W, kCount, true, kSorted, false>
                           : sample_kernel<W, kCount, false, kSorted, false>;
 }
@@ -1359,7 +1371,7 @@ batch_root_kernel(const SampleArgs* __restrict__ jobs, const Tile* __restrict__ 
 template <typename W, bool kGeneral, int kWinMode>
 __global__ void __launch_bounds__(kBlock)
 batch_sample_kernel(const SampleArgs* __restrict__ jobs, const Tile* __restrict__ tiles, int n_tiles,
-                    int* __restrict__ counter, Partial* __restrict__ tile_parts, int* __restrict__ ovf) {
+                    int* __restrict__ counter, Partial* __restrict__ tile_parts) {
     __shared__ int s_tile;
     while (true) {
         __syncthreads();
@@ -1378,22 +1390,22 @@ batch_sample_kernel(const SampleArgs* __restrict__ jobs, const Tile* __restrict_
             else
                 sample_positions<W, false, kGeneral, true, false>(a, a, nullptr, T.begin + threadIdx.x, T.end, kBlock, L);
         }
-        lanes_reduce(L, &tile_parts[t], ovf);
+        lanes_reduce(L, &tile_parts[t]);
     }
 }
 
 template <typename W, bool kGeneral>
 void launch_batch_sample(int mode, dim3 grid, hipStream_t st, const SampleArgs* jobs, const Tile* tiles, int n_tiles,
-                         int* counter, Partial* tile_parts, int* ovf) {
+                         int* counter, Partial* tile_parts) {
     if (mode == 0)
         hipLaunchKernelGGL((batch_sample_kernel<W, kGeneral, 0>), grid, dim3(kBlock), 0, st, jobs, tiles, n_tiles,
-                           counter, tile_parts, ovf);
+                           counter, tile_parts);
     else if (mode == 1)
         hipLaunchKernelGGL((batch_sample_kernel<W, kGeneral, 1>), grid, dim3(kBlock), 0, st, jobs, tiles, n_tiles,
-                           counter, tile_parts, ovf);
+                           counter, tile_parts);
     else
         hipLaunchKernelGGL((batch_sample_kernel<W, kGeneral, 2>), grid, dim3(kBlock), 0, st, jobs, tiles, n_tiles,
-                           counter, tile_parts, ovf);
+                           counter, tile_parts);
 }
 
 // One block per job: the sum of the job's tile partials.
@@ -1560,11 +1572,12 @@ int sample_run(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, hipStrea
     int* ovf = nullptr;
     uint32_t *k0 = nullptr, *v0 = nullptr, *k1 = nullptr, *v1 = nullptr;
     TM_HIP(dev_alloc((void**)&parts, (size_t)(blocks + 1) * sizeof(Partial), st));
-    // the flag word and the sort's scratch in one block, cleared together
-    const size_t flag_bytes = 256 + (sorted ? sort_scratch_bytes((int64_t)chunk) : 0);
-    TM_HIP(dev_alloc((void**)&ovf, flag_bytes, st));
+    // root draws and sort: their flag word and the sort's scratch in one block,
+    // cleared together (the samplers' flags travel with their sums)
+    const size_t flag_bytes = 256 + sort_scratch_bytes((int64_t)chunk);
     SortScratch sort;
     if (sorted) {
+        TM_HIP(dev_alloc((void**)&ovf, flag_bytes, st));
         sort = sort_scratch_at(reinterpret_cast<unsigned char*>(ovf) + 256);
         TM_HIP(dev_alloc((void**)&k0, chunk * sizeof(uint32_t), st));
         TM_HIP(dev_alloc((void**)&v0, chunk * sizeof(uint32_t), st));
@@ -1591,8 +1604,8 @@ int sample_run(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, hipStrea
         // the root draws keep a wider grid (more draws in flight)
         const dim3 rgrid((unsigned)std::min<u64>((n + kBlock - 1) / kBlock, 8192));
         StageTimer t_roots, t_sample, t_reduce;
-        TM_TRY(fill_u32(ovf, (int64_t)(flag_bytes / sizeof(uint32_t)), 0u, st));
         if (sorted) {
+            TM_TRY(fill_u32(ovf, (int64_t)(flag_bytes / sizeof(uint32_t)), 0u, st));
             if (!model_bytes) t_roots.start(TM_STAGE_ROOTS, st);
             if (w->wide)
                 hipLaunchKernelGGL(root_kernel<u128>, rgrid, dim3(kBlock), lds, st, a, k0, v0);
@@ -1610,20 +1623,28 @@ int sample_run(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, hipStrea
         TM_HIP(launch_sample(kfn, grid, klds, st, a));
         t_sample.stop();
         if (!model_bytes) t_reduce.start(TM_STAGE_REDUCE, st);
-        hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kBlock), 0, st, (const Partial*)parts,
-                           (int)grid.x, parts + blocks);
-        TM_HIP(hipGetLastError());
-        t_reduce.stop();
+        // the last kernel delivers the call's results to the host
         Partial hc;
-        TM_HIP(read_back({{&hc, parts + blocks, sizeof hc},
-                          {&hovf, ovf, sizeof hovf},
-                          {&hflag, wflag, deferred ? sizeof hflag : 0},
-                          {&hW, a.Wdev, deferred ? sizeof hW : 0}},
-                         st));
+        const HostRead reads[kStageReads] = {{&hc, parts + blocks, sizeof hc},
+                                             {&hovf, ovf, sorted ? sizeof hovf : 0},
+                                             {&hflag, wflag, deferred ? sizeof hflag : 0},
+                                             {&hW, a.Wdev, deferred ? sizeof hW : 0}};
+        HostStage hs;
+        const bool staged = hs.stage(reads, kStageReads);
+        hs.list.words[0] = 0;  // the sums go there themselves
+        hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kBlock), 0, st, (const Partial*)parts, (int)grid.x,
+                           staged ? reinterpret_cast<Partial*>(hs.list.dst[0]) : parts + blocks, hs.list);
+        const hipError_t le = hipGetLastError();
+        t_reduce.stop();
+        // (waited for also after a failed launch, before the block goes back)
+        const hipError_t re = staged ? hs.finish(st) : read_back(reads, kStageReads, st);
+        TM_HIP(le);
+        TM_HIP(re);
         t_roots.finish();
         t_sample.finish();
         t_reduce.finish();
-        if (hovf) break;
+        h.flags |= hc.flags;
+        if (hovf || (hc.flags & (kPartOverflow | kPartBad))) break;
         if (deferred && (hflag || hW == 0)) break;  // nothing was drawn
         if (!add_ok(h.acc2, hc.acc2, &h.acc2)) h.flags |= 1;
         if (!add_ok(h.acc2_sq, hc.acc2_sq, &h.acc2_sq)) {
@@ -1635,12 +1656,11 @@ int sample_run(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, hipStrea
         h.n_delta += hc.n_delta;
         h.n_order += hc.n_order;
         h.n_nonzero += hc.n_nonzero;
-        h.flags |= hc.flags;
         h.bytes += hc.bytes;
     }
     TM_HIP(dev_free(parts, st));
-    TM_HIP(dev_free(ovf, st));
     if (sorted) {
+        TM_HIP(dev_free(ovf, st));
         TM_HIP(dev_free(k0, st));
         TM_HIP(dev_free(v0, st));
         TM_HIP(dev_free(k1, st));
@@ -1662,8 +1682,8 @@ int sample_run(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, hipStrea
         }
     }
     if (hovf & kSortStall) return tm_fail(TM_EDEVICE, "sample: root sort look-back stalled");
-    if (hovf & 2) return tm_fail(TM_EDEVICE, "sample: inconsistent weight tables");
-    if (hovf || (h.flags & 1)) return tm_fail(TM_EOVERFLOW, "sample: a count reaches 2^128");
+    if ((hovf & 2) || (h.flags & kPartBad)) return tm_fail(TM_EDEVICE, "sample: inconsistent weight tables");
+    if (hovf || (h.flags & (1 | kPartOverflow))) return tm_fail(TM_EOVERFLOW, "sample: a count reaches 2^128");
     out->acc2.lo = (u64)h.acc2;
     out->acc2.hi = (u64)(h.acc2 >> 64);
     out->acc2_sq.lo = (u64)h.acc2_sq;
@@ -1730,7 +1750,9 @@ struct Group {
     uint32_t *k0 = nullptr, *v0 = nullptr, *k1 = nullptr, *v1 = nullptr;
     Partial *tparts = nullptr, *jparts = nullptr;
     int *ctr = nullptr, *ovf = nullptr, *djf = nullptr, *djc = nullptr;
-    unsigned char* pinned = nullptr;  // captured passes: host staging of the uploads
+    unsigned char* up = nullptr;         // the uploaded arrays' block
+    std::vector<unsigned char> packed;   // ... and its host copy, as the copy command reads it
+    unsigned char* pinned = nullptr;     // captured passes: the same in pinned memory
 };
 
 // Host side: job arguments, tiles grouped by kernel variant.  Wdev / wflag
@@ -1807,21 +1829,36 @@ void group_prepare(tm_weights* const* ws, const std::vector<int>& act, const u64
     G.g_st_first[4] = (int)G.stt.size();
 }
 
+// Offsets of the uploaded arrays in their block; at[5]: its size.
+void group_layout(const Group& G, size_t (&at)[6]) {
+    const size_t sz[5] = {G.na * sizeof(SampleArgs), G.rt.size() * sizeof(Tile), G.stt.size() * sizeof(Tile),
+                          G.na * sizeof(int), G.na * sizeof(int)};
+    at[0] = 0;
+    for (int x = 0; x < 5; ++x) at[x + 1] = at[x] + ((sz[x] + 255) & ~(size_t)255);
+}
+
 int group_alloc(Group& G, hipStream_t st) {
     const int na = G.na;
-    TM_HIP(dev_alloc((void**)&G.djobs, na * sizeof(SampleArgs), st));
-    TM_HIP(dev_alloc((void**)&G.drt, G.rt.size() * sizeof(Tile), st));
-    TM_HIP(dev_alloc((void**)&G.dst, G.stt.size() * sizeof(Tile), st));
+    // the host arrays' device copies lie in one block, uploaded together
+    {
+        size_t at[6];
+        group_layout(G, at);
+        TM_HIP(dev_alloc((void**)&G.up, at[5], st));
+        G.djobs = reinterpret_cast<SampleArgs*>(G.up + at[0]);
+        G.drt = reinterpret_cast<Tile*>(G.up + at[1]);
+        G.dst = reinterpret_cast<Tile*>(G.up + at[2]);
+        G.djf = reinterpret_cast<int*>(G.up + at[3]);
+        G.djc = reinterpret_cast<int*>(G.up + at[4]);
+    }
     TM_HIP(dev_alloc((void**)&G.k0, G.total * sizeof(uint32_t), st));
     TM_HIP(dev_alloc((void**)&G.v0, G.total * sizeof(uint32_t), st));
     TM_HIP(dev_alloc((void**)&G.k1, G.total * sizeof(uint32_t), st));
     TM_HIP(dev_alloc((void**)&G.v1, G.total * sizeof(uint32_t), st));
     TM_HIP(dev_alloc((void**)&G.tparts, G.stt.size() * sizeof(Partial), st));
     TM_HIP(dev_alloc((void**)&G.jparts, na * sizeof(Partial), st));
-    TM_HIP(dev_alloc((void**)&G.ctr, 16 * sizeof(int), st));
-    TM_HIP(dev_alloc((void**)&G.ovf, sizeof(int), st));
-    TM_HIP(dev_alloc((void**)&G.djf, na * sizeof(int), st));
-    TM_HIP(dev_alloc((void**)&G.djc, na * sizeof(int), st));
+    // work counters, flag word and the sort's scratch, cleared together
+    TM_HIP(dev_alloc((void**)&G.ctr, 256 + sort_scratch_bytes((int64_t)G.total), st));
+    G.ovf = G.ctr + 16;
     // the sorted arrays end where an even number of passes leaves them
     for (int y = 0; y < na; ++y) {
         G.args[y].skey = G.passes % 2 == 0 ? G.k0 : G.k1;
@@ -1830,33 +1867,32 @@ int group_alloc(Group& G, hipStream_t st) {
     return TM_OK;
 }
 
-// Uploads of the host arrays; staged through pinned memory when `pinned`
-// (captured passes replay the copies from that buffer).
+// The upload of the host arrays, packed into one copy (five took 8 us each);
+// from pinned memory when `pinned` (captured passes replay the copy from that
+// buffer).
 int group_upload(Group& G, bool pinned, hipStream_t st) {
     const size_t sz[5] = {G.na * sizeof(SampleArgs), G.rt.size() * sizeof(Tile), G.stt.size() * sizeof(Tile),
                           G.na * sizeof(int), G.na * sizeof(int)};
     const void* src[5] = {G.args.data(), G.rt.data(), G.stt.data(), G.jfirst.data(), G.jcount.data()};
-    void* dst[5] = {G.djobs, G.drt, G.dst, G.djf, G.djc};
+    size_t at[6];
+    group_layout(G, at);
+    unsigned char* host;
     if (pinned) {
-        size_t total = 0;
-        for (size_t b : sz) total += (b + 255) & ~(size_t)255;
-        TM_HIP(hipHostMalloc((void**)&G.pinned, total, hipHostMallocDefault));
-        size_t o = 0;
-        for (int x = 0; x < 5; ++x) {
-            std::memcpy(G.pinned + o, src[x], sz[x]);
-            src[x] = G.pinned + o;
-            o += (sz[x] + 255) & ~(size_t)255;
-        }
+        TM_HIP(hipHostMalloc((void**)&G.pinned, at[5], hipHostMallocDefault));
+        host = G.pinned;
+    } else {
+        G.packed.resize(at[5]);
+        host = G.packed.data();
     }
     for (int x = 0; x < 5; ++x)
-        if (sz[x]) TM_HIP(hipMemcpyAsync(dst[x], src[x], sz[x], hipMemcpyHostToDevice, st));
+        if (sz[x]) std::memcpy(host + at[x], src[x], sz[x]);
+    TM_HIP(hipMemcpyAsync(G.up, host, at[5], hipMemcpyHostToDevice, st));
     return TM_OK;
 }
 
 // Counters, root draws, the sort, sampling and per-job sums into jparts.
 int group_launch(Group& G, hipStream_t st, bool timed) {
-    TM_TRY(fill_u32(G.ctr, 16, 0u, st));
-    TM_TRY(fill_u32(G.ovf, 1, 0u, st));
+    TM_TRY(fill_u32(G.ctr, (int64_t)((256 + sort_scratch_bytes((int64_t)G.total)) / sizeof(uint32_t)), 0u, st));
     StageTimer t_roots, t_sample, t_reduce;
     if (timed) t_roots.start(TM_STAGE_ROOTS, st);
     for (int grp = 0; grp < 4; ++grp) {
@@ -1876,7 +1912,8 @@ int group_launch(Group& G, hipStream_t st, bool timed) {
         uint32_t *ksr, *vsr;
         TM_TRY(radix_sort_pairs<uint32_t>(G.k0, G.v0, G.k1, G.v1, (int64_t)G.total, root_sort_lo_bit(G.key_bits),
                                           G.key_bits, &ksr, &vsr,
-                                          G.ovf, st));
+                                          G.ovf, st, false,
+                                          sort_scratch_at(reinterpret_cast<unsigned char*>(G.ctr) + 256)));
         if (ksr != G.args[0].skey) return tm_fail(TM_EDEVICE, "batch: unexpected sort buffer");
     }
     t_roots.stop();
@@ -1890,10 +1927,10 @@ int group_launch(Group& G, hipStream_t st, bool timed) {
         int* c = G.ctr + 4 + grp;
         const int wm = G.g_win[grp];
         switch (grp) {
-            case 0: launch_batch_sample<u64, false>(wm, grid, st, G.djobs, tl, nt, c, tp, G.ovf); break;
-            case 1: launch_batch_sample<u64, true>(wm, grid, st, G.djobs, tl, nt, c, tp, G.ovf); break;
-            case 2: launch_batch_sample<u128, false>(wm, grid, st, G.djobs, tl, nt, c, tp, G.ovf); break;
-            default: launch_batch_sample<u128, true>(wm, grid, st, G.djobs, tl, nt, c, tp, G.ovf); break;
+            case 0: launch_batch_sample<u64, false>(wm, grid, st, G.djobs, tl, nt, c, tp); break;
+            case 1: launch_batch_sample<u64, true>(wm, grid, st, G.djobs, tl, nt, c, tp); break;
+            case 2: launch_batch_sample<u128, false>(wm, grid, st, G.djobs, tl, nt, c, tp); break;
+            default: launch_batch_sample<u128, true>(wm, grid, st, G.djobs, tl, nt, c, tp); break;
         }
         TM_HIP(hipGetLastError());
     }
@@ -1913,8 +1950,8 @@ int group_launch(Group& G, hipStream_t st, bool timed) {
 }
 
 void group_free(Group& G, hipStream_t st) {
-    for (void* q : {(void*)G.djobs, (void*)G.drt, (void*)G.dst, (void*)G.k0, (void*)G.v0, (void*)G.k1, (void*)G.v1,
-                    (void*)G.tparts, (void*)G.jparts, (void*)G.ctr, (void*)G.ovf, (void*)G.djf, (void*)G.djc})
+    for (void* q : {(void*)G.up, (void*)G.k0, (void*)G.v0, (void*)G.k1, (void*)G.v1, (void*)G.tparts, (void*)G.jparts,
+                    (void*)G.ctr})
         (void)dev_free(q, st);
     if (G.pinned) (void)hipHostFree(G.pinned);
     G.pinned = nullptr;
@@ -1926,12 +1963,14 @@ int group_read(Group& G, const std::vector<int>& act, hipStream_t st, JobSums* o
     int hovf = 0;
     TM_HIP(read_back({{hp.data(), G.jparts, G.na * sizeof(Partial)}, {&hovf, G.ovf, sizeof(int)}}, st));
     if (hovf & kSortStall) return tm_fail(TM_EDEVICE, "batch: root sort look-back stalled");
-    if (hovf & 2) return tm_fail(TM_EDEVICE, "batch: inconsistent weight tables");
+    u64 any = 0;
+    for (const Partial& h : hp) any |= h.flags;
+    if ((hovf & 2) || (any & kPartBad)) return tm_fail(TM_EDEVICE, "batch: inconsistent weight tables");
     for (int y = 0; y < G.na; ++y) {
         const Partial& h = hp[y];
         JobSums& o = out[act[y]];
         o = JobSums{};
-        if ((hovf & 1) || (h.flags & 1)) {
+        if ((any & kPartOverflow) || (h.flags & 1)) {
             o.status = TM_EOVERFLOW;
             continue;
         }
@@ -2149,16 +2188,18 @@ int family_run(tm_weights* w, const HostPlan* plans, int n, u64 seed, u64 k, hip
     }
     const int key_bits = bits_of(2 * (u64)w->g->m - 1);
     // per chunk: every member's reduced sums (after the per-block partials)
-    // and flags (ovf[0] for the shared root pass and sort, ovf[1 + f] for
-    // member f), read back together
+    // and the flags of the shared root pass and sort, read back together
     std::vector<Partial> hp(n);
-    std::vector<int> hov(n + 1);
+    int hovf = 0;
     Partial* parts = nullptr;
     int* ovf = nullptr;
     uint32_t *k0 = nullptr, *v0 = nullptr, *k1 = nullptr, *v1 = nullptr;
     TM_HIP(dev_alloc((void**)&parts, (size_t)(blocks + n) * sizeof(Partial), st));
-    TM_HIP(dev_alloc((void**)&ovf, (size_t)(n + 1) * sizeof(int), st));
+    const size_t flag_bytes = 256 + sort_scratch_bytes((int64_t)chunk);
+    SortScratch sort;
     if (sorted) {
+        TM_HIP(dev_alloc((void**)&ovf, flag_bytes, st));
+        sort = sort_scratch_at(reinterpret_cast<unsigned char*>(ovf) + 256);
         TM_HIP(dev_alloc((void**)&k0, chunk * sizeof(uint32_t), st));
         TM_HIP(dev_alloc((void**)&v0, chunk * sizeof(uint32_t), st));
         TM_HIP(dev_alloc((void**)&k1, chunk * sizeof(uint32_t), st));
@@ -2172,11 +2213,10 @@ int family_run(tm_weights* w, const HostPlan* plans, int n, u64 seed, u64 k, hip
             args[f].count = cnt;
             args[f].recs = nullptr;
             args[f].parts = parts;
-            args[f].ovf = ovf + 1 + f;
         }
-        rc = fill_u32(ovf, n + 1, 0u, st);
-        if (rc != TM_OK) break;
         if (sorted) {
+            rc = fill_u32(ovf, (int64_t)(flag_bytes / sizeof(uint32_t)), 0u, st);
+            if (rc != TM_OK) break;
             const dim3 rgrid((unsigned)std::min<u64>((cnt + kBlock - 1) / kBlock, 8192));
             SampleArgs ra = args[0];
             ra.ovf = ovf;
@@ -2187,7 +2227,7 @@ int family_run(tm_weights* w, const HostPlan* plans, int n, u64 seed, u64 k, hip
             if (hipGetLastError() != hipSuccess) { rc = tm_fail(TM_EDEVICE, "family: launch"); break; }
             uint32_t *ks, *vs;
             rc = radix_sort_pairs<uint32_t>(k0, v0, k1, v1, (int64_t)cnt, root_sort_lo_bit(key_bits), key_bits, &ks,
-                                            &vs, ovf, st, true);
+                                            &vs, ovf, st, true, sort);
             if (rc != TM_OK) break;
             for (int f = 0; f < n; ++f) {
                 args[f].skey = ks;
@@ -2201,20 +2241,19 @@ int family_run(tm_weights* w, const HostPlan* plans, int n, u64 seed, u64 k, hip
                 break;
             }
             hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kBlock), 0, st, (const Partial*)parts, (int)grid.x,
-                               parts + blocks + f);
+                               parts + blocks + f, StageList{});
             if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "family: launch");
         }
         if (rc != TM_OK) break;
         if (read_back({{hp.data(), parts + blocks, (size_t)n * sizeof(Partial)},
-                       {hov.data(), ovf, (size_t)(n + 1) * sizeof(int)}},
+                       {&hovf, ovf, sorted ? sizeof hovf : 0}},
                       st) != hipSuccess) {
             rc = tm_fail(TM_EDEVICE, "family: copy");
             break;
         }
         for (int f = 0; f < n && rc == TM_OK; ++f) {
             const Partial& h = hp[f];
-            const int hovf = hov[0] | hov[1 + f];
-            if (hovf & (2 | kSortStall)) {
+            if ((hovf & (2 | kSortStall)) || (h.flags & kPartBad)) {
                 rc = tm_fail(TM_EDEVICE, (hovf & kSortStall) ? "family: root sort look-back stalled"
                                                              : "family: inconsistent weight tables");
                 break;
@@ -2224,7 +2263,7 @@ int family_run(tm_weights* w, const HostPlan* plans, int n, u64 seed, u64 k, hip
             x.acc2_sq = h.acc2_sq;
             x.n_nonzero = h.n_nonzero;
             x.flags = h.flags & 3;
-            if (hovf & 1) x.flags |= 1;
+            if (h.flags & kPartOverflow) x.flags |= 1;
             sums_merge(sums[f], x);
             if (f == 0) {
                 JobSums t;
@@ -2407,7 +2446,7 @@ int sample_run_noalloc(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, 
     }
     TM_HIP(launch_sample(kfn, grid, klds, st, a));
     hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kBlock), 0, st, (const Partial*)parts, (int)grid.x,
-                       parts + blocks);
+                       parts + blocks, StageList{});
     TM_HIP(hipGetLastError());
     Partial h;
     int hovf = 0;
@@ -2415,8 +2454,8 @@ int sample_run_noalloc(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, 
     TM_HIP(hipMemcpyAsync(&hovf, ovf, sizeof hovf, hipMemcpyDeviceToHost, st));
     TM_HIP(hipStreamSynchronize(st));
     if (hovf & kSortStall) return tm_fail(TM_EDEVICE, "sample: root sort look-back stalled");
-    if (hovf & 2) return tm_fail(TM_EDEVICE, "sample: inconsistent weight tables");
-    if (hovf || (h.flags & 1)) return tm_fail(TM_EOVERFLOW, "sample: a count reaches 2^128");
+    if ((hovf & 2) || (h.flags & kPartBad)) return tm_fail(TM_EDEVICE, "sample: inconsistent weight tables");
+    if (hovf || (h.flags & (1 | kPartOverflow))) return tm_fail(TM_EOVERFLOW, "sample: a count reaches 2^128");
     out->acc2.lo = (u64)h.acc2;
     out->acc2.hi = (u64)(h.acc2 >> 64);
     out->acc2_sq.lo = (u64)h.acc2_sq;

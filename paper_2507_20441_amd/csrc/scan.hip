@@ -32,7 +32,14 @@ __global__ void __launch_bounds__(kBlock) scan_single_kernel(u128* a, int64_t n,
     if (carry) atomicOr(ovf, 1);
 }
 
+__global__ void __launch_bounds__(kBlock) stage_kernel(StageList list) { stage_copy(list); }
+
 }  // namespace
+
+hipError_t stage_launch(const StageList& list, hipStream_t st) {
+    hipLaunchKernelGGL(stage_kernel, dim3(1), dim3(kBlock), 0, st, list);
+    return hipGetLastError();
+}
 
 __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)

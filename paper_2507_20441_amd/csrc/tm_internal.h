@@ -86,19 +86,53 @@ constexpr size_t kHostStageBytes = 16384;
 void* host_stage_acquire();
 void host_stage_release(void* p);
 
-// One device-to-host copy of read_back.
+// One device-to-host copy of read_back (whole 32-bit words).
 struct HostRead {
     void* host;
     const void* dev;
     size_t bytes;
 };
+
+// Device words on their way into a pinned block: up to kStageReads copies that
+// one kernel makes (stage_copy in tm_primitives.h; a copy command for each
+// took 8-10 us, most of it between the commands).
+constexpr int kStageReads = 4;
+struct StageList {
+    uint32_t* dst[kStageReads];
+    const uint32_t* src[kStageReads];
+    uint32_t words[kStageReads];  // 0: unused
+};
+
+// The kernel that makes them (scan.hip).
+hipError_t stage_launch(const StageList& list, hipStream_t st);
+
 // The n copies, in stream order on st, then one synchronisation of st (as
-// sync_stream); through one pinned block when they fit in it, else straight
-// into the destinations.
+// sync_stream); through one pinned block by a kernel when they fit in it,
+// else by copies straight into the destinations.
 hipError_t read_back(const HostRead* r, int n, hipStream_t st);
 inline hipError_t read_back(std::initializer_list<HostRead> r, hipStream_t st) {
     return read_back(r.begin(), (int)r.size(), st);
 }
+
+// The same around a kernel of the caller's that takes the list itself, so that
+// the call's last kernel also delivers its results: stage(r) lays the copies
+// out (false: they do not fit, or no pinned memory; the caller uses
+// read_back), finish synchronises st and fills the destinations.
+class HostStage {
+public:
+    HostStage() = default;
+    ~HostStage() { host_stage_release(block_); }
+    HostStage(const HostStage&) = delete;
+    HostStage& operator=(const HostStage&) = delete;
+    bool stage(const HostRead* r, int n);
+    StageList list{};
+    hipError_t finish(hipStream_t st);
+
+private:
+    HostRead r_[kStageReads];
+    int n_ = 0;
+    void* block_ = nullptr;
+};
 
 // ---------------------------------------------------------------------------
 // Graph handle.

@@ -38,6 +38,24 @@ __global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v);
 // p[i] = i for i < n.
 int fill_iota_u32(uint32_t* p, int64_t n, hipStream_t st);
 
+// Of two kernel arguments, as a select between the two loaded values: an index
+// into the kernel's arguments has the compiler copy them to scratch, and so
+// does a plain select, which the optimiser may turn back into a select of the
+// two addresses.  The empty asm statement pins both in scalar registers first
+// (arguments are uniform across the wave).
+template <typename P>
+__device__ __forceinline__ P pick_arg(P x0, P x1, int i) {
+    asm("" : "+s"(x0), "+s"(x1));
+    return i ? x1 : x0;
+}
+
+// The staged copies (StageList), by the lanes of one block.
+__device__ __forceinline__ void stage_copy(const StageList& L) {
+#pragma unroll
+    for (int i = 0; i < kStageReads; ++i)
+        for (uint32_t w = threadIdx.x; w < L.words[i]; w += blockDim.x) L.dst[i][w] = L.src[i][w];
+}
+
 // ---------------------------------------------------------------------------
 // Wave and block scans of 128-bit values (two 64-bit shuffles per step).
 // ---------------------------------------------------------------------------
@@ -216,17 +234,6 @@ struct Scan2Args {
     int self;
     int* ovf;
 };
-
-// Of two kernel arguments, as a select between the two loaded values: an index
-// into the kernel's arguments has the compiler copy them to scratch, and so
-// does a plain select, which the optimiser may turn back into a select of the
-// two addresses.  The empty asm statement pins both in scalar registers first
-// (arguments are uniform across the wave).
-template <typename P>
-__device__ __forceinline__ P pick_arg(P x0, P x1, int i) {
-    asm("" : "+s"(x0), "+s"(x1));
-    return i ? x1 : x0;
-}
 
 // The block's job (blockIdx.y); F::pick selects between two functors.
 template <typename T, typename F>
