@@ -898,9 +898,13 @@ __device__ __forceinline__ void sample_positions(const SampleArgs& a, const Samp
             if (leaf) {
                 mass = (WC)((w.p1 - w.p0) - (w.q1 - w.q0));
             } else {
+                // (most windows exclude nothing: no reads for an empty run)
                 bt0 = qt[w.p0];
-                bn0 = qn[w.q0];
-                mass = (qt[w.p1] - bt0) - (qn[w.q1] - bn0);
+                mass = qt[w.p1] - bt0;
+                if (w.q1 > w.q0) {
+                    bn0 = qn[w.q0];
+                    mass -= qn[w.q1] - bn0;
+                }
             }
             // a child of a positive-weight match always has positive mass
             if (mass == 0 || w.p1 <= w.p0) { bad = true; break; }
@@ -926,7 +930,7 @@ __device__ __forceinline__ void sample_positions(const SampleArgs& a, const Samp
             if (leaf) {
                 pos = w.p0 + (int32_t)rr + J;
             } else {
-                const WC tgt = bt0 + rr + (qn[w.q0 + J] - bn0);
+                const WC tgt = bt0 + rr + (J > 0 ? qn[w.q0 + J] - bn0 : (WC)0);
                 pos = qt.upper_bound_coarse(w.p0 + 1, w.p1 + 1, tgt) - 1;
             }
             pos = pos < w.p0 ? w.p0 : (pos >= w.p1 ? w.p1 - 1 : pos);

