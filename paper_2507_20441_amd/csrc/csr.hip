@@ -182,36 +182,71 @@ __device__ __forceinline__ void guide_fill(const uint32_t* own, const int32_t* o
     wave_fill(guide, to, end, (int32_t)m);
 }
 
-// What follows a T-order sort, in one pass over the positions: by eid the
-// edge's position (the inverse of leid), the (neighbour, time) records of
-// 32-bit lists, and the guide by time.
+// What follows a T-order sort, in one pass over the positions of each
+// direction (blockIdx.y): by eid the edge's position (the inverse of leid), the
+// (neighbour, time) records of 32-bit lists, and the guide by time.
+template <typename TT>
+struct ListFinish {
+    const uint32_t* own;
+    const int32_t* leid;
+    const uint32_t* nbr;
+    const TT* t;
+    const int32_t* off;
+    int32_t* pos;
+    uint2* nt;
+    int32_t* guide;
+};
+
 template <typename TT>
 __global__ void __launch_bounds__(kBlock)
-list_finish_kernel(const uint32_t* own, const int32_t* leid, const uint32_t* nbr, const TT* t, const int32_t* off,
-                   int64_t m, int32_t n, int bt, uint32_t tmul, int32_t* pos, uint2* nt, int32_t* guide) {
+list_finish_kernel(ListFinish<TT> f0, ListFinish<TT> f1, int64_t m, int32_t n, int bt, uint32_t tmul) {
+    const int y = blockIdx.y;
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const TT* t = pick_arg(f0.t, f1.t, y);
     if (p < m) {
-        if ((uint32_t)leid[p] < (uint64_t)m) pos[leid[p]] = (int32_t)p;
-        if (nt) nt[p] = make_uint2(nbr[p], (uint32_t)t[p]);
+        const int32_t e = pick_arg(f0.leid, f1.leid, y)[p];
+        if ((uint32_t)e < (uint64_t)m) pick_arg(f0.pos, f1.pos, y)[e] = (int32_t)p;
+        uint2* nt = pick_arg(f0.nt, f1.nt, y);
+        if (nt) nt[p] = make_uint2(pick_arg(f0.nbr, f1.nbr, y)[p], (uint32_t)t[p]);
     }
-    if (guide) guide_fill(own, off, m, n, p, [&](int64_t i) { return (u64)t[i]; }, bt, tmul, guide);
+    int32_t* guide = pick_arg(f0.guide, f1.guide, y);
+    if (guide)
+        guide_fill(pick_arg(f0.own, f1.own, y), pick_arg(f0.off, f1.off, y), m, n, p,
+                   [&](int64_t i) { return (u64)t[i]; }, bt, tmul, guide);
 }
 
-// N order: the packed key from the carried neighbour and time (ntime: the
-// carried times, which may be nkey itself), each entry's position in this
-// direction's T order, and the guide by neighbour.  own: the owners, the
-// same sequence in both orders.
+// N order (of one direction, or of both: blockIdx.y): the packed key from the
+// carried neighbour and time (time: the carried times, which may be nkey
+// itself), each entry's position in the direction's T order, and the guide by
+// neighbour.  own: the owners, the same sequence in both orders.
+template <typename TT>
+struct NOrderFix {
+    const uint32_t* nbr;
+    const TT* time;
+    const int32_t* neid;
+    const int32_t* tpos;
+    const uint32_t* own;
+    const int32_t* off;
+    u64* nkey;
+    int32_t* nxref;
+    int32_t* guide;
+};
+
 template <typename TT>
 __global__ void __launch_bounds__(kBlock)
-n_order_fix_kernel(const uint32_t* nbr, const TT* ntime, const int32_t* neid, const int32_t* tpos, const uint32_t* own,
-                   const int32_t* off, int64_t m, int32_t n, int bt, int bn, uint32_t nmul, u64* nkey, int32_t* nxref,
-                   int32_t* guide) {
+n_order_fix_kernel(NOrderFix<TT> f0, NOrderFix<TT> f1, int64_t m, int32_t n, int bt, int bn, uint32_t nmul) {
+    const int y = blockIdx.y;
     const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const uint32_t* nbr = pick_arg(f0.nbr, f1.nbr, y);
     if (q < m) {
-        nkey[q] = ((u64)nbr[q] << bt) | (u64)ntime[q];
-        nxref[q] = (uint32_t)neid[q] < (uint64_t)m ? tpos[neid[q]] : -1;
+        pick_arg(f0.nkey, f1.nkey, y)[q] = ((u64)nbr[q] << bt) | (u64)pick_arg(f0.time, f1.time, y)[q];
+        const int32_t e = pick_arg(f0.neid, f1.neid, y)[q];
+        pick_arg(f0.nxref, f1.nxref, y)[q] = (uint32_t)e < (uint64_t)m ? pick_arg(f0.tpos, f1.tpos, y)[e] : -1;
     }
-    if (guide) guide_fill(own, off, m, n, q, [&](int64_t i) { return (u64)nbr[i]; }, bn, nmul, guide);
+    int32_t* guide = pick_arg(f0.guide, f1.guide, y);
+    if (guide)
+        guide_fill(pick_arg(f0.own, f1.own, y), pick_arg(f0.off, f1.off, y), m, n, q,
+                   [&](int64_t i) { return (u64)nbr[i]; }, bn, nmul, guide);
 }
 
 // The pair ranks of both lists (see DevGraph), in one launch: thread i < m
@@ -266,7 +301,11 @@ pair_rank_kernel(DevGraph G, const uint32_t* own0, const uint32_t* own1, const u
 // List offsets from the owner-sorted keys: off[v] is the first position whose
 // owner is >= v.  Position p writes the offsets of the owners in
 // (key[p-1], key[p]]; the last position also closes the owners after it.
-__global__ void offsets_kernel(const uint32_t* key, int64_t m, int32_t n, int32_t* off) {
+// (both directions: blockIdx.y)
+__global__ void offsets_kernel(const uint32_t* key0, const uint32_t* key1, int64_t m, int32_t n, int32_t* off0,
+                               int32_t* off1) {
+    const uint32_t* key = pick_arg(key0, key1, blockIdx.y);
+    int32_t* off = pick_arg(off0, off1, blockIdx.y);
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     int64_t from = 0, to = 0, end = 0;
     if (p < m) {
@@ -288,6 +327,12 @@ __global__ void offsets_kernel(const uint32_t* key, int64_t m, int32_t n, int32_
 // would have to meet many motifs to earn them.  Above 2^28 edges their memory
 // goes to weight sets, as that of the owners.
 bool pair_ranks_kept(int64_t m) { return m >= ((int64_t)1 << 19) && m <= ((int64_t)1 << 28); }
+
+// List sorts side by side up to this many edges (a pass of few tiles leaves the
+// chip idle: a build of 2^14 edges takes 167 us with pairs and 201 without,
+// 2^20 512 and 630, 2^21 862 and 1028, 2^22 1685 and 1760).  Larger builds
+// gain 3% and keep the memory of the second buffers (28 to 36 B per edge).
+constexpr int64_t kPairedSorts = (int64_t)1 << 22;
 
 int bits_for(u64 x) {
     int b = 0;
@@ -376,8 +421,10 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     // 2^32 - 1; t32e: those times by eid, the list sorts' input.
     const bool narrow = g->T < (int64_t)0xFFFFFFFFll;
     uint32_t* t32e = nullptr;
-    unsigned char* scr = nullptr;  // the sorts' scratch
-    uint32_t* opos[3] = {nullptr, nullptr, nullptr};  // N orders: the carried other T positions, and their sort buffer
+    unsigned char* scr = nullptr;     // the sorts' scratch
+    unsigned char* second = nullptr;  // buffers of a second list sort
+    uint32_t* opos[4] = {nullptr, nullptr, nullptr, nullptr};  // N orders: the carried other T positions, and
+                                                               // their sort buffers
     uint32_t* nbr32[2] = {nullptr, nullptr};  // 32-bit times: the T orders' neighbours until packed
     auto release = [&]() {
         for (uint32_t*& b : nbr32) {
@@ -392,6 +439,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         nbr_tmp = nullptr;
         if (scr) (void)dev_free(scr, st);
         scr = nullptr;
+        if (second) (void)dev_free(second, st);
+        second = nullptr;
         for (uint32_t*& b : opos) {
             if (b) (void)dev_free(b, st);
             b = nullptr;
@@ -430,12 +479,14 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     // clearing, counting and starting five sorts one by one was a fifth of the
     // build.)
     constexpr int kHeads = 6;
-    const size_t scr_bytes = kHeads * kSortHeadBytes + sort_status_bytes(m);
+    const size_t scr_bytes = kHeads * kSortHeadBytes + (m <= kPairedSorts ? 2 : 1) * sort_status_bytes(m);
     uint32_t tag = 0;
     auto scratch_of = [&](int tickets, int counts) {
         SortScratch x = sort_scratch_at(scr + (size_t)tickets * kSortHeadBytes);
         x.counts = reinterpret_cast<uint32_t*>(scr + (size_t)counts * kSortHeadBytes);
-        x.status = reinterpret_cast<u64*>(scr + kHeads * kSortHeadBytes);
+        // (the directions' own when they sort side by side, with equal tags)
+        const bool own = m <= kPairedSorts && tickets >= 2 && (tickets & 1);
+        x.status = reinterpret_cast<u64*>(scr + kHeads * kSortHeadBytes + (own ? sort_status_bytes(m) : 0));
         x.counted = tickets >= 2;
         x.tag0 = tag;
         tag += kSortMaxPasses;
@@ -500,37 +551,72 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         using TT = decltype(time_tag);
         using V = typename std::conditional<sizeof(TT) == 4, uint32_t, u64>::type;
         using L = SortSet<uint32_t, V, uint32_t, uint32_t>;
-        L tmp;  // the other buffer of the list sorts
-        tmp.k = reinterpret_cast<uint32_t*>(work[0]);
-        tmp.v1 = reinterpret_cast<uint32_t*>(work[0]) + m;
-        tmp.v0 = reinterpret_cast<V*>(work[1]);
-        tmp.v2 = reinterpret_cast<uint32_t*>(work[2]);
-        uint32_t* nkeys_out = reinterpret_cast<uint32_t*>(work[2]) + m;  // N order: its sorted keys (unused)
-        // N order: the carried times (32-bit: the upper half of work[1]; 64-bit:
-        // the key array itself, packed in place afterwards)
-        uint32_t* ntime32 = reinterpret_cast<uint32_t*>(work[1]) + m;
+        using LR = SortSet<uint32_t, V, uint32_t, uint32_t, uint32_t>;
+        // Graphs of few sort tiles sort both directions side by side, with
+        // buffers of their own; larger ones in turn, through the same ones.
+        const bool paired = m <= kPairedSorts;
+        const bool ranks = pair_ranks_kept(m);
+        struct Bufs {
+            LR tmp;               // the other buffer of the list sorts
+            uint32_t* nkeys;      // N order: its sorted keys (unused)
+            uint32_t* ntime;      // N order: the carried 32-bit times (64-bit ones: the key array itself,
+                                  // packed in place afterwards)
+            uint32_t* nbr;        // N order: the carried neighbours
+        } buf[2];
         const bool keep_own = m <= ((int64_t)1 << 28);
-        uint32_t* own[2] = {nullptr, nullptr};
         if (!keep_own && dev_alloc((void**)&nbr_tmp, (size_t)m * sizeof(uint32_t), st) != hipSuccess)
             return tm_fail(TM_ENOMEM, "graph: work arrays");
-        uint32_t* nbr_carried = keep_own ? reinterpret_cast<uint32_t*>(work[3]) : nbr_tmp;
+        for (int x = 0; x < (paired ? 4 : 3) && ranks; ++x)
+            if (dev_alloc((void**)&opos[x], (size_t)m * sizeof(uint32_t), st) != hipSuccess)
+                return tm_fail(TM_ENOMEM, "graph: work arrays");
+        buf[0].tmp.k = reinterpret_cast<uint32_t*>(work[0]);
+        buf[0].tmp.v1 = reinterpret_cast<uint32_t*>(work[0]) + m;
+        buf[0].tmp.v0 = reinterpret_cast<V*>(work[1]);
+        buf[0].tmp.v2 = reinterpret_cast<uint32_t*>(work[2]);
+        buf[0].tmp.v3 = opos[2];
+        buf[0].nkeys = reinterpret_cast<uint32_t*>(work[2]) + m;
+        buf[0].ntime = reinterpret_cast<uint32_t*>(work[1]) + m;
+        buf[0].nbr = keep_own ? reinterpret_cast<uint32_t*>(work[3]) : nbr_tmp;
+        buf[1] = buf[0];
+        if (paired) {
+            // six 4-byte arrays and the values of type V
+            if (dev_alloc((void**)&second, (size_t)m * (6 * sizeof(uint32_t) + sizeof(V)), st) != hipSuccess)
+                return tm_fail(TM_ENOMEM, "graph: work arrays");
+            buf[1].tmp.v0 = reinterpret_cast<V*>(second);
+            uint32_t* at = reinterpret_cast<uint32_t*>(buf[1].tmp.v0 + m);
+            uint32_t** const arrays[6] = {&buf[1].tmp.k, &buf[1].tmp.v1, &buf[1].tmp.v2, &buf[1].nkeys, &buf[1].ntime,
+                                          &buf[1].nbr};
+            for (uint32_t** x : arrays) {
+                *x = at;
+                at += m;
+            }
+            buf[1].tmp.v3 = opos[3];
+        }
+        uint32_t* own[2] = {nullptr, nullptr};
         int32_t* tpos[2] = {nullptr, nullptr};
         TT* ltab[2] = {nullptr, nullptr};
         uint32_t* lnbr_of[2] = {nullptr, nullptr};  // each T order's neighbours (the N-order sorts' keys)
+        int32_t* off[2] = {nullptr, nullptr};
         // guides pay from lists of a few entries on; with fewer edges than
         // vertices the lists are shorter than that and the guides' entry per
         // vertex would outweigh the edges
         const bool guides = n <= m;
-        const bool ranks = pair_ranks_kept(m);
-        for (int x = 0; x < 3 && ranks; ++x)
-            if (dev_alloc((void**)&opos[x], (size_t)m * sizeof(uint32_t), st) != hipSuccess)
-                return tm_fail(TM_ENOMEM, "graph: work arrays");
         const size_t guide_len = (size_t)guide_first(n, (int32_t)m) + 1;
-        TM_TRY(sort_count<uint32_t>(reinterpret_cast<uint32_t*>(esrc), reinterpret_cast<uint32_t*>(edst), 2, m,
-                                    sort_plan_copy(0, bn), scratch_of(2, 2).counts, scratch_of(3, 3).counts, st));
+        const SortPlan plan = sort_plan_copy(0, bn);
+        // two sorts side by side, or one after the other
+        auto sort_lists = [&](auto* jobs, int iota) -> int {
+            int res = 0;
+            if (paired) return sort_run(jobs, 2, m, plan, iota, flags + 1, st, &res);
+            TM_TRY(sort_run(jobs, 1, m, plan, iota, flags + 1, st, &res));
+            return sort_run(jobs + 1, 1, m, plan, iota, flags + 1, st, &res);
+        };
+        TM_TRY(sort_count<uint32_t>(reinterpret_cast<uint32_t*>(esrc), reinterpret_cast<uint32_t*>(edst), 2, m, plan,
+                                    scratch_of(2, 2).counts, scratch_of(3, 3).counts, st));
+        SortJob<L> tsort[2];
+        ListFinish<TT> fin[2];
         for (int dir = 0; dir < 2; ++dir) {
             TT* lt = nullptr;
-            int32_t *leid = nullptr, *lnbr = nullptr, *lown = nullptr, *off = nullptr;
+            int32_t *leid = nullptr, *lnbr = nullptr, *lown = nullptr;
             TM_TRY(arena_alloc(g->arena, &lt, m));
             TM_TRY(arena_alloc(g->arena, &leid, m));
             if constexpr (sizeof(TT) == 4) {
@@ -542,10 +628,14 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
                 TM_TRY(arena_alloc(g->arena, &lnbr, m));
             }
             if (keep_own) TM_TRY(arena_alloc(g->arena, &lown, m));
-            TM_TRY(arena_alloc(g->arena, &off, (size_t)n + 1));
+            TM_TRY(arena_alloc(g->arena, &off[dir], (size_t)n + 1));
             TM_TRY(arena_alloc(g->arena, &tpos[dir], (size_t)m));
             own[dir] = keep_own ? reinterpret_cast<uint32_t*>(lown) : reinterpret_cast<uint32_t*>(work[3]) + dir * m;
-            L in, out;
+            uint2* nt = nullptr;
+            int32_t* tguide = nullptr;
+            if constexpr (sizeof(TT) == 4) TM_TRY(arena_alloc(g->arena, &nt, m));
+            if (guides) TM_TRY(arena_alloc(g->arena, &tguide, guide_len));
+            L in, out, tmp;
             in.k = reinterpret_cast<uint32_t*>(dir == 0 ? esrc : edst);
             in.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(t32e) : reinterpret_cast<V*>(et);
             in.v2 = reinterpret_cast<uint32_t*>(dir == 0 ? edst : esrc);
@@ -553,19 +643,14 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             out.v0 = reinterpret_cast<V*>(lt);
             out.v1 = reinterpret_cast<uint32_t*>(leid);
             out.v2 = reinterpret_cast<uint32_t*>(lnbr);
-            TM_TRY(sort_into(in, out, tmp, m, 0, bn, 2 /* eids: 0, 1, ... */, flags + 1, st,
-                             scratch_of(2 + dir, 2 + dir)));
-            hipLaunchKernelGGL(offsets_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const uint32_t*)own[dir],
-                               m, n, off);
-            uint2* nt = nullptr;
-            int32_t* tguide = nullptr;
-            if constexpr (sizeof(TT) == 4) TM_TRY(arena_alloc(g->arena, &nt, m));
-            if (guides) TM_TRY(arena_alloc(g->arena, &tguide, guide_len));
-            hipLaunchKernelGGL((list_finish_kernel<TT>), dim3(grid_for(m)), dim3(kBlock), 0, st,
-                               (const uint32_t*)own[dir], (const int32_t*)leid, (const uint32_t*)lnbr, (const TT*)lt,
-                               (const int32_t*)off, m, n, D.bt, D.tmul, tpos[dir], nt, tguide);
-            if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: list launch");
-            D.off[dir] = off;
+            tmp.k = buf[dir].tmp.k;
+            tmp.v0 = buf[dir].tmp.v0;
+            tmp.v1 = buf[dir].tmp.v1;
+            tmp.v2 = buf[dir].tmp.v2;
+            tsort[dir] = sort_job(in, out, tmp, plan.npass, scratch_of(2 + dir, 2 + dir));
+            fin[dir] = ListFinish<TT>{own[dir], leid, reinterpret_cast<uint32_t*>(lnbr), lt, off[dir], tpos[dir], nt,
+                                      tguide};
+            D.off[dir] = off[dir];
             D.tpos[dir] = tpos[dir];
             D.tguide[dir] = tguide;
             ltab[dir] = lt;
@@ -584,53 +669,76 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             D.leid[dir] = leid;
             D.lown[dir] = lown;
         }
+        TM_TRY(sort_lists(tsort, 2 /* eids: 0, 1, ... */));
+        hipLaunchKernelGGL(offsets_kernel, dim3(grid_for(m), 2), dim3(kBlock), 0, st, (const uint32_t*)own[0],
+                           (const uint32_t*)own[1], m, n, off[0], off[1]);
+        hipLaunchKernelGGL((list_finish_kernel<TT>), dim3(grid_for(m), 2), dim3(kBlock), 0, st, fin[0], fin[1], m, n,
+                           D.bt, D.tmul);
+        if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: list launch");
         // N order of dir d: the T order of the other direction (sorted by this
         // direction's neighbour, then time) stably re-sorted by this
-        // direction's owner, carrying time, eid and neighbour.
+        // direction's owner, carrying time, eid and neighbour, and for the pair
+        // ranks its position (0, 1, ...).
+        SortJob<LR> nsort[2];
+        NOrderFix<V> fix[2];
         for (int dir = 0; dir < 2; ++dir) {
             const int other = 1 - dir;
             u64* nkey = nullptr;
-            int32_t *nxref = nullptr, *neid = nullptr;
+            int32_t *nxref = nullptr, *neid = nullptr, *nguide = nullptr;
             TM_TRY(arena_alloc(g->arena, &nkey, m));
             TM_TRY(arena_alloc(g->arena, &nxref, m));
             TM_TRY(arena_alloc(g->arena, &neid, m));
-            int32_t* nguide = nullptr;
             if (guides) TM_TRY(arena_alloc(g->arena, &nguide, guide_len));
-            auto sort_n = [&](auto set) -> int {
-                using S = decltype(set);
-                S in, out, buf;
-                in.k = lnbr_of[other];
-                in.v0 = reinterpret_cast<V*>(ltab[other]);
-                in.v1 = reinterpret_cast<uint32_t*>(const_cast<int32_t*>(D.leid[other]));
-                in.v2 = own[other];
-                out.k = nkeys_out;
-                out.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(ntime32) : reinterpret_cast<V*>(nkey);
-                out.v1 = reinterpret_cast<uint32_t*>(neid);
-                out.v2 = nbr_carried;
-                buf.k = tmp.k;
-                buf.v0 = tmp.v0;
-                buf.v1 = tmp.v1;
-                buf.v2 = tmp.v2;
-                int iota = 0;
-                if constexpr (!std::is_same<decltype(in.v3), SortNone*>::value) {
-                    out.v3 = opos[dir];
-                    buf.v3 = opos[2];
-                    iota = 8;  // the other list's positions: 0, 1, ...
-                }
-                return sort_into(in, out, buf, m, 0, bn, iota, flags + 1, st, scratch_of(4 + dir, 2 + dir));
-            };
-            if (ranks) TM_TRY(sort_n(SortSet<uint32_t, V, uint32_t, uint32_t, uint32_t>{}));
-            else TM_TRY(sort_n(L{}));
-            const V* nt_sorted = sizeof(TT) == 4 ? reinterpret_cast<V*>(ntime32) : reinterpret_cast<V*>(nkey);
-            hipLaunchKernelGGL((n_order_fix_kernel<V>), dim3(grid_for(m)), dim3(kBlock), 0, st,
-                               (const uint32_t*)nbr_carried, nt_sorted, (const int32_t*)neid,
-                               (const int32_t*)tpos[dir], (const uint32_t*)own[dir], D.off[dir], m, n, D.bt, bn,
-                               D.nmul, nkey, nxref, nguide);
-            if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: list launch");
+            LR in, out;
+            in.k = lnbr_of[other];
+            in.v0 = reinterpret_cast<V*>(ltab[other]);
+            in.v1 = reinterpret_cast<uint32_t*>(const_cast<int32_t*>(D.leid[other]));
+            in.v2 = own[other];
+            out.k = buf[dir].nkeys;
+            out.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(buf[dir].ntime) : reinterpret_cast<V*>(nkey);
+            out.v1 = reinterpret_cast<uint32_t*>(neid);
+            out.v2 = buf[dir].nbr;
+            out.v3 = opos[dir];
+            nsort[dir] = sort_job(in, out, buf[dir].tmp, plan.npass, scratch_of(4 + dir, 2 + dir));
+            fix[dir] = NOrderFix<V>{buf[dir].nbr, out.v0, neid, tpos[dir], own[dir], off[dir], nkey, nxref, nguide};
             D.nkey[dir] = nkey;
             D.nxref[dir] = nxref;
             D.neid[dir] = neid;
             D.nguide[dir] = nguide;
+        }
+        auto fix_lists = [&](int first, int count) -> int {
+            hipLaunchKernelGGL((n_order_fix_kernel<V>), dim3(grid_for(m), (unsigned)count), dim3(kBlock), 0, st,
+                               fix[first], fix[1], m, n, D.bt, bn, D.nmul);
+            return hipGetLastError() == hipSuccess ? TM_OK : tm_fail(TM_EDEVICE, "graph: list launch");
+        };
+        auto n_orders = [&](const auto* jobs, int iota) -> int {
+            int res = 0;
+            if (paired) {
+                TM_TRY(sort_run(jobs, 2, m, plan, iota, flags + 1, st, &res));
+                return fix_lists(0, 2);
+            }
+            for (int dir = 0; dir < 2; ++dir) {
+                TM_TRY(sort_run(jobs + dir, 1, m, plan, iota, flags + 1, st, &res));
+                TM_TRY(fix_lists(dir, 1));
+            }
+            return TM_OK;
+        };
+        if (ranks) {
+            TM_TRY(n_orders(nsort, 8));
+        } else {
+            auto plain = [](const LR& x) {
+                L y;
+                y.k = x.k;
+                y.v0 = x.v0;
+                y.v1 = x.v1;
+                y.v2 = x.v2;
+                return y;
+            };
+            SortJob<L> three[2];
+            for (int dir = 0; dir < 2; ++dir)
+                three[dir] = SortJob<L>{plain(nsort[dir].in), {plain(nsort[dir].bufs[0]), plain(nsort[dir].bufs[1])},
+                                        nsort[dir].scratch};
+            TM_TRY(n_orders(three, 0));
         }
         if (ranks) {
             uint4* rank[2] = {nullptr, nullptr};

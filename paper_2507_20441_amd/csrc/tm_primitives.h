@@ -563,6 +563,14 @@ struct SortSize<SortNone> {
 struct SortIO {
     const void* in[5];  // keys, then the value arrays
     void* out[5];
+    const uint32_t* counts;
+    uint32_t* ticket;
+    u64* status;
+};
+
+// One pass of one sort or of two of the same kind (blockIdx.y).
+struct SortPass {
+    SortIO io[2];
 };
 
 // (two key arrays of one length: blockIdx.y picks)
@@ -654,8 +662,7 @@ __device__ __forceinline__ void sort_move_values(const void* vin, void* vout, bo
 
 template <typename K, typename V0, typename V1, typename V2, typename V3, int kItems>
 __global__ void __launch_bounds__(kBlock)
-sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int iota, const uint32_t* __restrict__ counts,
-                 uint32_t* __restrict__ ticket, u64* __restrict__ status, int* __restrict__ err) {
+sort_pass_kernel(SortPass pass, int64_t n, int shift, int bits, uint32_t tag, int iota, int* __restrict__ err) {
     constexpr size_t kElt = std::max(std::max(sizeof(K), SortSize<V0>::value),
                                      std::max(std::max(SortSize<V1>::value, SortSize<V2>::value), SortSize<V3>::value));
     constexpr int kTile = kBlock * kItems;
@@ -669,6 +676,16 @@ sort_pass_kernel(SortIO io, int64_t n, int shift, int bits, uint32_t tag, int io
     __shared__ uint32_t wsum[kWaves];
     __shared__ uint32_t s_tile;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int which = blockIdx.y;
+    SortIO io;
+#pragma unroll
+    for (int x = 0; x < 5; ++x) {
+        io.in[x] = pick_arg(pass.io[0].in[x], pass.io[1].in[x], which);
+        io.out[x] = pick_arg(pass.io[0].out[x], pass.io[1].out[x], which);
+    }
+    const uint32_t* __restrict__ counts = pick_arg(pass.io[0].counts, pass.io[1].counts, which);
+    uint32_t* __restrict__ ticket = pick_arg(pass.io[0].ticket, pass.io[1].ticket, which);
+    u64* __restrict__ status = pick_arg(pass.io[0].status, pass.io[1].status, which);
     if (threadIdx.x == 0) s_tile = atomicAdd(ticket, 1u);
     const uint32_t mask = (1u << bits) - 1u;
     const uint32_t d = threadIdx.x;
@@ -832,42 +849,68 @@ struct SortSet {
     V3* v3 = nullptr;
 };
 
-// Runs the plan's passes: pass p reads `in` (p = 0) or the previous pass's
-// output, and writes bufs[p & 1]; bufs[0] must not be `in` (bufs[1] may be:
-// the first pass has consumed it before the second writes).  Returns the
-// index of the buffer that holds the result.  iota: bit j set, value array j
-// holds nothing yet and stands for 0, 1, ..., n - 1.  scratch: cleared by the
-// caller, or with null counts allocated and
-// cleared here.
+// Where a sort's passes read and write: pass p reads `in` (p = 0) or the
+// previous pass's output, and writes bufs[p & 1]; bufs[0] must not be `in`
+// (bufs[1] may be: the first pass has consumed it before the second writes).
+// scratch: cleared by the caller, or with null counts allocated and cleared by
+// the sort.
+template <typename S>
+struct SortJob {
+    S in;
+    S bufs[2];
+    SortScratch scratch;
+};
+
+// Runs the plan's passes of one sort, or of two of n keys each with the same
+// plan side by side (their scratch must be the caller's): a pass of few tiles
+// leaves the chip idle, and two fill it better for the time of one.  Sets
+// *result to the index of the buffer that holds the result.  iota: bit j set,
+// value array j holds nothing yet and stands for 0, 1, ..., n - 1.
 template <typename K, typename V0, typename V1, typename V2, typename V3>
-int sort_run(const SortSet<K, V0, V1, V2, V3>& in, const SortSet<K, V0, V1, V2, V3> (&bufs)[2], int64_t n,
-             const SortPlan& P, int iota, int* err, hipStream_t st, SortScratch scratch, int* result) {
+int sort_run(const SortJob<SortSet<K, V0, V1, V2, V3>>* jobs, int njobs, int64_t n, const SortPlan& P, int iota,
+             int* err, hipStream_t st, int* result) {
+    using S = SortSet<K, V0, V1, V2, V3>;
     *result = (P.npass - 1) & 1;
     if (n <= 0 || P.npass <= 0) return TM_OK;
-    if (bufs[0].k == in.k) return tm_fail(TM_EDEVICE, "sort: the first pass would overwrite its input");
+    SortScratch scratch[2];
     unsigned char* own = nullptr;
     int rc = TM_OK;
-    if (!scratch.counts) {
+    for (int j = 0; j < njobs; ++j) {
+        scratch[j] = jobs[j].scratch;
+        if (jobs[j].bufs[0].k == jobs[j].in.k)
+            return tm_fail(TM_EDEVICE, "sort: the first pass would overwrite its input");
+        if (!scratch[j].counts && (njobs > 1 || j > 0)) return tm_fail(TM_EDEVICE, "sort: no scratch");
+    }
+    if (!scratch[0].counts) {
         const size_t bytes = sort_scratch_bytes(n);
         TM_HIP(dev_alloc((void**)&own, bytes, st));
-        scratch = sort_scratch_at(own);
+        scratch[0] = sort_scratch_at(own);
         rc = fill_u32(own, (int64_t)(bytes / sizeof(uint32_t)), 0u, st);
     }
-    if (rc == TM_OK && !scratch.counted) rc = sort_count<K>(in.k, in.k, 1, n, P, scratch.counts, scratch.counts, st);
+    for (int j = 0; j < njobs && rc == TM_OK; ++j)
+        if (!scratch[j].counted)
+            rc = sort_count<K>(jobs[j].in.k, jobs[j].in.k, 1, n, P, scratch[j].counts, scratch[j].counts, st);
     const int items = sort_items(n);
-    const dim3 grid((unsigned)sort_tiles(n));
+    const dim3 grid((unsigned)sort_tiles(n), (unsigned)njobs);
     for (int p = 0; p < P.npass && rc == TM_OK; ++p) {
-        const SortSet<K, V0, V1, V2, V3>& src = p == 0 ? in : bufs[(p - 1) & 1];
-        const SortSet<K, V0, V1, V2, V3>& dst = bufs[p & 1];
-        SortIO io{{src.k, src.v0, src.v1, src.v2, src.v3}, {dst.k, dst.v0, dst.v1, dst.v2, dst.v3}};
-        const uint32_t tag = scratch.tag0 + (uint32_t)p + 1;
-        const uint32_t* cp = scratch.counts + p * kSortDigits;
+        SortPass pass;
+        for (int j = 0; j < 2; ++j) {
+            const int y = j < njobs ? j : 0;
+            const S& src = p == 0 ? jobs[y].in : jobs[y].bufs[(p - 1) & 1];
+            const S& dst = jobs[y].bufs[p & 1];
+            pass.io[j] = SortIO{{src.k, src.v0, src.v1, src.v2, src.v3},
+                                {dst.k, dst.v0, dst.v1, dst.v2, dst.v3},
+                                scratch[y].counts + p * kSortDigits,
+                                scratch[y].tickets + p,
+                                scratch[y].status};
+        }
+        const uint32_t tag = scratch[0].tag0 + (uint32_t)p + 1;
         if (items == kSortItems)
-            hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, V3, kSortItems>), grid, dim3(kBlock), 0, st, io, n,
-                               P.shift[p], P.bits[p], tag, p == 0 ? iota : 0, cp, scratch.tickets + p, scratch.status, err);
+            hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, V3, kSortItems>), grid, dim3(kBlock), 0, st, pass, n,
+                               P.shift[p], P.bits[p], tag, p == 0 ? iota : 0, err);
         else
-            hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, V3, kSortItemsSmall>), grid, dim3(kBlock), 0, st, io, n,
-                               P.shift[p], P.bits[p], tag, p == 0 ? iota : 0, cp, scratch.tickets + p, scratch.status, err);
+            hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, V3, kSortItemsSmall>), grid, dim3(kBlock), 0, st, pass,
+                               n, P.shift[p], P.bits[p], tag, p == 0 ? iota : 0, err);
         if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "sort: pass launch");
     }
     if (own) {
@@ -877,18 +920,23 @@ int sort_run(const SortSet<K, V0, V1, V2, V3>& in, const SortSet<K, V0, V1, V2, 
     return rc;
 }
 
-// Sorts `in` by bits [lo_bit, nbits) of its keys into `out`, stably, with
-// `tmp` as the other buffer of the passes (`in` is left as it was unless
-// tmp is `in`, which is allowed only when an odd number of passes runs).  At
-// least one pass runs: a stable copy when no bit is sorted.
-template <typename K, typename V0, typename V1, typename V2, typename V3>
-int sort_into(const SortSet<K, V0, V1, V2, V3>& in, const SortSet<K, V0, V1, V2, V3>& out,
-              const SortSet<K, V0, V1, V2, V3>& tmp, int64_t n, int lo_bit, int nbits, int iota, int* err,
+// The job that sorts `in` into `out` in npass passes, with `tmp` as the other
+// buffer (`in` is left as it was unless tmp is `in`, which is allowed only
+// when an odd number of passes runs).
+template <typename S>
+SortJob<S> sort_job(const S& in, const S& out, const S& tmp, int npass, const SortScratch& scratch) {
+    return SortJob<S>{in, {(npass & 1) ? out : tmp, (npass & 1) ? tmp : out}, scratch};
+}
+
+// Sorts `in` by bits [lo_bit, nbits) of its keys into `out`, stably (see
+// sort_job).  At least one pass runs: a stable copy when no bit is sorted.
+template <typename S>
+int sort_into(const S& in, const S& out, const S& tmp, int64_t n, int lo_bit, int nbits, int iota, int* err,
               hipStream_t st, const SortScratch& scratch = {}) {
     const SortPlan P = sort_plan_copy(lo_bit, nbits);
-    const SortSet<K, V0, V1, V2, V3> bufs[2] = {(P.npass & 1) ? out : tmp, (P.npass & 1) ? tmp : out};
+    const SortJob<S> job = sort_job(in, out, tmp, P.npass, scratch);
     int res = 0;
-    return sort_run(in, bufs, n, P, iota, err, st, scratch, &res);
+    return sort_run(&job, 1, n, P, iota, err, st, &res);
 }
 
 // Sorts (keys, vals) by bits [lo_bit, nbits) of the key, stably.  Buffers
@@ -911,12 +959,12 @@ int radix_sort_pairs(K* keys, uint32_t* vals, K* tkeys, uint32_t* tvals, int64_t
         b0.k = tkeys;
         b0.v0 = tvals;
         b1 = in;
-        const S bufs[2] = {b0, b1};
+        const SortJob<S> job{in, {b0, b1}, scratch};
         const SortPlan P = sort_plan(lo_bit, nbits);
         int res = 0;
-        TM_TRY(sort_run(in, bufs, n, P, iota_vals ? 1 : 0, err, st, scratch, &res));
-        *k_out = bufs[res].k;
-        *v_out = bufs[res].v0;
+        TM_TRY(sort_run(&job, 1, n, P, iota_vals ? 1 : 0, err, st, &res));
+        *k_out = job.bufs[res].k;
+        *v_out = job.bufs[res].v0;
     } else if (iota_vals) {
         TM_TRY(fill_iota_u32(vals, n, st));  // no pass ran
     }
