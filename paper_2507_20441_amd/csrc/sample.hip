@@ -90,6 +90,27 @@ struct SampleArgs {
     uint32_t key_base;     // batched: skey of this job = key_base + its root key
 };
 
+// Members of a motif family that one pass completes together: their non-tree
+// edges (as in SampleArgs; the tree is the pass's).
+constexpr int kFamMax = 4;
+
+struct FamMember {
+    int n_runs;
+    int run_first[TM_MAX_L], run_len[TM_MAX_L], run_prev[TM_MAX_L], run_next[TM_MAX_L];
+    int free_src[TM_MAX_L], free_dst[TM_MAX_L];
+};
+
+struct FamArgs {
+    int n;  // 0: no family
+    FamMember mem[kFamMax];
+};
+
+struct FamLane {
+    u128 acc2[kFamMax], acc2_sq[kFamMax];
+    uint32_t n_nonzero[kFamMax];
+    uint32_t flags[kFamMax];  // Partial's
+};
+
 // Per-lane running sums of a sampling pass.
 struct LaneAcc {
     u128 acc2, acc2_sq;
@@ -105,6 +126,8 @@ struct Partial {
                 // completion count overflowed, bit 3: inconsistent tables
     u64 bytes;  // access-model bytes (counting pass only)
 };
+
+constexpr u64 kPartOverflow = 4, kPartBad = 8;
 
 constexpr int kCumLdsBytes = 24 * 1024;
 
@@ -718,9 +741,10 @@ __global__ void __launch_bounds__(kBlock) root_kernel(SampleArgs a, uint32_t* ke
 // ga: the same arguments where the no-inline routines read them (an LDS copy
 // in the single-job kernel, so that the kernel's arguments are never copied
 // to scratch for them).
-template <bool kCount, bool kGeneral, int NT, int K>
-__device__ __forceinline__ u128 completions(const SampleArgs& a, const SampleArgs& ga, const int32_t (&img)[K],
-                                            const int64_t (&te)[NT], bool& ovf, u64& nb) {
+// mem: whose non-tree edges (a, or a member of a family; general runs: a's).
+template <bool kCount, bool kGeneral, int NT, int K, typename M>
+__device__ __forceinline__ u128 completions(const SampleArgs& a, const SampleArgs& ga, const M& mem,
+                                            const int32_t (&img)[K], const int64_t (&te)[NT], bool& ovf, u64& nb) {
     const DevGraph& G = a.G;
     u128 m_phi = 0;
     const int64_t tfirst = pick(te, a.by_pi[0]), tlast = pick(te, a.by_pi[a.nt - 1]);
@@ -747,9 +771,9 @@ __device__ __forceinline__ u128 completions(const SampleArgs& a, const SampleArg
         }
     } else {
         m_phi = 1;
-        for (int r2 = 0; r2 < a.n_runs && m_phi != 0; ++r2) {
-            const int pv = a.run_prev[r2], nx = a.run_next[r2];
-            const int f0 = a.run_first[r2], len = a.run_len[r2];
+        for (int r2 = 0; r2 < mem.n_runs && m_phi != 0; ++r2) {
+            const int pv = mem.run_prev[r2], nx = mem.run_next[r2];
+            const int f0 = mem.run_first[r2], len = mem.run_len[r2];
             int64_t lo_t, hi_t;
             if (pv >= 0 && nx >= 0) {
                 lo_t = pick(te, pv) + 1;
@@ -761,9 +785,9 @@ __device__ __forceinline__ u128 completions(const SampleArgs& a, const SampleArg
                 lo_t = tlast + 1;
                 hi_t = tfirst + a.delta;
             }
-            const int32_t x0 = pick(img, a.free_src[f0]), y0 = pick(img, a.free_dst[f0]);
-            const int32_t x1 = len > 1 ? pick(img, a.free_src[f0 + 1]) : 0;
-            const int32_t y1 = len > 1 ? pick(img, a.free_dst[f0 + 1]) : 0;
+            const int32_t x0 = pick(img, mem.free_src[f0]), y0 = pick(img, mem.free_dst[f0]);
+            const int32_t x1 = len > 1 ? pick(img, mem.free_src[f0 + 1]) : 0;
+            const int32_t y1 = len > 1 ? pick(img, mem.free_dst[f0 + 1]) : 0;
             const u128 c = run_count_short<kCount>(G, x0, y0, x1, y1, len, lo_t, hi_t, nb);
             if (!mul_ok(m_phi, c, &m_phi)) ovf = true;
         }
@@ -779,10 +803,12 @@ __device__ __forceinline__ u128 completions(const SampleArgs& a, const SampleArg
 // its child masses fit 64 bits, so the child picks run in 64-bit arithmetic
 // (the same draws: floor(X n / 2^128) does not depend on the width n is
 // held in), and only the root draw is 128-bit.
+// kFam: the sums of fam's members go to F (L takes the validation counts).
 template <typename W, bool kCount, bool kGeneral, bool kSorted, bool kWin = false, bool kSmall = false,
-          bool kNarrow = false>
+          bool kNarrow = false, bool kFam = false>
 __device__ __forceinline__ void sample_positions(const SampleArgs& a, const SampleArgs& ga, const W* cum, u64 x0,
-                                                 u64 xend, u64 stride, LaneAcc& L) {
+                                                 u64 xend, u64 stride, LaneAcc& L, const FamArgs* fam = nullptr,
+                                                 FamLane* F = nullptr) {
     static_assert(!kNarrow || sizeof(W) == 16, "only a 128-bit set has narrower list tables");
     using WC = typename std::conditional<kNarrow, u64, W>::type;  // child-pick arithmetic
     constexpr int NT = kSmall ? 4 : kMaxSlots - 1;  // register slots; a.nt of them are used
@@ -998,16 +1024,34 @@ __device__ __forceinline__ void sample_positions(const SampleArgs& a, const Samp
             const int64_t b = tmin / a.ilen;
             n_phi = (b < a.q ? 1u : 0u) + ((b >= 1 && tmax < (b + 1) * a.ilen) ? 1u : 0u);
             // Alg. 5: completions over the non-tree edges
-            m_phi = completions<kCount, kGeneral, NT, K>(a, ga, img, te, ovf, nb);
             ++n_valid;
-            if (m_phi != 0) ++n_nonzero;
-            u128 term;
-            if (!mul_ok(m_phi, (u128)(2 / n_phi), &term)) ovf = true;
-            if (!add_ok(acc2, term, &acc2)) flags |= 1;
-            u128 sq;
-            if (!mul_ok(term, term, &sq) || !add_ok(acc2_sq, sq, &acc2_sq)) {
-                acc2_sq = ~(u128)0;
-                flags |= 2;
+            if constexpr (kFam) {
+                sfor<0, kFamMax>([&](auto fc) {
+                    constexpr int f = decltype(fc)::value;
+                    if (f >= fam->n) return;
+                    bool fo = false;
+                    const u128 mf = completions<kCount, false, NT, K>(a, ga, fam->mem[f], img, te, fo, nb);
+                    if (mf != 0) ++F->n_nonzero[f];
+                    u128 term, sq;
+                    if (!mul_ok(mf, (u128)(2 / n_phi), &term)) fo = true;
+                    if (!add_ok(F->acc2[f], term, &F->acc2[f])) F->flags[f] |= 1;
+                    if (!mul_ok(term, term, &sq) || !add_ok(F->acc2_sq[f], sq, &F->acc2_sq[f])) {
+                        F->acc2_sq[f] = ~(u128)0;
+                        F->flags[f] |= 2;
+                    }
+                    if (fo) F->flags[f] |= (uint32_t)kPartOverflow;
+                });
+            } else {
+                m_phi = completions<kCount, kGeneral, NT, K>(a, ga, a, img, te, ovf, nb);
+                if (m_phi != 0) ++n_nonzero;
+                u128 term;
+                if (!mul_ok(m_phi, (u128)(2 / n_phi), &term)) ovf = true;
+                if (!add_ok(acc2, term, &acc2)) flags |= 1;
+                u128 sq;
+                if (!mul_ok(term, term, &sq) || !add_ok(acc2_sq, sq, &acc2_sq)) {
+                    acc2_sq = ~(u128)0;
+                    flags |= 2;
+                }
             }
         } else if (status == 1) {
             ++n_vertex;
@@ -1052,8 +1096,6 @@ __device__ __forceinline__ LaneAcc lane_zero() {
     L.ovf = L.bad = false;
     return L;
 }
-
-constexpr u64 kPartOverflow = 4, kPartBad = 8;
 
 // Block-wide sum of the lanes' partials into *out.
 __device__ __forceinline__ void lanes_reduce(const LaneAcc& L, Partial* out) {
@@ -1102,11 +1144,41 @@ __global__ void __launch_bounds__(kBlock) sample_kernel(SampleArgs a) {
     lanes_reduce(L, &a.parts[blockIdx.x]);
 }
 
+// One pass of tree samples completed for up to kFamMax members of a family:
+// drawing and checking the tree is most of a sample's work, and the members
+// share it (four members, 2e6 samples on a graph of 2e6 edges: 252 us in one
+// pass, 382 us in four).  parts: member f's block partials from f gridDim.x on.
+template <typename W, bool kSorted, bool kSmall>
+__global__ void __launch_bounds__(kBlock) family_kernel(SampleArgs a, FamArgs fam) {
+    LaneAcc L = lane_zero();
+    FamLane F;
+    sfor<0, kFamMax>([&](auto fc) {
+        constexpr int f = decltype(fc)::value;
+        F.acc2[f] = F.acc2_sq[f] = 0;
+        F.n_nonzero[f] = F.flags[f] = 0;
+    });
+    sample_positions<W, false, false, kSorted, true, kSmall, false, true>(
+        a, a, static_cast<const W*>(a.cumW), (u64)blockIdx.x * kBlock + threadIdx.x, a.count, (u64)gridDim.x * kBlock, L,
+        &fam, &F);
+    sfor<0, kFamMax>([&](auto fc) {
+        constexpr int f = decltype(fc)::value;
+        if (f >= fam.n) return;
+        L.acc2 = F.acc2[f];
+        L.acc2_sq = F.acc2_sq[f];
+        L.n_nonzero = F.n_nonzero[f];
+        L.flags = F.flags[f];
+        __syncthreads();  // (the reduction's buffer)
+        lanes_reduce(L, &a.parts[(size_t)f * gridDim.x + blockIdx.x]);
+    });
+}
+
 // Sum of the block partials (integers: the order does not matter) into *out,
 // which may be a pinned block of the host, and the call's other results with
 // it (list).
+// (several such sums of n partials each: one per block)
 __global__ void __launch_bounds__(kBlock) reduce_kernel(const Partial* parts, int n, Partial* out, StageList list) {
-    stage_copy(list);
+    if (blockIdx.x == 0) stage_copy(list);
+    parts += (size_t)blockIdx.x * n;
     Partial acc;
     acc.acc2 = 0;
     acc.acc2_sq = 0;
@@ -1114,7 +1186,7 @@ __global__ void __launch_bounds__(kBlock) reduce_kernel(const Partial* parts, in
     acc.flags = 0;
     acc.bytes = 0;
     for (int b = threadIdx.x; b < n; b += kBlock) combine(acc, parts[b]);
-    block_reduce_write(acc, out);
+    block_reduce_write(acc, out + blockIdx.x);
 }
 
 __global__ void fill_undrawn_kernel(tm_sample_rec* recs, u64 count) {
@@ -1166,13 +1238,13 @@ hipError_t launch_sample(SampleKernel k, dim3 grid, size_t lds, hipStream_t st, 
 // the workgroups the chip holds at once for kernel k, since a partial last
 // round leaves CUs idle while the rest finish; two rounds, six for runs of
 // 2^25 samples and more (the partials' reduction is then negligible).
-unsigned sample_grid(SampleKernel k, size_t lds, u64 n) {
+unsigned sample_grid(const void* k, size_t lds, u64 n) {
     // a grid of at most one workgroup per CU is never more than one round
     // (the unsorted runs, below 2^16 samples, all stay there)
     const u64 need = (n + kBlock - 1) / kBlock;
     if (need <= 256) return (unsigned)std::max<u64>(1, need);
     struct Occ {
-        SampleKernel k;
+        const void* k;
         size_t lds;
         int dev, resident;
     };
@@ -1188,7 +1260,7 @@ unsigned sample_grid(SampleKernel k, size_t lds, u64 n) {
     }
     if (resident == 0) {
         int per_cu = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k), kBlock, lds) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kBlock, lds) !=
                 hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
             (void)hipGetLastError();
@@ -1200,6 +1272,16 @@ unsigned sample_grid(SampleKernel k, size_t lds, u64 n) {
     }
     const u64 rounds = n >= ((u64)1 << 25) ? 6 : 2;
     return (unsigned)std::min<u64>(need, rounds * (u64)resident);
+}
+
+unsigned sample_grid(SampleKernel k, size_t lds, u64 n) { return sample_grid(reinterpret_cast<const void*>(k), lds, n); }
+
+using FamilyKernel = void (*)(SampleArgs, FamArgs);
+
+template <typename W>
+FamilyKernel pick_family(bool sorted, bool small) {
+    if (small) return sorted ? family_kernel<W, true, true> : family_kernel<W, false, true>;
+    return sorted ? family_kernel<W, true, false> : family_kernel<W, false, false>;
 }
 
 // Samples per chunk (sort keys and offsets are 32-bit), and the smallest
@@ -2175,21 +2257,42 @@ int family_run(tm_weights* w, const HostPlan* plans, int n, u64 seed, u64 k, hip
         args[f].delta = P.mo.delta;
     }
     // the tree samples are the same for every member (draws keyed by sample
-    // id and slot): one root pass and sort per chunk, then one sampling pass
-    // per member over the sorted roots, completing that member's non-tree
-    // edges; the tree's validation counts come from the first member's pass
+    // id and slot): one root pass and sort per chunk, then sampling passes over
+    // the sorted roots, each completing the non-tree edges of its members; the
+    // tree's validation counts come from the first member's pass
     const u64 chunk = std::min<u64>(k, kChunk);
     const bool sorted = chunk >= kSortMin;
-    // each member's kernel and grid; the per-block partials of the widest
-    // grid come first in parts, the members' reduced sums after them
-    std::vector<SampleKernel> kfn(n);
-    std::vector<int> fblocks(n);
-    int blocks = 1;
+    // passes over the samples: members without general runs together where
+    // the set keeps its windows, the others each on its own; per pass its
+    // kernel and grid, and of the widest one the per-block partials come first
+    // in parts, the members' reduced sums after them
+    struct Pass {
+        std::vector<int> mem;
+        SampleKernel one = nullptr;
+        FamilyKernel many = nullptr;
+        int blocks = 1;
+    };
+    std::vector<Pass> passes;
     for (int f = 0; f < n; ++f) {
-        kfn[f] = pick_sample(false, w->wide, sorted, args[f]);
-        fblocks[f] = (int)sample_grid(kfn[f], sorted ? 0 : lds, chunk);
-        blocks = std::max(blocks, fblocks[f]);
+        const bool joins = args[f].has_win && !args[f].general_runs;
+        if (joins && !passes.empty() && passes.back().many && (int)passes.back().mem.size() < kFamMax) {
+            passes.back().mem.push_back(f);
+            continue;
+        }
+        Pass x;
+        x.mem.push_back(f);
+        if (joins && f + 1 < n && !args[f + 1].general_runs) {
+            const bool small = args[f].nt <= 4 && args[f].k <= 5;
+            x.many = w->wide ? pick_family<u128>(sorted, small) : pick_family<u64>(sorted, small);
+            x.blocks = (int)sample_grid(reinterpret_cast<const void*>(x.many), 0, chunk);
+        } else {
+            x.one = pick_sample(false, w->wide, sorted, args[f]);
+            x.blocks = (int)sample_grid(x.one, sorted ? 0 : lds, chunk);
+        }
+        passes.push_back(std::move(x));
     }
+    int blocks = 1;
+    for (const Pass& x : passes) blocks = std::max(blocks, x.blocks * (x.many ? kFamMax : 1));
     const int key_bits = bits_of(2 * (u64)w->g->m - 1);
     // per chunk: every member's reduced sums (after the per-block partials)
     // and the flags of the shared root pass and sort, read back together
@@ -2238,15 +2341,39 @@ int family_run(tm_weights* w, const HostPlan* plans, int n, u64 seed, u64 k, hip
                 args[f].sval = vs;
             }
         }
-        for (int f = 0; f < n && rc == TM_OK; ++f) {
-            const dim3 grid((unsigned)std::min<u64>((cnt + kBlock - 1) / kBlock, (u64)fblocks[f]));
-            if (launch_sample(kfn[f], grid, sorted ? 0 : lds, st, args[f]) != hipSuccess) {
+        for (const Pass& x : passes) {
+            const int f = x.mem[0], nf = (int)x.mem.size();
+            const dim3 grid((unsigned)std::min<u64>((cnt + kBlock - 1) / kBlock, (u64)x.blocks));
+            hipError_t e;
+            if (x.many) {
+                FamArgs fa;
+                std::memset(&fa, 0, sizeof fa);
+                fa.n = nf;
+                for (int y = 0; y < nf; ++y) {
+                    const SampleArgs& m = args[f + y];
+                    FamMember& o = fa.mem[y];
+                    o.n_runs = m.n_runs;
+                    std::memcpy(o.run_first, m.run_first, sizeof o.run_first);
+                    std::memcpy(o.run_len, m.run_len, sizeof o.run_len);
+                    std::memcpy(o.run_prev, m.run_prev, sizeof o.run_prev);
+                    std::memcpy(o.run_next, m.run_next, sizeof o.run_next);
+                    std::memcpy(o.free_src, m.free_src, sizeof o.free_src);
+                    std::memcpy(o.free_dst, m.free_dst, sizeof o.free_dst);
+                }
+                void* kargs[] = {&args[f], &fa};
+                e = hipLaunchKernel(reinterpret_cast<const void*>(x.many), grid, dim3(kBlock), kargs, 0, st);
+            } else {
+                e = launch_sample(x.one, grid, sorted ? 0 : lds, st, args[f]);
+            }
+            if (e == hipSuccess) {
+                hipLaunchKernelGGL(reduce_kernel, dim3((unsigned)nf), dim3(kBlock), 0, st, (const Partial*)parts,
+                                   (int)grid.x, parts + blocks + f, StageList{});
+                e = hipGetLastError();
+            }
+            if (e != hipSuccess) {
                 rc = tm_fail(TM_EDEVICE, "family: launch");
                 break;
             }
-            hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(kBlock), 0, st, (const Partial*)parts, (int)grid.x,
-                               parts + blocks + f, StageList{});
-            if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "family: launch");
         }
         if (rc != TM_OK) break;
         if (read_back({{hp.data(), parts + blocks, (size_t)n * sizeof(Partial)},
