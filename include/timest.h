@@ -357,8 +357,9 @@ int tm_batch_config(int tile, int blocks, int* prev_tile, int* prev_blocks);
 
 /* The full schedule of the batched kernels (tm_batch_config sets the first
  * two fields only).  Process-wide; the autotuner searches these.
- *   tile: samples per tile, >= 256; each lane of a 256-lane workgroup takes
- *     tile / 256 of a tile's samples (the samples per lane);
+ *   tile: samples per tile, >= 256 (fewer in a pass of few samples); each lane
+ *     of a 256-lane workgroup takes tile / 256 of a tile's samples (the
+ *     samples per lane);
  *   blocks: workgroups of the persistent kernels (0 = 8 per compute unit);
  *   root_lds: LDS bytes per workgroup that stage a job's interval prefix W_i
  *     for its root draws when it fits (jobs with a root guide read one or

@@ -1441,12 +1441,21 @@ batch_root_kernel(const SampleArgs* __restrict__ jobs, const Tile* __restrict__ 
             __syncthreads();
         }
         const W* cum = a.cum_in_lds ? cumL : cumG;
-        for (u64 r = T.begin + threadIdx.x; r < T.end; r += kBlock) {
-            const X128 X = draw_block(a.seed, a.j0 + r, 0);
-            RootGuide g0, g1;
-            guide_pair(a, X, g0, g1);
-            keys[T.out + r] = a.key_base + root_key<W>(a, cum, Wtot, X, g0, g1, bad);
+        // two draws per lane and step, as in root_kernel
+        for (u64 r = T.begin + threadIdx.x; r < T.end; r += 2 * kBlock) {
+            const u64 r1 = r + kBlock;
+            const bool two = r1 < T.end;
+            const X128 X0 = draw_block(a.seed, a.j0 + r, 0);
+            const X128 X1 = draw_block(a.seed, a.j0 + (two ? r1 : r), 0);
+            RootGuide g00, g01, g10, g11;
+            guide_pair(a, X0, g00, g01);
+            guide_pair(a, X1, g10, g11);
+            keys[T.out + r] = a.key_base + root_key<W>(a, cum, Wtot, X0, g00, g01, bad);
             vals[T.out + r] = (uint32_t)r;
+            if (two) {
+                keys[T.out + r1] = a.key_base + root_key<W>(a, cum, Wtot, X1, g10, g11, bad);
+                vals[T.out + r1] = (uint32_t)r1;
+            }
         }
     }
     if (bad) atomicOr(ovf, 2);
@@ -1493,6 +1502,14 @@ void launch_batch_sample(int mode, dim3 grid, hipStream_t st, const SampleArgs* 
         hipLaunchKernelGGL((batch_sample_kernel<W, kGeneral, 2>), grid, dim3(kBlock), 0, st, jobs, tiles, n_tiles,
                            counter, tile_parts);
 }
+
+constexpr u64 kBatchTiles = 8192;  // tiles a pass is split into where the configured ones are larger
+
+// The kernel groups of a batched pass, by width and completion counter.  (A
+// group of their own for the plans that kSmall holds, with five or six waves a
+// SIMD instead of four, won nothing: every group more is a launch that ends
+// with its last tiles.)
+constexpr int kBatchGroups = 4;
 
 // One block per job: the sum of the job's tile partials.
 __global__ void __launch_bounds__(kBlock)
@@ -1830,7 +1847,7 @@ struct Group {
     std::vector<SampleArgs> args;
     std::vector<Tile> rt, stt;
     std::vector<int> g_rt_first, g_st_first, jfirst, jcount;
-    int g_win[4] = {0, 0, 0, 0};  // per kernel group: the batch_sample_kernel window mode
+    int g_win[kBatchGroups] = {};  // per kernel group: the batch_sample_kernel window mode
     SampleArgs* djobs = nullptr;
     Tile *drt = nullptr, *dst = nullptr;
     uint32_t *k0 = nullptr, *v0 = nullptr, *k1 = nullptr, *v1 = nullptr;
@@ -1857,7 +1874,14 @@ void group_prepare(tm_weights* const* ws, const std::vector<int>& act, const u64
     }
     G.key_bits = std::max(1, bits_of(key_space - 1));
     G.passes = radix_passes(G.key_bits - root_sort_lo_bit(G.key_bits));
-    const int tile = cfg.tile > 0 ? cfg.tile : 8192;
+    // at most the configured tile: a lane takes its samples of a tile one after
+    // the other, so a pass is never shorter than that, and a few large tiles
+    // leave most of the chip waiting for them (16 jobs of 1e4 to 1e6 edges,
+    // 1e7 samples, whole call: 3.1 ms with tiles of 8192 samples, 2.63 with
+    // this; 24 warm queries at a server 4.3 and 3.55; split into half or twice
+    // as many tiles within 3%)
+    const u64 fair = (G.total / kBatchTiles + kBlock - 1) / kBlock * kBlock;
+    const int tile = (int)std::min<u64>(cfg.tile > 0 ? cfg.tile : 8192, std::max<u64>(fair, 2 * kBlock));
     int cus = 256;
     {
         int dev = 0;
@@ -1887,11 +1911,11 @@ void group_prepare(tm_weights* const* ws, const std::vector<int>& act, const u64
         base[y] = off;
         off += counts[act[y]];
     }
-    G.g_rt_first.assign(5, 0);
-    G.g_st_first.assign(5, 0);
+    G.g_rt_first.assign(kBatchGroups + 1, 0);
+    G.g_st_first.assign(kBatchGroups + 1, 0);
     G.jfirst.assign(na, 0);
     G.jcount.assign(na, 0);
-    for (int grp = 0; grp < 4; ++grp) {
+    for (int grp = 0; grp < kBatchGroups; ++grp) {
         G.g_rt_first[grp] = (int)G.rt.size();
         G.g_st_first[grp] = (int)G.stt.size();
         int with = 0, without = 0;
@@ -1911,8 +1935,8 @@ void group_prepare(tm_weights* const* ws, const std::vector<int>& act, const u64
         }
         G.g_win[grp] = with == 0 ? 0 : (without == 0 ? 1 : 2);
     }
-    G.g_rt_first[4] = (int)G.rt.size();
-    G.g_st_first[4] = (int)G.stt.size();
+    G.g_rt_first[kBatchGroups] = (int)G.rt.size();
+    G.g_st_first[kBatchGroups] = (int)G.stt.size();
 }
 
 // Offsets of the uploaded arrays in their block; at[5]: its size.
@@ -1981,17 +2005,18 @@ int group_launch(Group& G, hipStream_t st, bool timed) {
     TM_TRY(fill_u32(G.ctr, (int64_t)((256 + sort_scratch_bytes((int64_t)G.total)) / sizeof(uint32_t)), 0u, st));
     StageTimer t_roots, t_sample, t_reduce;
     if (timed) t_roots.start(TM_STAGE_ROOTS, st);
-    for (int grp = 0; grp < 4; ++grp) {
-        const int nt = G.g_rt_first[grp + 1] - G.g_rt_first[grp];
+    // root draws: the groups of one width together
+    for (int wide = 0; wide < 2; ++wide) {
+        const int first = G.g_rt_first[wide ? 2 : 0], nt = G.g_rt_first[wide ? 4 : 2] - first;
         if (nt == 0) continue;
         const dim3 grid((unsigned)std::min(G.blocks, nt));
-        const Tile* tl = G.drt + G.g_rt_first[grp];
-        if (grp >= 2)
+        const Tile* tl = G.drt + first;
+        if (wide)
             hipLaunchKernelGGL(batch_root_kernel<u128>, grid, dim3(kBlock), G.root_lds, st, G.djobs, tl, nt,
-                               G.ctr + grp, G.k0, G.v0, G.ovf);
+                               G.ctr + 1, G.k0, G.v0, G.ovf);
         else
             hipLaunchKernelGGL(batch_root_kernel<u64>, grid, dim3(kBlock), G.root_lds, st, G.djobs, tl, nt,
-                               G.ctr + grp, G.k0, G.v0, G.ovf);
+                               G.ctr, G.k0, G.v0, G.ovf);
         TM_HIP(hipGetLastError());
     }
     {
@@ -2004,13 +2029,13 @@ int group_launch(Group& G, hipStream_t st, bool timed) {
     }
     t_roots.stop();
     if (timed) t_sample.start(TM_STAGE_SAMPLE, st);
-    for (int grp = 0; grp < 4; ++grp) {
+    for (int grp = 0; grp < kBatchGroups; ++grp) {
         const int nt = G.g_st_first[grp + 1] - G.g_st_first[grp];
         if (nt == 0) continue;
         const dim3 grid((unsigned)std::min(G.blocks, nt));
         const Tile* tl = G.dst + G.g_st_first[grp];
         Partial* tp = G.tparts + G.g_st_first[grp];
-        int* c = G.ctr + 4 + grp;
+        int* c = G.ctr + 2 + grp;
         const int wm = G.g_win[grp];
         switch (grp) {
             case 0: launch_batch_sample<u64, false>(wm, grid, st, G.djobs, tl, nt, c, tp); break;
