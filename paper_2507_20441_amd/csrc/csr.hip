@@ -15,7 +15,7 @@
 
 namespace {
 
-enum : int { kBadRange = 1, kSelfLoop = 2, kDup = 4 };
+enum : int { kBadRange = 1, kSelfLoop = 2, kDup = 4, kLongTie = 8 };
 
 __device__ __forceinline__ u64 order_key(int64_t t) { return (u64)t ^ 0x8000000000000000ull; }
 
@@ -62,9 +62,44 @@ validate_kernel(const int32_t* src, const int32_t* dst, const int64_t* t, int64_
     }
 }
 
-// One workgroup: the partials of nb workgroups into *flags, *tmin, *tmax.
+// Times at kTieSamples pseudo-random edges: how many repeat one before them
+// tells how many edges share a time (see graph_build).
+constexpr int kTieSamples = 1024;
+
+__device__ __forceinline__ int repeated_times(const int64_t* t, int64_t m) {
+    constexpr int kSlots = 4 * kTieSamples;
+    constexpr u64 kEmpty = ~0ull;
+    __shared__ u64 table[kSlots];
+    __shared__ int repeats;
+    for (int i = threadIdx.x; i < kSlots; i += kBlock) table[i] = kEmpty;
+    if (threadIdx.x == 0) repeats = 0;
+    __syncthreads();
+    int mine = 0;
+    for (int i = threadIdx.x; i < kTieSamples; i += kBlock) {
+        const u64 at = __umul64hi((u64)(i + 1) * 0x9E3779B97F4A7C15ull, (u64)m);
+        u64 x = (u64)t[at];
+        if (x == kEmpty) x = 0;
+        // at most kTieSamples of the kSlots fill: the probe ends
+        for (uint32_t h = (uint32_t)((x * 0x9E3779B97F4A7C15ull) >> 40) % kSlots;; h = (h + 1) % kSlots) {
+            const u64 old = atomicCAS((unsigned long long*)&table[h], kEmpty, x);
+            if (old == kEmpty) break;
+            if (old == x) {
+                ++mine;
+                break;
+            }
+        }
+    }
+    if (mine) atomicAdd(&repeats, mine);
+    __syncthreads();
+    return repeats;
+}
+
+// One workgroup: the partials of nb workgroups into *flags, *tmin, *tmax, and
+// *rep, the repeated times among the sampled ones.
 __global__ void __launch_bounds__(kBlock)
-validate_reduce_kernel(const u64* part, int nb, int* flags, u64* tmin, u64* tmax) {
+validate_reduce_kernel(const u64* part, int nb, const int64_t* t, int64_t m, int* flags, u64* tmin, u64* tmax,
+                       u64* rep) {
+    const int repeats = repeated_times(t, m);
     u64 lo = ~0ull, hi = 0;
     uint32_t f = 0;
     for (int b = threadIdx.x; b < nb; b += kBlock) {
@@ -95,6 +130,7 @@ validate_reduce_kernel(const u64* part, int nb, int* flags, u64* tmin, u64* tmax
         }
         *tmin = lo;
         *tmax = hi;
+        *rep = (u64)repeats;
         *flags = (int)f;
     }
 }
@@ -128,6 +164,51 @@ __global__ void decode_packed_kernel(const u64* key, int64_t m, int bn, int32_t*
     ot[e] = (int64_t)(k >> (2 * bn));
     if (ot32) ot32[e] = (uint32_t)(k >> (2 * bn));
     if (e > 0 && key[e - 1] == k) atomicOr(flags, kDup);
+}
+
+// Edge arrays from keys in time order only: an edge's place among the edges of
+// its time is the number of smaller (u, v) there, counted by reading them all
+// (the average time of the graphs that come here holds a few edges).  More
+// than kTieMax on either side set kLongTie: the caller then sorts in full.
+// keys: the packed keys (uv null), or the times with the (u, v) keys beside.
+constexpr int kTieMax = 256;
+
+__global__ void __launch_bounds__(kBlock)
+decode_ties_kernel(const u64* key, const u64* uv, int64_t m, int bn, int32_t* osrc, int32_t* odst, int64_t* ot,
+                   uint32_t* ot32, int* flags) {
+    const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    // (once a long run is known, what is left need not be looked at)
+    if (e >= m || (__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kLongTie)) return;
+    const int tshift = uv ? 0 : 2 * bn;
+    const u64* order = uv ? uv : key;  // equal times: order by these
+    const u64 t = key[e] >> tshift, k = order[e];
+    int64_t l = e - 1, r = e + 1;
+    int less = 0;
+    bool dup = false;
+    int steps = 0;
+    // a run that reaches further than kTieMax on a side shows there at once
+    bool over = (e >= kTieMax && (key[e - kTieMax] >> tshift) == t) ||
+                (e + kTieMax < m && (key[e + kTieMax] >> tshift) == t);
+    for (; !over && l >= 0 && (key[l] >> tshift) == t && steps < kTieMax; --l, ++steps) {
+        less += order[l] < k ? 1 : 0;
+        dup = dup || order[l] == k;
+    }
+    over = over || steps == kTieMax;
+    for (steps = 0; !over && r < m && (key[r] >> tshift) == t && steps < kTieMax; ++r, ++steps) {
+        less += order[r] < k ? 1 : 0;
+        dup = dup || order[r] == k;
+    }
+    over = over || steps == kTieMax;
+    // one atomic per wave and flag
+    const u64 lanes = __ballot(1), dups = __ballot(dup), overs = __ballot(over);
+    if ((dups | overs) && (threadIdx.x & 63) == __ffsll(lanes) - 1)
+        atomicOr(flags, (dups ? kDup : 0) | (overs ? kLongTie : 0));
+    const int64_t at = l + 1 + less;  // inside the edges looked at
+    const u64 mask = (1ull << bn) - 1;
+    osrc[at] = (int32_t)((k >> bn) & mask);
+    odst[at] = (int32_t)(k & mask);
+    ot[at] = (int64_t)t;
+    if (ot32) ot32[at] = (uint32_t)t;
 }
 
 // Edge arrays from the sorted times and the (u, v) keys carried with them.
@@ -372,7 +453,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     int* flags = nullptr;
     u64* tbounds = nullptr;
     TM_HIP(dev_alloc((void**)&flags, sizeof(int) * 2, st));
-    TM_HIP(dev_alloc((void**)&tbounds, sizeof(u64) * 2, st));
+    TM_HIP(dev_alloc((void**)&tbounds, sizeof(u64) * 3, st));
     TM_HIP(hipMemsetAsync(flags, 0, sizeof(int) * 2, st));
     {
         const unsigned blocks = (unsigned)std::min<int64_t>(grid_for(m), 1024);
@@ -381,7 +462,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         hipLaunchKernelGGL(validate_kernel, dim3(blocks), dim3(kBlock), 0, st, src, dst, t, m, n, part);
         TM_HIP(hipGetLastError());
         hipLaunchKernelGGL(validate_reduce_kernel, dim3(1), dim3(kBlock), 0, st, (const u64*)part, (int)blocks,
-                           flags, tbounds, tbounds + 1);
+                           t, m, flags, tbounds, tbounds + 1, tbounds + 2);
         TM_HIP(hipGetLastError());
         TM_HIP(dev_free(part, st));
     }
@@ -392,7 +473,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         return r;
     };
     int hflags[2];
-    u64 hb[2];
+    u64 hb[3];
     TM_HIP(read_back({{hflags, flags, sizeof hflags}, {hb, tbounds, sizeof hb}}, st));
     if (hflags[0] & kBadRange) return bail(tm_fail(TM_EINVAL, "graph: vertex id outside [0, %d)", n));
     if (hflags[0] & kSelfLoop) return bail(tm_fail(TM_ESELFLOOP, "graph: self loop"));
@@ -478,16 +559,16 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     // serve them), and the status words all of them share.  (At 20,000 edges
     // clearing, counting and starting five sorts one by one was a fifth of the
     // build.)
-    constexpr int kHeads = 6;
+    constexpr int kHeads = 7;  // (6: the sort by time alone)
     const size_t scr_bytes = kHeads * kSortHeadBytes + (m <= kPairedSorts ? 2 : 1) * sort_status_bytes(m);
     uint32_t tag = 0;
     auto scratch_of = [&](int tickets, int counts) {
         SortScratch x = sort_scratch_at(scr + (size_t)tickets * kSortHeadBytes);
         x.counts = reinterpret_cast<uint32_t*>(scr + (size_t)counts * kSortHeadBytes);
         // (the directions' own when they sort side by side, with equal tags)
-        const bool own = m <= kPairedSorts && tickets >= 2 && (tickets & 1);
+        const bool own = m <= kPairedSorts && tickets >= 2 && tickets < 6 && (tickets & 1);
         x.status = reinterpret_cast<u64*>(scr + kHeads * kSortHeadBytes + (own ? sort_status_bytes(m) : 0));
-        x.counted = tickets >= 2;
+        x.counted = tickets >= 2 && tickets < 6;
         x.tag0 = tag;
         tag += kSortMaxPasses;
         return x;
@@ -495,22 +576,66 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     if (rc == TM_OK && dev_alloc((void**)&scr, scr_bytes, st) != hipSuccess)
         rc = tm_fail(TM_ENOMEM, "graph: sort scratch");
     if (rc == TM_OK) rc = fill_u32(scr, (int64_t)(scr_bytes / sizeof(uint32_t)), 0u, st);
-    auto sort_two = [&](const auto& in, const auto& spare, int nbits, int which, auto* res) -> int {
-        const bool odd = (std::max(1, radix_passes(nbits)) & 1) != 0;
+    auto sort_two = [&](const auto& in, const auto& spare, int lo_bit, int nbits, int which, auto* res) -> int {
+        const bool odd = (std::max(1, radix_passes(nbits - lo_bit)) & 1) != 0;
         *res = odd ? spare : in;
-        return sort_into(in, odd ? spare : in, odd ? in : spare, m, 0, nbits, 0, flags + 1, st,
+        return sort_into(in, odd ? spare : in, odd ? in : spare, m, lo_bit, nbits, 0, flags + 1, st,
                          scratch_of(which, which));
     };
-    if (rc == TM_OK && one_key) {
+    // Times first: where the average time holds few edges, a sort by the time
+    // bits alone (2-4 passes instead of 5-10) leaves short runs of equal times
+    // to put in order; finding out whether they are short costs a round trip to
+    // the host.  Builds with the full sort and this way: 2^14 edges 164 and
+    // 151 us, 2^18 285 and 232, 2^20 513 and 425, 2^22 1690 and 1515, 2^24
+    // 6.76 and 5.90 ms.  Runs too long for it (times on a coarse grid) fall
+    // back to the full sort; where the sampled times say that an edge shares
+    // its time with more than 64 others on average, it is not tried (the
+    // passes in vain made a build of 4e6 edges at whole days 2.2 instead of
+    // 1.5 ms).
+    bool ordered = false;
+    const double shared = (double)hb[2] * (double)m / (0.5 * kTieSamples * (kTieSamples - 1));
+    if (rc == TM_OK && m / 8 <= g->T && shared <= 64.0) {
+        if (one_key) {
+            using S = SortSet<u64>;
+            S in, spare, res;
+            in.k = work[0];
+            spare.k = work[2];
+            rc = sort_two(in, spare, 2 * bn, 2 * bn + D.bt, 6, &res);
+            if (rc == TM_OK)
+                hipLaunchKernelGGL(decode_ties_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)res.k,
+                                   (const u64*)nullptr, m, bn, esrc, edst, et, t32e, flags);
+        } else {
+            using S = SortSet<u64, u64>;
+            S in, spare, res;
+            in.k = work[1];
+            in.v0 = work[0];
+            spare.k = work[2];
+            spare.v0 = work[3];
+            rc = sort_two(in, spare, 0, D.bt, 6, &res);
+            if (rc == TM_OK)
+                hipLaunchKernelGGL(decode_ties_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)res.k,
+                                   (const u64*)res.v0, m, bn, esrc, edst, et, t32e, flags);
+        }
+        if (rc == TM_OK && hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "graph: decode launch");
+        if (rc == TM_OK && read_back({{hflags, flags, sizeof hflags}}, st) != hipSuccess)
+            rc = tm_fail(TM_EDEVICE, "graph: flags");
+        ordered = !(hflags[0] & kLongTie);
+        if (rc == TM_OK && !ordered) {
+            hipLaunchKernelGGL(canon_keys_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, src, dst, t, m, tmin, bn,
+                               one_key ? 1 : 0, work[0], work[1]);
+            if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "graph: key launch");
+        }
+    }
+    if (rc == TM_OK && !ordered && one_key) {
         using S = SortSet<u64>;
         S in, spare, res;
         in.k = work[0];
         spare.k = work[2];
-        rc = sort_two(in, spare, 2 * bn + D.bt, 0, &res);
+        rc = sort_two(in, spare, 0, 2 * bn + D.bt, 0, &res);
         if (rc == TM_OK)
             hipLaunchKernelGGL(decode_packed_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)res.k, m,
                                bn, esrc, edst, et, t32e, flags);
-    } else if (rc == TM_OK) {
+    } else if (rc == TM_OK && !ordered) {
         // by (u, v) with the time carried, then by time with (u, v) carried
         using S = SortSet<u64, u64>;
         S x, y, r1, r2;
@@ -518,7 +643,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         x.v0 = work[1];
         y.k = work[2];
         y.v0 = work[3];
-        rc = sort_two(x, y, 2 * bn, 0, &r1);
+        rc = sort_two(x, y, 0, 2 * bn, 0, &r1);
         if (rc == TM_OK) {
             const S& o1 = r1.k == x.k ? y : x;
             S in2, spare2;
@@ -526,7 +651,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             in2.v0 = r1.k;
             spare2.k = o1.k;
             spare2.v0 = o1.v0;
-            rc = sort_two(in2, spare2, D.bt, 1, &r2);
+            rc = sort_two(in2, spare2, 0, D.bt, 1, &r2);
         }
         if (rc == TM_OK)
             hipLaunchKernelGGL(decode_split_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)r2.k,
@@ -598,8 +723,9 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         uint32_t* lnbr_of[2] = {nullptr, nullptr};  // each T order's neighbours (the N-order sorts' keys)
         int32_t* off[2] = {nullptr, nullptr};
         // guides pay from lists of a few entries on; with fewer edges than
-        // vertices the lists are shorter than that and the guides' entry per
-        // vertex would outweigh the edges
+        // vertices the lists are shorter than that (1e6 edges, 9e5 and 1.1e6
+        // vertices: a build 511 and 503 us, a 6-chain estimate 375 and 379)
+        // and the guides' entry per vertex would outweigh the edges
         const bool guides = n <= m;
         const size_t guide_len = (size_t)guide_first(n, (int32_t)m) + 1;
         const SortPlan plan = sort_plan_copy(0, bn);
