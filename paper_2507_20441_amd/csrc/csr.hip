@@ -189,8 +189,10 @@ decode_ties_kernel(const u64* key, const u64* uv, int64_t m, int bn, int32_t* os
     // a run that reaches further than kTieMax on a side shows there at once
     bool over = (e >= kTieMax && (key[e - kTieMax] >> tshift) == t) ||
                 (e + kTieMax < m && (key[e + kTieMax] >> tshift) == t);
+    // (of equal keys, an error, the earlier one comes first: every position of
+    // the edge arrays is written, whatever the input)
     for (; !over && l >= 0 && (key[l] >> tshift) == t && steps < kTieMax; --l, ++steps) {
-        less += order[l] < k ? 1 : 0;
+        less += order[l] <= k ? 1 : 0;
         dup = dup || order[l] == k;
     }
     over = over || steps == kTieMax;
@@ -250,10 +252,13 @@ __device__ __forceinline__ void guide_fill(const uint32_t* own, const int32_t* o
     int64_t from = 0, to = 0, end = 0;
     if (p < m) {
         auto entry = [&](int64_t i) -> int64_t {
-            // (clamped owners: a broken order must not write outside the guide)
+            // (clamped: a broken order must not write outside the guide)
             const int32_t g = own[i] < (uint32_t)n ? (int32_t)own[i] : n - 1;
             const int32_t a = off[g], b = off[g + 1];
-            return guide_first(g, a) + slice_of(slice_frac(key(i), bits, mul), guide_slices(a, b));
+            const int32_t ns = guide_slices(a, b);
+            const int64_t at = guide_first(g, a) + slice_of(slice_frac(key(i), bits, mul), ns > 0 ? ns : 1);
+            const int64_t last = guide_first(n, (int32_t)m);
+            return at < 0 ? 0 : (at > last ? last : at);
         };
         to = entry(p) + 1;
         from = p == 0 ? 0 : entry(p - 1) + 1;
@@ -351,19 +356,21 @@ pair_rank_kernel(DevGraph G, const uint32_t* own0, const uint32_t* own1, const u
     const int32_t g = own < (uint32_t)G.n ? (int32_t)own : G.n - 1;  // (a broken order must not read outside)
     const int32_t* off = w ? G.off[1] : G.off[0];
     const int32_t* ooff = w ? G.off[0] : G.off[1];
-    const int32_t a = ooff[g], b = ooff[g + 1];
+    // (clamped, as below: a broken order must not read outside)
+    auto within = [](int32_t x, int32_t lo, int32_t hi) { return x < lo ? lo : (x > hi ? hi : x); };
+    const int32_t a = within(ooff[g], 0, (int32_t)m), b = within(ooff[g + 1], a, (int32_t)m);
     const u64 key = nk[q];
     const u64 o = key >> G.bt;
     // two keys of one neighbour differ by their times
     uint32_t sp = kGapNone, sn = kGapNone, rp = kGapNone, rn = kGapNone;
-    if (q > off[g] && (nk[q - 1] >> G.bt) == o) sp = gap_code(key - nk[q - 1]);
-    if (q + 1 < off[g + 1] && (nk[q + 1] >> G.bt) == o) sn = gap_code(nk[q + 1] - key);
+    if (q > 0 && q > off[g] && (nk[q - 1] >> G.bt) == o) sp = gap_code(key - nk[q - 1]);
+    if (q + 1 < m && q + 1 < off[g + 1] && (nk[q + 1] >> G.bt) == o) sn = gap_code(nk[q + 1] - key);
     int32_t c = a, n = b - a;
     const int32_t* gd = w ? G.nguide[0] : G.nguide[1];
     if (gd) {
         const int32_t* e = gd + guide_first(g, a) + slice_of(slice_frac(o, G.bn, G.nmul), guide_slices(a, b));
-        c = e[0];
-        n = e[1] - c;
+        c = within(e[0], a, b);
+        n = within(e[1], c, b) - c;
     }
     while (n > 0) {
         const int32_t h = n >> 1;
