@@ -492,10 +492,13 @@ constexpr size_t kSortHeadBytes =
     ((size_t)kSortMaxPasses * kSortDigits * sizeof(uint32_t) + kSortMaxPasses * sizeof(uint32_t) + 255) &
     ~(size_t)255;
 
-// Scratch of a sort of n keys: per-pass digit counts and tickets, then one
-// status word per tile and digit.
+// Scratch of a sort of up to n keys: per-pass digit counts and tickets, then
+// one status word per tile and digit.  (2^18 keys take more tiles than 2^18 + 1,
+// whose tiles are larger: the size is that of the count with the most.)
 constexpr size_t sort_status_bytes(int64_t n) {
-    return (size_t)(n > 0 ? sort_tiles(n) : 0) * kSortDigits * sizeof(u64);
+    const int64_t small = n > kSortSmall ? sort_tiles(kSortSmall) : 0;
+    const int64_t tiles = n > 0 ? sort_tiles(n) : 0;
+    return (size_t)(tiles > small ? tiles : small) * kSortDigits * sizeof(u64);
 }
 constexpr size_t sort_scratch_bytes(int64_t n) { return kSortHeadBytes + sort_status_bytes(n); }
 
