@@ -105,8 +105,11 @@ __device__ __forceinline__ uint32_t time_frac(TT x, int bt, uint32_t mul) {
 // no such edge).  Byte 0, 1: the entries of the same pair before and after the
 // edge in its own list; byte 2, 3: those of the pair in the vertex's other
 // list before t and at or after t (that gap plus one, as it may be zero).
+// (An edge given twice has the gap 0, coded as 1: such a graph is refused, some
+// of them only once their lists are there.)
 constexpr uint32_t kGapNone = 255;
-TM_HD uint32_t gap_code(u64 gap) {  // gap >= 1
+TM_HD uint32_t gap_code(u64 gap) {
+    gap |= gap == 0 ? 1 : 0;
     const int e = 63 - __builtin_clzll(gap);
     const uint32_t frac = (uint32_t)(e >= 2 ? (gap >> (e - 2)) & 3 : (gap << (2 - e)) & 3);
     const uint32_t c = (uint32_t)e * 4 + frac;
