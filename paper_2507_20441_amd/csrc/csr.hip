@@ -589,6 +589,12 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         return sort_into(in, odd ? spare : in, odd ? in : spare, m, lo_bit, nbits, 0, flags + 1, st,
                          scratch_of(which, which));
     };
+    // What the flag words, once read, say of the edges.
+    auto verdict = [&]() -> int {
+        if (hflags[0] & kDup) return tm_fail(TM_EDUP, "graph: duplicate (u, v, t) tuple");
+        if (hflags[1]) return tm_fail(TM_EDEVICE, "graph: internal sort error (look-back stalled)");
+        return TM_OK;
+    };
     // Times first: where the average time holds few edges, a sort by the time
     // bits alone (2-4 passes instead of 5-10) leaves short runs of equal times
     // to put in order; finding out whether they are short costs a round trip to
@@ -626,6 +632,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         if (rc == TM_OK && hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "graph: decode launch");
         if (rc == TM_OK && read_back({{hflags, flags, sizeof hflags}}, st) != hipSuccess)
             rc = tm_fail(TM_EDEVICE, "graph: flags");
+        // (what this refuses, no list is built for)
+        if (rc == TM_OK) rc = verdict();
         ordered = !(hflags[0] & kLongTie);
         if (rc == TM_OK && !ordered) {
             hipLaunchKernelGGL(canon_keys_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, src, dst, t, m, tmin, bn,
@@ -892,7 +900,5 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     TM_HIP(dev_free(flags, st));
     TM_HIP(dev_free(tbounds, st));
     timer.finish();
-    if (hflags[0] & kDup) return tm_fail(TM_EDUP, "graph: duplicate (u, v, t) tuple");
-    if (hflags[1]) return tm_fail(TM_EDEVICE, "graph: internal sort error (look-back stalled)");
-    return TM_OK;
+    return verdict();
 }
