@@ -15,7 +15,11 @@
 
 namespace {
 
-enum : int { kBadRange = 1, kSelfLoop = 2, kDup = 4, kLongTie = 8 };
+enum : int { kBadRange = 1, kSelfLoop = 2, kDup = 4 };
+
+// The build's words on the device: the flags above, the sorts' error word, the
+// edges of long runs (decode_ties_kernel).
+enum : int { kFlags, kSortErr, kLongEdges, kFlagWords };
 
 __device__ __forceinline__ u64 order_key(int64_t t) { return (u64)t ^ 0x8000000000000000ull; }
 
@@ -62,27 +66,29 @@ validate_kernel(const int32_t* src, const int32_t* dst, const int64_t* t, int64_
     }
 }
 
-// Times at kTieSamples pseudo-random edges: how many repeat one before them
-// tells how many edges share a time (see graph_build).
-constexpr int kTieSamples = 1024;
+// Times at pseudo-random edges: how many repeat one before them tells how many
+// edges share a time (see graph_build).  Four times as many for large graphs,
+// where few of them would repeat.
+constexpr int kTieSamples = 4096;
 
-__device__ __forceinline__ int repeated_times(const int64_t* t, int64_t m) {
-    constexpr int kSlots = 4 * kTieSamples;
-    constexpr u64 kEmpty = ~0ull;
-    __shared__ u64 table[kSlots];
+int tie_samples(int64_t m) { return m < ((int64_t)1 << 23) ? kTieSamples / 4 : kTieSamples; }
+
+__device__ __forceinline__ int repeated_times(const int64_t* t, int64_t m, int samples) {
+    constexpr int kSlots = 2 * kTieSamples;
+    __shared__ uint32_t table[kSlots];  // 32 bits of a time's hash; 0: empty
     __shared__ int repeats;
-    for (int i = threadIdx.x; i < kSlots; i += kBlock) table[i] = kEmpty;
+    for (int i = threadIdx.x; i < kSlots; i += kBlock) table[i] = 0;
     if (threadIdx.x == 0) repeats = 0;
     __syncthreads();
     int mine = 0;
-    for (int i = threadIdx.x; i < kTieSamples; i += kBlock) {
+    for (int i = threadIdx.x; i < samples; i += kBlock) {
         const u64 at = __umul64hi((u64)(i + 1) * 0x9E3779B97F4A7C15ull, (u64)m);
-        u64 x = (u64)t[at];
-        if (x == kEmpty) x = 0;
+        const u64 hash = (u64)t[at] * 0x9E3779B97F4A7C15ull;
+        const uint32_t x = (uint32_t)(hash >> 32) | 1u;
         // at most kTieSamples of the kSlots fill: the probe ends
-        for (uint32_t h = (uint32_t)((x * 0x9E3779B97F4A7C15ull) >> 40) % kSlots;; h = (h + 1) % kSlots) {
-            const u64 old = atomicCAS((unsigned long long*)&table[h], kEmpty, x);
-            if (old == kEmpty) break;
+        for (uint32_t h = (uint32_t)(hash >> 40) % kSlots;; h = (h + 1) % kSlots) {
+            const uint32_t old = atomicCAS(&table[h], 0u, x);
+            if (old == 0) break;
             if (old == x) {
                 ++mine;
                 break;
@@ -95,11 +101,11 @@ __device__ __forceinline__ int repeated_times(const int64_t* t, int64_t m) {
 }
 
 // One workgroup: the partials of nb workgroups into *flags, *tmin, *tmax, and
-// *rep, the repeated times among the sampled ones.
+// *rep, the repeated times among `samples` ones.
 __global__ void __launch_bounds__(kBlock)
-validate_reduce_kernel(const u64* part, int nb, const int64_t* t, int64_t m, int* flags, u64* tmin, u64* tmax,
-                       u64* rep) {
-    const int repeats = repeated_times(t, m);
+validate_reduce_kernel(const u64* part, int nb, const int64_t* t, int64_t m, int samples, int* flags, u64* tmin,
+                       u64* tmax, u64* rep) {
+    const int repeats = repeated_times(t, m, samples);
     u64 lo = ~0ull, hi = 0;
     uint32_t f = 0;
     for (int b = threadIdx.x; b < nb; b += kBlock) {
@@ -168,44 +174,87 @@ __global__ void decode_packed_kernel(const u64* key, int64_t m, int bn, int32_t*
 
 // Edge arrays from keys in time order only: an edge's place among the edges of
 // its time is the number of smaller (u, v) there, counted by reading them all
-// (the average time of the graphs that come here holds a few edges).  More
-// than kTieMax on either side set kLongTie: the caller then sorts in full.
-// keys: the packed keys (uv null), or the times with the (u, v) keys beside.
+// (the average time of the graphs that come here holds a few edges).  The edges
+// of a time with more than kTieMax go to a list instead, counted in
+// words[kLongEdges] and kept while it holds at most cap, which the caller
+// sorts (decode_long_kernel).  Every edge of a run of equal times finds its
+// length, or that it exceeds kTieMax, so a run is placed or listed as a whole.
+// key: the packed keys (uv null), or the times with the (u, v) keys beside.
 constexpr int kTieMax = 256;
 
 __global__ void __launch_bounds__(kBlock)
 decode_ties_kernel(const u64* key, const u64* uv, int64_t m, int bn, int32_t* osrc, int32_t* odst, int64_t* ot,
-                   uint32_t* ot32, int* flags) {
+                   uint32_t* ot32, int* words, u64* lkey, u64* luv, int64_t cap) {
     const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    // (once a long run is known, what is left need not be looked at)
-    if (e >= m || (__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kLongTie)) return;
+    const int lane = threadIdx.x & 63;
     const int tshift = uv ? 0 : 2 * bn;
     const u64* order = uv ? uv : key;  // equal times: order by these
-    const u64 t = key[e] >> tshift, k = order[e];
+    const bool edge = e < m;
+    const u64 t = edge ? key[e] >> tshift : 0, k = edge ? order[e] : 0;
     int64_t l = e - 1, r = e + 1;
     int less = 0;
     bool dup = false;
-    int steps = 0;
-    // a run that reaches further than kTieMax on a side shows there at once
-    bool over = (e >= kTieMax && (key[e - kTieMax] >> tshift) == t) ||
-                (e + kTieMax < m && (key[e + kTieMax] >> tshift) == t);
+    // a run that reaches kTieMax further on a side shows there at once
+    bool over = edge && ((e >= kTieMax && (key[e - kTieMax] >> tshift) == t) ||
+                         (e + kTieMax < m && (key[e + kTieMax] >> tshift) == t));
     // (of equal keys, an error, the earlier one comes first: every position of
     // the edge arrays is written, whatever the input)
-    for (; !over && l >= 0 && (key[l] >> tshift) == t && steps < kTieMax; --l, ++steps) {
+    for (; edge && !over && l >= 0 && (key[l] >> tshift) == t; --l) {
+        over = r - l > kTieMax;  // e, those between and l
         less += order[l] <= k ? 1 : 0;
         dup = dup || order[l] == k;
     }
-    over = over || steps == kTieMax;
-    for (steps = 0; !over && r < m && (key[r] >> tshift) == t && steps < kTieMax; ++r, ++steps) {
+    for (; edge && !over && r < m && (key[r] >> tshift) == t; ++r) {
+        over = r - l > kTieMax;
         less += order[r] < k ? 1 : 0;
         dup = dup || order[r] == k;
     }
-    over = over || steps == kTieMax;
-    // one atomic per wave and flag
-    const u64 lanes = __ballot(1), dups = __ballot(dup), overs = __ballot(over);
-    if ((dups | overs) && (threadIdx.x & 63) == __ffsll(lanes) - 1)
-        atomicOr(flags, (dups ? kDup : 0) | (overs ? kLongTie : 0));
+    // one atomic per wave
+    if (__ballot(dup && !over) && lane == 0) atomicOr(&words[kFlags], kDup);
+    if (const u64 overs = __ballot(over)) {
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(reinterpret_cast<uint32_t*>(&words[kLongEdges]), (uint32_t)__popcll(overs));
+        const int64_t at = (int64_t)__shfl(base, 0, 64) + __popcll(overs & (lane ? ~0ull >> (64 - lane) : 0ull));
+        if (over && at < cap) {
+            lkey[at] = key[e];
+            if (luv) luv[at] = k;
+        }
+    }
+    if (!edge || over) return;
     const int64_t at = l + 1 + less;  // inside the edges looked at
+    const u64 mask = (1ull << bn) - 1;
+    osrc[at] = (int32_t)((k >> bn) & mask);
+    odst[at] = (int32_t)(k & mask);
+    ot[at] = (int64_t)t;
+    if (ot32) ot32[at] = (uint32_t)t;
+}
+
+// The first of n keys in time order whose time is at or past t.
+__device__ __forceinline__ int64_t first_at(const u64* key, int64_t n, int tshift, u64 t) {
+    int64_t a = 0;
+    while (n > 0) {
+        const int64_t h = n >> 1;
+        const bool up = (key[a + h] >> tshift) < t;
+        a = up ? a + h + 1 : a;
+        n = up ? n - h - 1 : h;
+    }
+    return a;
+}
+
+// The c listed edges of long runs, in canonical order (lkey, luv), to their
+// places: as far after the first edge of their time among all edges (key, in
+// time order) as after the first of it in the list.
+__global__ void __launch_bounds__(kBlock)
+decode_long_kernel(const u64* lkey, const u64* luv, int64_t c, const u64* key, int64_t m, int bn, int32_t* osrc,
+                   int32_t* odst, int64_t* ot, uint32_t* ot32, int* words) {
+    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (j >= c) return;
+    const int tshift = luv ? 0 : 2 * bn;
+    const u64* order = luv ? luv : lkey;
+    const u64 t = lkey[j] >> tshift, k = order[j];
+    if (j > 0 && order[j - 1] == k && (lkey[j - 1] >> tshift) == t) atomicOr(&words[kFlags], kDup);
+    const int64_t at = first_at(key, m, tshift, t) + (j - first_at(lkey, c, tshift, t));
+    if (at < 0 || at >= m) return;  // (a broken order must not write outside)
     const u64 mask = (1ull << bn) - 1;
     osrc[at] = (int32_t)((k >> bn) & mask);
     odst[at] = (int32_t)(k & mask);
@@ -459,9 +508,9 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     // --- validation: ids, self loops, time span -------------------------
     int* flags = nullptr;
     u64* tbounds = nullptr;
-    TM_HIP(dev_alloc((void**)&flags, sizeof(int) * 2, st));
+    TM_HIP(dev_alloc((void**)&flags, sizeof(int) * kFlagWords, st));
     TM_HIP(dev_alloc((void**)&tbounds, sizeof(u64) * 3, st));
-    TM_HIP(hipMemsetAsync(flags, 0, sizeof(int) * 2, st));
+    TM_HIP(hipMemsetAsync(flags, 0, sizeof(int) * kFlagWords, st));
     {
         const unsigned blocks = (unsigned)std::min<int64_t>(grid_for(m), 1024);
         u64* part = nullptr;
@@ -469,7 +518,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         hipLaunchKernelGGL(validate_kernel, dim3(blocks), dim3(kBlock), 0, st, src, dst, t, m, n, part);
         TM_HIP(hipGetLastError());
         hipLaunchKernelGGL(validate_reduce_kernel, dim3(1), dim3(kBlock), 0, st, (const u64*)part, (int)blocks,
-                           t, m, flags, tbounds, tbounds + 1, tbounds + 2);
+                           t, m, tie_samples(m), flags, tbounds, tbounds + 1, tbounds + 2);
         TM_HIP(hipGetLastError());
         TM_HIP(dev_free(part, st));
     }
@@ -479,11 +528,11 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         (void)dev_free(tbounds, st);
         return r;
     };
-    int hflags[2];
+    int hflags[kFlagWords];
     u64 hb[3];
     TM_HIP(read_back({{hflags, flags, sizeof hflags}, {hb, tbounds, sizeof hb}}, st));
-    if (hflags[0] & kBadRange) return bail(tm_fail(TM_EINVAL, "graph: vertex id outside [0, %d)", n));
-    if (hflags[0] & kSelfLoop) return bail(tm_fail(TM_ESELFLOOP, "graph: self loop"));
+    if (hflags[kFlags] & kBadRange) return bail(tm_fail(TM_EINVAL, "graph: vertex id outside [0, %d)", n));
+    if (hflags[kFlags] & kSelfLoop) return bail(tm_fail(TM_ESELFLOOP, "graph: self loop"));
     const int64_t tmin = (int64_t)(hb[0] ^ 0x8000000000000000ull);
     const int64_t tmax = (int64_t)(hb[1] ^ 0x8000000000000000ull);
     if ((__int128)tmax - (__int128)tmin >= ((__int128)1 << 62))
@@ -557,8 +606,6 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
                            one_key ? 1 : 0, work[0], work[1]);
         if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "graph: key launch");
     }
-    // A sort between two buffer sets: the result lands in `spare` after an
-    // odd number of passes, else back in `in`.
     // One block, cleared by one launch, holds every sort's scratch: the digit
     // counts and tickets of the canonical sorts (0, 1) and of the lists' by
     // source and by destination (2, 3), tickets of the N orders (4, 5; they
@@ -583,96 +630,122 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     if (rc == TM_OK && dev_alloc((void**)&scr, scr_bytes, st) != hipSuccess)
         rc = tm_fail(TM_ENOMEM, "graph: sort scratch");
     if (rc == TM_OK) rc = fill_u32(scr, (int64_t)(scr_bytes / sizeof(uint32_t)), 0u, st);
-    auto sort_two = [&](const auto& in, const auto& spare, int lo_bit, int nbits, int which, auto* res) -> int {
+    // A sort of `count` keys between two buffer sets: the result lands in
+    // `spare` after an odd number of passes, else back in `in`.
+    auto sort_two = [&](const auto& in, const auto& spare, int64_t count, int lo_bit, int nbits, int which,
+                        auto* res) -> int {
         const bool odd = (std::max(1, radix_passes(nbits - lo_bit)) & 1) != 0;
         *res = odd ? spare : in;
-        return sort_into(in, odd ? spare : in, odd ? in : spare, m, lo_bit, nbits, 0, flags + 1, st,
+        return sort_into(in, odd ? spare : in, odd ? in : spare, count, lo_bit, nbits, 0, flags + kSortErr, st,
                          scratch_of(which, which));
+    };
+    using S1 = SortSet<u64>;
+    using S2 = SortSet<u64, u64>;
+    auto set1 = [](u64* k) {
+        S1 x;
+        x.k = k;
+        return x;
+    };
+    auto set2 = [](u64* k, u64* v) {
+        S2 x;
+        x.k = k;
+        x.v0 = v;
+        return x;
+    };
+    // The canonical order of `count` edges, by every bit of their keys.
+    // Packed keys in k0 (k1 the other buffer): *key the result, *uv null.
+    // Else (u, v) keys in k0 and times in v0 (k1, v1 the other buffers): by
+    // (u, v) with the time carried, then by time with (u, v) carried.
+    auto order_all = [&](u64* k0, u64* v0, u64* k1, u64* v1, int64_t count, u64** key, u64** uv) -> int {
+        if (one_key) {
+            S1 res;
+            TM_TRY(sort_two(set1(k0), set1(k1), count, 0, 2 * bn + D.bt, 0, &res));
+            *key = res.k;
+            *uv = nullptr;
+            return TM_OK;
+        }
+        S2 r1, r2;
+        TM_TRY(sort_two(set2(k0, v0), set2(k1, v1), count, 0, 2 * bn, 0, &r1));
+        const S2 o1 = r1.k == k0 ? set2(k1, v1) : set2(k0, v0);
+        TM_TRY(sort_two(set2(r1.v0, r1.k), set2(o1.k, o1.v0), count, 0, D.bt, 1, &r2));
+        *key = r2.k;
+        *uv = r2.v0;
+        return TM_OK;
     };
     // What the flag words, once read, say of the edges.
     auto verdict = [&]() -> int {
-        if (hflags[0] & kDup) return tm_fail(TM_EDUP, "graph: duplicate (u, v, t) tuple");
-        if (hflags[1]) return tm_fail(TM_EDEVICE, "graph: internal sort error (look-back stalled)");
+        if (hflags[kFlags] & kDup) return tm_fail(TM_EDUP, "graph: duplicate (u, v, t) tuple");
+        if (hflags[kSortErr]) return tm_fail(TM_EDEVICE, "graph: internal sort error (look-back stalled)");
         return TM_OK;
     };
     // Times first: where the average time holds few edges, a sort by the time
     // bits alone (2-4 passes instead of 5-10) leaves short runs of equal times
-    // to put in order; finding out whether they are short costs a round trip to
-    // the host.  Builds with the full sort and this way: 2^14 edges 164 and
-    // 151 us, 2^18 285 and 232, 2^20 513 and 425, 2^22 1690 and 1515, 2^24
-    // 6.76 and 5.90 ms.  Runs too long for it (times on a coarse grid) fall
-    // back to the full sort; where the sampled times say that an edge shares
-    // its time with more than 64 others on average, it is not tried (the
-    // passes in vain made a build of 4e6 edges at whole days 2.2 instead of
-    // 1.5 ms).
-    bool ordered = false;
-    const double shared = (double)hb[2] * (double)m / (0.5 * kTieSamples * (kTieSamples - 1));
-    if (rc == TM_OK && m / 8 <= g->T && shared <= 64.0) {
+    // to put in order, and the edges of the few long ones are sorted apart; how
+    // many those are costs a round trip to the host.  Builds with the full sort
+    // and this way: 2^14 edges 164 and 151 us, 2^18 285 and 232, 2^20 513 and
+    // 425, 2^22 1690 and 1515, 2^24 6.76 and 5.90 ms.  (With 300 edges at one
+    // time, which started the full sort over before there was the list, 2^18
+    // edges 421 and 342 us, 4e6 1.94 and 1.57 ms, 2e7 9.32 and 7.26 ms.)  It pays
+    // while fewer than half of the edges are in long runs (each then costs the
+    // full sort's passes on top); past that the full sort starts over, so where
+    // the sampled times say that an edge shares its time with more than 64
+    // others on average, it is not tried (the passes in vain made a build of 4e6
+    // edges at whole days 2.2 instead of 1.5 ms).
+    auto order_by_time = [&](bool* done) -> int {
+        u64 *key, *uv = nullptr;
+        u64 *lk, *lv = nullptr, *lk1, *lv1 = nullptr;  // the listed edges' keys and their sort's other buffers
+        const int64_t cap = m / 2;
         if (one_key) {
-            using S = SortSet<u64>;
-            S in, spare, res;
-            in.k = work[0];
-            spare.k = work[2];
-            rc = sort_two(in, spare, 2 * bn, 2 * bn + D.bt, 6, &res);
-            if (rc == TM_OK)
-                hipLaunchKernelGGL(decode_ties_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)res.k,
-                                   (const u64*)nullptr, m, bn, esrc, edst, et, t32e, flags);
+            S1 res;
+            TM_TRY(sort_two(set1(work[0]), set1(work[2]), m, 2 * bn, 2 * bn + D.bt, 6, &res));
+            key = res.k;
+            lk = work[1];
+            lk1 = work[3];
         } else {
-            using S = SortSet<u64, u64>;
-            S in, spare, res;
-            in.k = work[1];
-            in.v0 = work[0];
-            spare.k = work[2];
-            spare.v0 = work[3];
-            rc = sort_two(in, spare, 0, D.bt, 6, &res);
-            if (rc == TM_OK)
-                hipLaunchKernelGGL(decode_ties_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)res.k,
-                                   (const u64*)res.v0, m, bn, esrc, edst, et, t32e, flags);
+            S2 res;
+            TM_TRY(sort_two(set2(work[1], work[0]), set2(work[2], work[3]), m, 0, D.bt, 6, &res));
+            key = res.k;
+            uv = res.v0;
+            lk = res.k == work[1] ? work[2] : work[1];
+            lv = res.k == work[1] ? work[3] : work[0];
+            lk1 = lk + cap;
+            lv1 = lv + cap;
         }
-        if (rc == TM_OK && hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "graph: decode launch");
-        if (rc == TM_OK && read_back({{hflags, flags, sizeof hflags}}, st) != hipSuccess)
-            rc = tm_fail(TM_EDEVICE, "graph: flags");
-        // (what this refuses, no list is built for)
-        if (rc == TM_OK) rc = verdict();
-        ordered = !(hflags[0] & kLongTie);
-        if (rc == TM_OK && !ordered) {
+        hipLaunchKernelGGL(decode_ties_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)key,
+                           (const u64*)uv, m, bn, esrc, edst, et, t32e, flags, lk, lv, cap);
+        TM_HIP(hipGetLastError());
+        TM_HIP(read_back({{hflags, flags, sizeof hflags}}, st));
+        TM_TRY(verdict());  // (what this refuses, no list is built for)
+        const int64_t c = (int64_t)(uint32_t)hflags[kLongEdges];
+        *done = c <= cap;
+        if (c == 0) return TM_OK;
+        if (c > cap) {
             hipLaunchKernelGGL(canon_keys_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, src, dst, t, m, tmin, bn,
                                one_key ? 1 : 0, work[0], work[1]);
-            if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "graph: key launch");
+            TM_HIP(hipGetLastError());
+            return TM_OK;
         }
+        u64 *sk, *suv;
+        TM_TRY(one_key ? order_all(lk, nullptr, lk1, nullptr, c, &sk, &suv) : order_all(lv, lk, lv1, lk1, c, &sk, &suv));
+        hipLaunchKernelGGL(decode_long_kernel, dim3(grid_for(c)), dim3(kBlock), 0, st, (const u64*)sk,
+                           (const u64*)suv, c, (const u64*)key, m, bn, esrc, edst, et, t32e, flags);
+        TM_HIP(hipGetLastError());
+        return TM_OK;
+    };
+    bool ordered = false;
+    const double pairs = 0.5 * tie_samples(m) * (tie_samples(m) - 1);
+    if (rc == TM_OK && m / 8 <= g->T && (double)hb[2] * (double)m <= 64.0 * pairs) rc = order_by_time(&ordered);
+    if (rc == TM_OK && !ordered) {
+        u64 *key = nullptr, *uv = nullptr;
+        rc = order_all(work[0], work[1], work[2], work[3], m, &key, &uv);
+        if (rc == TM_OK && one_key)
+            hipLaunchKernelGGL(decode_packed_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)key, m, bn,
+                               esrc, edst, et, t32e, flags);
+        else if (rc == TM_OK)
+            hipLaunchKernelGGL(decode_split_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)key,
+                               (const u64*)uv, m, bn, esrc, edst, et, t32e, flags);
+        if (rc == TM_OK && hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "graph: decode launch");
     }
-    if (rc == TM_OK && !ordered && one_key) {
-        using S = SortSet<u64>;
-        S in, spare, res;
-        in.k = work[0];
-        spare.k = work[2];
-        rc = sort_two(in, spare, 0, 2 * bn + D.bt, 0, &res);
-        if (rc == TM_OK)
-            hipLaunchKernelGGL(decode_packed_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)res.k, m,
-                               bn, esrc, edst, et, t32e, flags);
-    } else if (rc == TM_OK && !ordered) {
-        // by (u, v) with the time carried, then by time with (u, v) carried
-        using S = SortSet<u64, u64>;
-        S x, y, r1, r2;
-        x.k = work[0];
-        x.v0 = work[1];
-        y.k = work[2];
-        y.v0 = work[3];
-        rc = sort_two(x, y, 0, 2 * bn, 0, &r1);
-        if (rc == TM_OK) {
-            const S& o1 = r1.k == x.k ? y : x;
-            S in2, spare2;
-            in2.k = r1.v0;
-            in2.v0 = r1.k;
-            spare2.k = o1.k;
-            spare2.v0 = o1.v0;
-            rc = sort_two(in2, spare2, 0, D.bt, 1, &r2);
-        }
-        if (rc == TM_OK)
-            hipLaunchKernelGGL(decode_split_kernel, dim3(grid_for(m)), dim3(kBlock), 0, st, (const u64*)r2.k,
-                               (const u64*)r2.v0, m, bn, esrc, edst, et, t32e, flags);
-    }
-    if (rc == TM_OK && hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "graph: decode launch");
     if (rc != TM_OK) {
         release();
         return bail(rc);
@@ -747,9 +820,9 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         // two sorts side by side, or one after the other
         auto sort_lists = [&](auto* jobs, int iota) -> int {
             int res = 0;
-            if (paired) return sort_run(jobs, 2, m, plan, iota, flags + 1, st, &res);
-            TM_TRY(sort_run(jobs, 1, m, plan, iota, flags + 1, st, &res));
-            return sort_run(jobs + 1, 1, m, plan, iota, flags + 1, st, &res);
+            if (paired) return sort_run(jobs, 2, m, plan, iota, flags + kSortErr, st, &res);
+            TM_TRY(sort_run(jobs, 1, m, plan, iota, flags + kSortErr, st, &res));
+            return sort_run(jobs + 1, 1, m, plan, iota, flags + kSortErr, st, &res);
         };
         TM_TRY(sort_count<uint32_t>(reinterpret_cast<uint32_t*>(esrc), reinterpret_cast<uint32_t*>(edst), 2, m, plan,
                                     scratch_of(2, 2).counts, scratch_of(3, 3).counts, st));
@@ -855,11 +928,11 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         auto n_orders = [&](const auto* jobs, int iota) -> int {
             int res = 0;
             if (paired) {
-                TM_TRY(sort_run(jobs, 2, m, plan, iota, flags + 1, st, &res));
+                TM_TRY(sort_run(jobs, 2, m, plan, iota, flags + kSortErr, st, &res));
                 return fix_lists(0, 2);
             }
             for (int dir = 0; dir < 2; ++dir) {
-                TM_TRY(sort_run(jobs + dir, 1, m, plan, iota, flags + 1, st, &res));
+                TM_TRY(sort_run(jobs + dir, 1, m, plan, iota, flags + kSortErr, st, &res));
                 TM_TRY(fix_lists(dir, 1));
             }
             return TM_OK;
