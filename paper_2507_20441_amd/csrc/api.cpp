@@ -441,6 +441,7 @@ extern "C" int tm_graph_create(const int32_t* src, const int32_t* dst, const int
     (void)sync_stream(st);
     if (rc != TM_OK) {
         g->arena.release();
+        g->ranks.arena.release();
         delete g;
         return rc;
     }
@@ -451,6 +452,7 @@ extern "C" int tm_graph_create(const int32_t* src, const int32_t* dst, const int
 extern "C" void tm_graph_destroy(tm_graph* g) {
     if (!g) return;
     g->arena.release();
+    g->ranks.arena.release();
     delete g;
 }
 
@@ -461,7 +463,8 @@ extern "C" int tm_graph_info(const tm_graph* g, int64_t* m, int32_t* n, int64_t*
     if (n) *n = g->n;
     if (t_shift) *t_shift = g->shift;
     if (t_span) *t_span = g->T;
-    if (device_bytes) *device_bytes = g->arena.bytes;
+    const bool ranks = g->ranks.state.load(std::memory_order_acquire) == PairRanks::kReady;
+    if (device_bytes) *device_bytes = g->arena.bytes + (ranks ? g->ranks.arena.bytes : 0);
     return TM_OK;
 }
 
@@ -1271,6 +1274,14 @@ extern "C" int tm_batch_plan_create(tm_graph* const* g, const tm_motif* mo, cons
         w->arena.stream = raw->br[branch[i]];
         w->plan = plans[i];
         raw->ws[i] = w;
+    }
+    // the replayed builds read pair ranks, which cannot be made while recording
+    for (int i = 0; i < n_jobs; ++i) {
+        HostPlan& p = raw->ws[i]->plan;
+        const int64_t q = raw->g[i]->m > 0 ? raw->g[i]->T / p.mo.delta + 1 : 0;
+        graph_pair_ranks(raw->g[i], kRankLaunches,
+                         weights_footprint(p, raw->g[i]->m, q, false) + weights_build_extra(raw->g[i]->m, false),
+                         raw->cs);
     }
     // record: every 64-bit weight build, W of each job, the batched pass
     int rc = TM_OK;

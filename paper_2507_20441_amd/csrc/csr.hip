@@ -384,16 +384,16 @@ n_order_fix_kernel(NOrderFix<TT> f0, NOrderFix<TT> f1, int64_t m, int32_t n, int
                    [&](int64_t i) { return (u64)nbr[i]; }, bn, nmul, guide);
 }
 
-// The pair ranks of both lists (see DevGraph), in one launch: thread i < m
-// takes position i of the out-lists' N order, the next m those of the
-// in-lists.  Both lists of a vertex are in (neighbour, time) order, so
-// consecutive lanes search the other list at nearby keys (their probes fall
-// on lines the wave shares); the write to the edge's T position, one record
-// inside one line, is the scattered part.  opos: per N position, the edge's T
-// position in the other list.
+// The pair ranks of both lists (see DevGraph) of a finished graph, in one
+// launch: thread i < m takes position i of the out-lists' N order, the next m
+// those of the in-lists.  Both lists of a vertex are in (neighbour, time) order,
+// so consecutive lanes search the other list at nearby keys (their probes fall
+// on lines the wave shares); the lookup of the edge's T position in the other
+// list and the write to its own, one record inside one line, are the scattered
+// part and most of its time (6.8 ms at 1e8 edges; carrying that position through
+// the list sorts instead took 4 ms there and 1.3 off the kernel).
 __global__ void __launch_bounds__(kBlock)
-pair_rank_kernel(DevGraph G, const uint32_t* own0, const uint32_t* own1, const uint32_t* opos0, const uint32_t* opos1,
-                 uint4* rank0, uint4* rank1) {
+pair_rank_kernel(DevGraph G, uint4* rank0, uint4* rank1) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t m = G.m;
     if (i >= 2 * m) return;
@@ -401,13 +401,10 @@ pair_rank_kernel(DevGraph G, const uint32_t* own0, const uint32_t* own1, const u
     const int64_t q = w ? i - m : i;
     const u64* nk = w ? G.nkey[1] : G.nkey[0];
     const u64* ok = w ? G.nkey[0] : G.nkey[1];
-    const uint32_t own = w ? own1[q] : own0[q];
-    const int32_t g = own < (uint32_t)G.n ? (int32_t)own : G.n - 1;  // (a broken order must not read outside)
+    const int32_t g = (w ? G.lown[1] : G.lown[0])[q];  // (the same sequence in both orders)
     const int32_t* off = w ? G.off[1] : G.off[0];
     const int32_t* ooff = w ? G.off[0] : G.off[1];
-    // (clamped, as below: a broken order must not read outside)
-    auto within = [](int32_t x, int32_t lo, int32_t hi) { return x < lo ? lo : (x > hi ? hi : x); };
-    const int32_t a = within(ooff[g], 0, (int32_t)m), b = within(ooff[g + 1], a, (int32_t)m);
+    const int32_t a = ooff[g], b = ooff[g + 1];
     const u64 key = nk[q];
     const u64 o = key >> G.bt;
     // two keys of one neighbour differ by their times
@@ -418,8 +415,8 @@ pair_rank_kernel(DevGraph G, const uint32_t* own0, const uint32_t* own1, const u
     const int32_t* gd = w ? G.nguide[0] : G.nguide[1];
     if (gd) {
         const int32_t* e = gd + guide_first(g, a) + slice_of(slice_frac(o, G.bn, G.nmul), guide_slices(a, b));
-        c = within(e[0], a, b);
-        n = within(e[1], c, b) - c;
+        c = e[0];
+        n = e[1] - c;
     }
     while (n > 0) {
         const int32_t h = n >> 1;
@@ -429,10 +426,9 @@ pair_rank_kernel(DevGraph G, const uint32_t* own0, const uint32_t* own1, const u
     }
     if (c > a && (ok[c - 1] >> G.bt) == o) rp = gap_code(key - ok[c - 1]);
     if (c < b && (ok[c] >> G.bt) == o) rn = gap_code(ok[c] - key + 1);
-    const uint32_t at = (uint32_t)(w ? G.nxref[1] : G.nxref[0])[q];
-    if (at < (u64)m)
-        (w ? rank1 : rank0)[at] = make_uint4((uint32_t)q, (uint32_t)c, (w ? opos1 : opos0)[q],
-                                             sp | (sn << 8) | (rp << 16) | (rn << 24));
+    const int32_t at = (w ? G.nxref[1] : G.nxref[0])[q], e = (w ? G.neid[1] : G.neid[0])[q];
+    (w ? rank1 : rank0)[at] = make_uint4((uint32_t)q, (uint32_t)c, (uint32_t)(w ? G.tpos[0] : G.tpos[1])[e],
+                                         sp | (sn << 8) | (rp << 16) | (rn << 24));
 }
 
 // List offsets from the owner-sorted keys: off[v] is the first position whose
@@ -458,13 +454,6 @@ __global__ void offsets_kernel(const uint32_t* key0, const uint32_t* key1, int64
     wave_fill(off, to, end, (int32_t)m);
 }
 
-// Graphs that keep pair ranks (32 B per edge).  They cost a graph build 25 us
-// at 1e5 edges, 35 us at 5e5 and 9 ms at 1e8, and take 2, 22-28 us and 3-4 ms
-// off every weight build with two to four levels: below 2^19 edges a graph
-// would have to meet many motifs to earn them.  Above 2^28 edges their memory
-// goes to weight sets, as that of the owners.
-bool pair_ranks_kept(int64_t m) { return m >= ((int64_t)1 << 19) && m <= ((int64_t)1 << 28); }
-
 // List sorts side by side up to this many edges (a pass of few tiles leaves the
 // chip idle: a build of 2^14 edges takes 167 us with pairs and 201 without,
 // 2^20 512 and 630, 2^21 862 and 1028, 2^22 1685 and 1760).  Larger builds
@@ -480,6 +469,38 @@ int bits_for(u64 x) {
 unsigned grid_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 }  // namespace
+
+void graph_pair_ranks(tm_graph* g, int launches, u64 need, hipStream_t st) {
+    PairRanks& R = g->ranks;
+    if (g->m < kRanksFrom || g->m > kRanksTo || R.state.load(std::memory_order_acquire) != PairRanks::kNone ||
+        dev_deferring())
+        return;
+    if (R.launches.fetch_add(launches) + launches < kRankAllLaunches && launches < kRankLaunches) return;
+    int none = PairRanks::kNone;
+    if (!R.state.compare_exchange_strong(none, PairRanks::kBusy)) return;  // another thread makes them
+    AllocScope scope_(alloc_of(g));
+    R.arena.stream = st;
+    uint4* rank[2] = {nullptr, nullptr};
+    bool ok = g->has_alloc || dev_room() >= need + 2 * (u64)g->m * sizeof(uint4);
+    for (uint4*& r : rank) ok = ok && arena_alloc(R.arena, &r, (size_t)g->m) == TM_OK;
+    if (ok) {
+        hipLaunchKernelGGL(pair_rank_kernel, dim3(grid_for(2 * g->m)), dim3(kBlock), 0, st, g->d, rank[0], rank[1]);
+        ok = hipGetLastError() == hipSuccess;
+        // (from here on every stream may read them)
+        ok = sync_stream(st) == hipSuccess && ok;
+    }
+    if (!ok) R.arena.release();
+    R.arena.stream = g->arena.stream;
+    for (int dir = 0; dir < 2; ++dir) R.rank[dir] = ok ? rank[dir] : nullptr;
+    R.state.store(ok ? PairRanks::kReady : PairRanks::kGivenUp, std::memory_order_release);
+}
+
+DevGraph graph_view(const tm_graph* g) {
+    DevGraph D = g->d;
+    if (g->ranks.state.load(std::memory_order_acquire) == PairRanks::kReady)
+        for (int dir = 0; dir < 2; ++dir) D.nrank[dir] = g->ranks.rank[dir];
+    return D;
+}
 
 int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64_t* t, hipStream_t st) {
     const int64_t m = g->m;
@@ -560,8 +581,6 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     uint32_t* t32e = nullptr;
     unsigned char* scr = nullptr;     // the sorts' scratch
     unsigned char* second = nullptr;  // buffers of a second list sort
-    uint32_t* opos[4] = {nullptr, nullptr, nullptr, nullptr};  // N orders: the carried other T positions, and
-                                                               // their sort buffers
     uint32_t* nbr32[2] = {nullptr, nullptr};  // 32-bit times: the T orders' neighbours until packed
     auto release = [&]() {
         for (uint32_t*& b : nbr32) {
@@ -578,10 +597,6 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         scr = nullptr;
         if (second) (void)dev_free(second, st);
         second = nullptr;
-        for (uint32_t*& b : opos) {
-            if (b) (void)dev_free(b, st);
-            b = nullptr;
-        }
         if (t32e) (void)dev_free(t32e, st);
         t32e = nullptr;
     };
@@ -764,13 +779,11 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         using TT = decltype(time_tag);
         using V = typename std::conditional<sizeof(TT) == 4, uint32_t, u64>::type;
         using L = SortSet<uint32_t, V, uint32_t, uint32_t>;
-        using LR = SortSet<uint32_t, V, uint32_t, uint32_t, uint32_t>;
         // Graphs of few sort tiles sort both directions side by side, with
         // buffers of their own; larger ones in turn, through the same ones.
         const bool paired = m <= kPairedSorts;
-        const bool ranks = pair_ranks_kept(m);
         struct Bufs {
-            LR tmp;               // the other buffer of the list sorts
+            L tmp;               // the other buffer of the list sorts
             uint32_t* nkeys;      // N order: its sorted keys (unused)
             uint32_t* ntime;      // N order: the carried 32-bit times (64-bit ones: the key array itself,
                                   // packed in place afterwards)
@@ -779,14 +792,10 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         const bool keep_own = m <= ((int64_t)1 << 28);
         if (!keep_own && dev_alloc((void**)&nbr_tmp, (size_t)m * sizeof(uint32_t), st) != hipSuccess)
             return tm_fail(TM_ENOMEM, "graph: work arrays");
-        for (int x = 0; x < (paired ? 4 : 3) && ranks; ++x)
-            if (dev_alloc((void**)&opos[x], (size_t)m * sizeof(uint32_t), st) != hipSuccess)
-                return tm_fail(TM_ENOMEM, "graph: work arrays");
         buf[0].tmp.k = reinterpret_cast<uint32_t*>(work[0]);
         buf[0].tmp.v1 = reinterpret_cast<uint32_t*>(work[0]) + m;
         buf[0].tmp.v0 = reinterpret_cast<V*>(work[1]);
         buf[0].tmp.v2 = reinterpret_cast<uint32_t*>(work[2]);
-        buf[0].tmp.v3 = opos[2];
         buf[0].nkeys = reinterpret_cast<uint32_t*>(work[2]) + m;
         buf[0].ntime = reinterpret_cast<uint32_t*>(work[1]) + m;
         buf[0].nbr = keep_own ? reinterpret_cast<uint32_t*>(work[3]) : nbr_tmp;
@@ -803,7 +812,6 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
                 *x = at;
                 at += m;
             }
-            buf[1].tmp.v3 = opos[3];
         }
         uint32_t* own[2] = {nullptr, nullptr};
         int32_t* tpos[2] = {nullptr, nullptr};
@@ -849,7 +857,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             int32_t* tguide = nullptr;
             if constexpr (sizeof(TT) == 4) TM_TRY(arena_alloc(g->arena, &nt, m));
             if (guides) TM_TRY(arena_alloc(g->arena, &tguide, guide_len));
-            L in, out, tmp;
+            L in, out;
             in.k = reinterpret_cast<uint32_t*>(dir == 0 ? esrc : edst);
             in.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(t32e) : reinterpret_cast<V*>(et);
             in.v2 = reinterpret_cast<uint32_t*>(dir == 0 ? edst : esrc);
@@ -857,11 +865,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             out.v0 = reinterpret_cast<V*>(lt);
             out.v1 = reinterpret_cast<uint32_t*>(leid);
             out.v2 = reinterpret_cast<uint32_t*>(lnbr);
-            tmp.k = buf[dir].tmp.k;
-            tmp.v0 = buf[dir].tmp.v0;
-            tmp.v1 = buf[dir].tmp.v1;
-            tmp.v2 = buf[dir].tmp.v2;
-            tsort[dir] = sort_job(in, out, tmp, plan.npass, scratch_of(2 + dir, 2 + dir));
+            tsort[dir] = sort_job(in, out, buf[dir].tmp, plan.npass, scratch_of(2 + dir, 2 + dir));
             fin[dir] = ListFinish<TT>{own[dir], leid, reinterpret_cast<uint32_t*>(lnbr), lt, off[dir], tpos[dir], nt,
                                       tguide};
             D.off[dir] = off[dir];
@@ -891,9 +895,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: list launch");
         // N order of dir d: the T order of the other direction (sorted by this
         // direction's neighbour, then time) stably re-sorted by this
-        // direction's owner, carrying time, eid and neighbour, and for the pair
-        // ranks its position (0, 1, ...).
-        SortJob<LR> nsort[2];
+        // direction's owner, carrying time, eid and neighbour.
+        SortJob<L> nsort[2];
         NOrderFix<V> fix[2];
         for (int dir = 0; dir < 2; ++dir) {
             const int other = 1 - dir;
@@ -903,7 +906,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             TM_TRY(arena_alloc(g->arena, &nxref, m));
             TM_TRY(arena_alloc(g->arena, &neid, m));
             if (guides) TM_TRY(arena_alloc(g->arena, &nguide, guide_len));
-            LR in, out;
+            L in, out;
             in.k = lnbr_of[other];
             in.v0 = reinterpret_cast<V*>(ltab[other]);
             in.v1 = reinterpret_cast<uint32_t*>(const_cast<int32_t*>(D.leid[other]));
@@ -912,7 +915,6 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             out.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(buf[dir].ntime) : reinterpret_cast<V*>(nkey);
             out.v1 = reinterpret_cast<uint32_t*>(neid);
             out.v2 = buf[dir].nbr;
-            out.v3 = opos[dir];
             nsort[dir] = sort_job(in, out, buf[dir].tmp, plan.npass, scratch_of(4 + dir, 2 + dir));
             fix[dir] = NOrderFix<V>{buf[dir].nbr, out.v0, neid, tpos[dir], own[dir], off[dir], nkey, nxref, nguide};
             D.nkey[dir] = nkey;
@@ -925,43 +927,14 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
                                fix[first], fix[1], m, n, D.bt, bn, D.nmul);
             return hipGetLastError() == hipSuccess ? TM_OK : tm_fail(TM_EDEVICE, "graph: list launch");
         };
-        auto n_orders = [&](const auto* jobs, int iota) -> int {
-            int res = 0;
-            if (paired) {
-                TM_TRY(sort_run(jobs, 2, m, plan, iota, flags + kSortErr, st, &res));
-                return fix_lists(0, 2);
-            }
-            for (int dir = 0; dir < 2; ++dir) {
-                TM_TRY(sort_run(jobs + dir, 1, m, plan, iota, flags + kSortErr, st, &res));
-                TM_TRY(fix_lists(dir, 1));
-            }
-            return TM_OK;
-        };
-        if (ranks) {
-            TM_TRY(n_orders(nsort, 8));
-        } else {
-            auto plain = [](const LR& x) {
-                L y;
-                y.k = x.k;
-                y.v0 = x.v0;
-                y.v1 = x.v1;
-                y.v2 = x.v2;
-                return y;
-            };
-            SortJob<L> three[2];
-            for (int dir = 0; dir < 2; ++dir)
-                three[dir] = SortJob<L>{plain(nsort[dir].in), {plain(nsort[dir].bufs[0]), plain(nsort[dir].bufs[1])},
-                                        nsort[dir].scratch};
-            TM_TRY(n_orders(three, 0));
+        int res = 0;
+        if (paired) {
+            TM_TRY(sort_run(nsort, 2, m, plan, 0, flags + kSortErr, st, &res));
+            return fix_lists(0, 2);
         }
-        if (ranks) {
-            uint4* rank[2] = {nullptr, nullptr};
-            for (uint4*& r : rank) TM_TRY(arena_alloc(g->arena, &r, m));
-            hipLaunchKernelGGL(pair_rank_kernel, dim3(grid_for(2 * m)), dim3(kBlock), 0, st, D,
-                               (const uint32_t*)own[0], (const uint32_t*)own[1], (const uint32_t*)opos[0],
-                               (const uint32_t*)opos[1], rank[0], rank[1]);
-            if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: rank launch");
-            for (int dir = 0; dir < 2; ++dir) D.nrank[dir] = rank[dir];
+        for (int dir = 0; dir < 2; ++dir) {
+            TM_TRY(sort_run(nsort + dir, 1, m, plan, 0, flags + kSortErr, st, &res));
+            TM_TRY(fix_lists(dir, 1));
         }
         return TM_OK;
     };

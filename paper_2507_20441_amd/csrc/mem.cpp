@@ -129,12 +129,25 @@ void dev_cache_trim() {
     for (const Block& b : drop) (void)hipFree(b.p);
 }
 
+u64 dev_room() {
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    const int dev = device_index();
+    std::lock_guard<std::mutex> lk(g_mu);
+    for (const Block& b : g_free[dev]) avail += b.cap;
+    return avail;
+}
+
 // While a capture is being recorded on this thread, released blocks are kept
 // by the capture's owner: the recorded work reuses them at every replay.
 static thread_local std::vector<std::pair<void*, hipStream_t>>* t_defer = nullptr;
 
 void dev_defer_begin(std::vector<std::pair<void*, hipStream_t>>* keep) { t_defer = keep; }
 void dev_defer_end() { t_defer = nullptr; }
+bool dev_deferring() { return t_defer != nullptr; }
 
 hipError_t dev_free(void* p, hipStream_t st) {
     if (!p) return hipSuccess;

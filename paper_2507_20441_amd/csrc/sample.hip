@@ -1313,7 +1313,7 @@ void fill_args(const tm_weights* w, SampleArgs* out, size_t* lds_out) {
     const HostPlan& P = w->plan;
     SampleArgs& a = *out;
     std::memset(&a, 0, sizeof a);
-    a.G = w->g->d;
+    a.G = graph_view(w->g);
     a.delta = P.mo.delta;
     a.ilen = w->ilen;
     a.exclude = (w->constraints & TM_C_EXCLUDE) ? 1 : 0;

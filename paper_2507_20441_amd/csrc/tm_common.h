@@ -67,7 +67,7 @@ struct DevGraph {
     // of list w; y: the first position in the N order of g's list 1 - w whose
     // key is >= (o, t); z: its T position in list 1 - w; w: how far in time
     // the nearest entries of o around those two N positions are (PairGaps).
-    // Null outside the sizes pair_ranks_kept names.
+    // Null for a graph that has none (graph_pair_ranks).
     const uint4* nrank[2];
     int bn;                    // bits of a vertex id
     uint32_t tmul, nmul;       // slice scale of times and of neighbours (slice_scale)
@@ -105,8 +105,7 @@ __device__ __forceinline__ uint32_t time_frac(TT x, int bt, uint32_t mul) {
 // no such edge).  Byte 0, 1: the entries of the same pair before and after the
 // edge in its own list; byte 2, 3: those of the pair in the vertex's other
 // list before t and at or after t (that gap plus one, as it may be zero).
-// (An edge given twice has the gap 0, coded as 1: such a graph is refused, some
-// of them only once their lists are there.)
+// (The gap 0, of an edge given twice, which no graph has, is coded as 1.)
 constexpr uint32_t kGapNone = 255;
 TM_HD uint32_t gap_code(u64 gap) {
     gap |= gap == 0 ? 1 : 0;

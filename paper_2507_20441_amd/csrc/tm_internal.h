@@ -2,6 +2,7 @@
 // error plumbing and the launchers each translation unit provides.
 #pragma once
 
+#include <atomic>
 #include <initializer_list>
 #include <memory>
 #include <string>
@@ -66,10 +67,14 @@ hipError_t dev_alloc(void** p, size_t bytes, hipStream_t st);
 hipError_t dev_free(void* p, hipStream_t st);
 // Synchronise the device and return every cached block to HIP.
 void dev_cache_trim();
+// Bytes the library could still allocate on the current device: HIP's free
+// memory and the cached blocks.
+u64 dev_room();
 // Between begin and end, dev_free on this thread appends to keep instead of
 // releasing (for work recorded into a graph, which replays on those blocks).
 void dev_defer_begin(std::vector<std::pair<void*, hipStream_t>>* keep);
 void dev_defer_end();
+bool dev_deferring();
 // Every block released on st becomes reusable by any stream.
 void dev_stream_synced(hipStream_t st);
 // hipStreamSynchronize, then dev_stream_synced.
@@ -137,6 +142,16 @@ private:
 // ---------------------------------------------------------------------------
 // Graph handle.
 // ---------------------------------------------------------------------------
+// The pair ranks of a graph (DevGraph::nrank), made by the weight builds that
+// they pay for (graph_pair_ranks) and kept as long as the graph.
+struct PairRanks {
+    enum : int { kNone, kBusy, kReady, kGivenUp };
+    std::atomic<int> state{kNone};
+    std::atomic<int> launches{0};  // level launches so far that would have read them
+    const uint4* rank[2] = {nullptr, nullptr};  // set before kReady
+    DevArena arena;
+};
+
 struct tm_graph {
     DevGraph d{};
     int64_t m = 0;
@@ -145,6 +160,7 @@ struct tm_graph {
     int64_t T = 0;
     int device = 0;
     DevArena arena;
+    PairRanks ranks;
     // the caller's allocator of everything built on this graph (has_alloc)
     tm_allocator alloc{};
     bool has_alloc = false;
@@ -269,6 +285,22 @@ struct tm_weights {
 // ---------------------------------------------------------------------------
 int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64_t* t,
                 hipStream_t st);
+// Makes g's pair ranks (32 B per edge), on st and waited for, in the first
+// weight build that they pay for: one with at least kRankLaunches level
+// launches, or that brings the graph's to kRankAllLaunches; `launches` are this
+// build's, and `need` its tables' bytes, which come first.  A graph that cannot
+// have them, or not while work is recorded, goes on without.
+//   Making them takes 40 us at 5e5 edges, 60 at 1e6, 240 at 4e6, 1.2 ms at 2e7
+// and 6.8 ms at 1e8; a level launch then gains 3, 11, 70, 330 and 2000 us.
+// Made by every graph build they had one of 1e8 edges take 35.1 ms, which takes
+// 29.6 without (2e7: 7.2 and 6.1), whatever was asked of the graph afterwards.
+// Below 2^19 edges a graph would have to meet many motifs to earn them; above
+// 2^28 their memory goes to weight sets, as that of the owners.
+constexpr int64_t kRanksFrom = (int64_t)1 << 19, kRanksTo = (int64_t)1 << 28;
+constexpr int kRankLaunches = 3, kRankAllLaunches = 8;
+void graph_pair_ranks(tm_graph* g, int launches, u64 need, hipStream_t st);
+// The graph as kernels take it, with the pair ranks that are there.
+DevGraph graph_view(const tm_graph* g);
 // model_bytes (optional): the level kernels' access-model bytes (every
 // attempt, as the level stage timing counts every attempt).
 int weights_build(tm_weights* w, hipStream_t st, u64* model_bytes = nullptr);

@@ -466,7 +466,7 @@ __device__ __forceinline__ uint32_t block_excl_scan_256(uint32_t v, uint32_t* ws
 }
 
 // ---------------------------------------------------------------------------
-// Stable LSD radix sort of keys that carry up to four value arrays
+// Stable LSD radix sort of keys that carry up to three value arrays
 // (structure of arrays), one kernel per digit of up to 8 bits:
 //  * sort_hist_kernel counts the digits of every pass in one read of the
 //    keys (each pass turns its counts into the digits' first positions);
@@ -564,8 +564,8 @@ struct SortSize<SortNone> {
 };
 
 struct SortIO {
-    const void* in[5];  // keys, then the value arrays
-    void* out[5];
+    const void* in[4];  // keys, then the value arrays
+    void* out[4];
     const uint32_t* counts;
     uint32_t* ticket;
     u64* status;
@@ -663,11 +663,11 @@ __device__ __forceinline__ void sort_move_values(const void* vin, void* vout, bo
     }
 }
 
-template <typename K, typename V0, typename V1, typename V2, typename V3, int kItems>
+template <typename K, typename V0, typename V1, typename V2, int kItems>
 __global__ void __launch_bounds__(kBlock)
 sort_pass_kernel(SortPass pass, int64_t n, int shift, int bits, uint32_t tag, int iota, int* __restrict__ err) {
     constexpr size_t kElt = std::max(std::max(sizeof(K), SortSize<V0>::value),
-                                     std::max(std::max(SortSize<V1>::value, SortSize<V2>::value), SortSize<V3>::value));
+                                     std::max(SortSize<V1>::value, SortSize<V2>::value));
     constexpr int kTile = kBlock * kItems;
     constexpr bool kPre = kItems <= kSortItemsSmall;
     __shared__ __align__(16) unsigned char sbuf[kElt * kTile];
@@ -682,7 +682,7 @@ sort_pass_kernel(SortPass pass, int64_t n, int shift, int bits, uint32_t tag, in
     const int which = blockIdx.y;
     SortIO io;
 #pragma unroll
-    for (int x = 0; x < 5; ++x) {
+    for (int x = 0; x < 4; ++x) {
         io.in[x] = pick_arg(pass.io[0].in[x], pass.io[1].in[x], which);
         io.out[x] = pick_arg(pass.io[0].out[x], pass.io[1].out[x], which);
     }
@@ -707,7 +707,6 @@ sort_pass_kernel(SortPass pass, int64_t n, int shift, int bits, uint32_t tag, in
     V0 x0[kPre ? kItems : 1];
     V1 x1[kPre ? kItems : 1];
     V2 x2[kPre ? kItems : 1];
-    V3 x3[kPre ? kItems : 1];
     uint32_t lp[kItems];  // (the digits are recomputed from the keys: fewer registers)
     if (tbase + kTile <= n) {
         // a whole tile: one base address, the items at fixed offsets
@@ -725,7 +724,6 @@ sort_pass_kernel(SortPass pass, int64_t n, int shift, int bits, uint32_t tag, in
         sort_load_values(io.in[1], iota & 1, wbase, lane, n, x0);
         sort_load_values(io.in[2], iota & 2, wbase, lane, n, x1);
         sort_load_values(io.in[3], iota & 4, wbase, lane, n, x2);
-        sort_load_values(io.in[4], iota & 8, wbase, lane, n, x3);
     }
 #pragma unroll
     for (int k = 0; k < kItems; ++k) {
@@ -838,18 +836,15 @@ sort_pass_kernel(SortPass pass, int64_t n, int shift, int bits, uint32_t tag, in
                                        tn);
     sort_move_values<V2, kItems, kPre>(io.in[3], io.out[3], iota & 4, wbase, lane, n, lp, x2, sbuf, sdig, gofs,
                                        tn);
-    sort_move_values<V3, kItems, kPre>(io.in[4], io.out[4], iota & 8, wbase, lane, n, lp, x3, sbuf, sdig, gofs,
-                                       tn);
 }
 
-// A key array and up to four value arrays (null where a value is absent).
-template <typename K, typename V0 = SortNone, typename V1 = SortNone, typename V2 = SortNone, typename V3 = SortNone>
+// A key array and up to three value arrays (null where a value is absent).
+template <typename K, typename V0 = SortNone, typename V1 = SortNone, typename V2 = SortNone>
 struct SortSet {
     K* k = nullptr;
     V0* v0 = nullptr;
     V1* v1 = nullptr;
     V2* v2 = nullptr;
-    V3* v3 = nullptr;
 };
 
 // Where a sort's passes read and write: pass p reads `in` (p = 0) or the
@@ -869,10 +864,10 @@ struct SortJob {
 // leaves the chip idle, and two fill it better for the time of one.  Sets
 // *result to the index of the buffer that holds the result.  iota: bit j set,
 // value array j holds nothing yet and stands for 0, 1, ..., n - 1.
-template <typename K, typename V0, typename V1, typename V2, typename V3>
-int sort_run(const SortJob<SortSet<K, V0, V1, V2, V3>>* jobs, int njobs, int64_t n, const SortPlan& P, int iota,
+template <typename K, typename V0, typename V1, typename V2>
+int sort_run(const SortJob<SortSet<K, V0, V1, V2>>* jobs, int njobs, int64_t n, const SortPlan& P, int iota,
              int* err, hipStream_t st, int* result) {
-    using S = SortSet<K, V0, V1, V2, V3>;
+    using S = SortSet<K, V0, V1, V2>;
     *result = (P.npass - 1) & 1;
     if (n <= 0 || P.npass <= 0) return TM_OK;
     SortScratch scratch[2];
@@ -901,19 +896,19 @@ int sort_run(const SortJob<SortSet<K, V0, V1, V2, V3>>* jobs, int njobs, int64_t
             const int y = j < njobs ? j : 0;
             const S& src = p == 0 ? jobs[y].in : jobs[y].bufs[(p - 1) & 1];
             const S& dst = jobs[y].bufs[p & 1];
-            pass.io[j] = SortIO{{src.k, src.v0, src.v1, src.v2, src.v3},
-                                {dst.k, dst.v0, dst.v1, dst.v2, dst.v3},
+            pass.io[j] = SortIO{{src.k, src.v0, src.v1, src.v2},
+                                {dst.k, dst.v0, dst.v1, dst.v2},
                                 scratch[y].counts + p * kSortDigits,
                                 scratch[y].tickets + p,
                                 scratch[y].status};
         }
         const uint32_t tag = scratch[0].tag0 + (uint32_t)p + 1;
         if (items == kSortItems)
-            hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, V3, kSortItems>), grid, dim3(kBlock), 0, st, pass, n,
+            hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, kSortItems>), grid, dim3(kBlock), 0, st, pass, n,
                                P.shift[p], P.bits[p], tag, p == 0 ? iota : 0, err);
         else
-            hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, V3, kSortItemsSmall>), grid, dim3(kBlock), 0, st, pass,
-                               n, P.shift[p], P.bits[p], tag, p == 0 ? iota : 0, err);
+            hipLaunchKernelGGL((sort_pass_kernel<K, V0, V1, V2, kSortItemsSmall>), grid, dim3(kBlock), 0, st, pass, n,
+                               P.shift[p], P.bits[p], tag, p == 0 ? iota : 0, err);
         if (hipGetLastError() != hipSuccess) rc = tm_fail(TM_EDEVICE, "sort: pass launch");
     }
     if (own) {

@@ -788,6 +788,7 @@ int build_typed(tm_weights* w, hipStream_t st, int* ovf, int* ovf_c, bool check_
     const HostPlan& P = w->plan;
     const int64_t m = g->m;
     const int64_t delta = P.mo.delta;
+    const DevGraph G = graph_view(g);
     w->has_win = !w->lean && weights_keep_windows(P, m);
     // bottom-up over heights; leaves other than the center have weight 1 and
     // no table (a lone center edge gets a table of ones)
@@ -816,7 +817,7 @@ int build_typed(tm_weights* w, hipStream_t st, int* ovf, int* ovf_c, bool check_
                 const std::vector<int>& cs = grp[side];
                 LevelArgs a;
                 std::memset(&a, 0, sizeof a);
-                a.G = g->d;
+                a.G = G;
                 a.delta = delta;
                 a.ilen = w->ilen;
                 a.exclude = (w->constraints & TM_C_EXCLUDE) ? 1 : 0;
@@ -996,6 +997,18 @@ int64_t interval_unit(const tm_weights* w) {
     return (w->constraints & TM_C_WINDOWS) ? w->plan.mo.delta : w->g->T + 1;
 }
 
+// Level launches of a weight build: one per slot with children and endpoint
+// that children attach at.
+int level_launches(const HostPlan& P) {
+    int n = 0;
+    for (int s = 0; s < P.nt; ++s) {
+        bool at[2] = {false, false};
+        for (int j = 0; j < P.n_children[s]; ++j) at[P.side[P.children[s][j]]] = true;
+        n += (at[0] ? 1 : 0) + (at[1] ? 1 : 0);
+    }
+    return n;
+}
+
 int weights_build(tm_weights* w, hipStream_t st, u64* model_bytes) {
     tm_graph* g = w->g;
     w->ilen = interval_unit(w);
@@ -1009,6 +1022,10 @@ int weights_build(tm_weights* w, hipStream_t st, u64* model_bytes) {
     if (w->q >= ((int64_t)1 << 31)) return tm_fail(TM_ERANGE, "weights: too many intervals");
     StageTimer timer;
     timer.start(TM_STAGE_WEIGHTS, st);
+    graph_pair_ranks(g, level_launches(w->plan),
+                     weights_footprint(w->plan, g->m, w->q, w->width_mode == 2, w->lean) +
+                         weights_build_extra(g->m, w->width_mode == 2),
+                     st);
     std::vector<std::unique_ptr<StageTimer>> level_timers;
     int* ovf = nullptr;
     TM_HIP(dev_alloc((void**)&ovf, 2 * sizeof(int), st));
@@ -1161,6 +1178,8 @@ int weights_enqueue(tm_weights* w, hipStream_t st, int* ovf,
     if (g->m == 0) return TM_OK;
     if (w->q >= ((int64_t)1 << 31)) return tm_fail(TM_ERANGE, "weights: too many intervals");
     clear_tables(w);
+    graph_pair_ranks(g, level_launches(w->plan),
+                     weights_footprint(w->plan, g->m, w->q, false, w->lean) + weights_build_extra(g->m, false), st);
     const int rc = build_typed<u64>(w, st, ovf, ovf, false, nullptr, level_timers);
     if (rc != TM_OK) clear_tables(w);
     return rc;
