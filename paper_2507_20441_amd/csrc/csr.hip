@@ -298,62 +298,71 @@ __device__ __forceinline__ void wave_fill(int32_t* out, int64_t from, int64_t to
 template <typename F>
 __device__ __forceinline__ void guide_fill(const uint32_t* own, const int32_t* off, int64_t m, int32_t n, int64_t p,
                                            const F& key, int bits, uint32_t mul, int32_t* guide) {
-    int64_t from = 0, to = 0, end = 0;
+    auto entry = [&](int64_t i) -> int64_t {
+        // (clamped: a broken order must not write outside the guide)
+        const int32_t g = own[i] < (uint32_t)n ? (int32_t)own[i] : n - 1;
+        const int32_t a = off[g], b = off[g + 1];
+        const int32_t ns = guide_slices(a, b);
+        const int64_t at = guide_first(g, a) + slice_of(slice_frac(key(i), bits, mul), ns > 0 ? ns : 1);
+        const int64_t last = guide_first(n, (int32_t)m);
+        return at < 0 ? 0 : (at > last ? last : at);
+    };
+    int64_t to = 0, end = 0;
     if (p < m) {
-        auto entry = [&](int64_t i) -> int64_t {
-            // (clamped: a broken order must not write outside the guide)
-            const int32_t g = own[i] < (uint32_t)n ? (int32_t)own[i] : n - 1;
-            const int32_t a = off[g], b = off[g + 1];
-            const int32_t ns = guide_slices(a, b);
-            const int64_t at = guide_first(g, a) + slice_of(slice_frac(key(i), bits, mul), ns > 0 ? ns : 1);
-            const int64_t last = guide_first(n, (int32_t)m);
-            return at < 0 ? 0 : (at > last ? last : at);
-        };
         to = entry(p) + 1;
-        from = p == 0 ? 0 : entry(p - 1) + 1;
         if (p == m - 1) end = guide_first(n, (int32_t)m) + 1;
     }
+    // the previous position's is the lane's before (the wave's first looks itself)
+    int64_t from = __shfl_up((long long)to, 1, 64);
+    if ((threadIdx.x & 63) == 0) from = p == 0 || p >= m ? 0 : entry(p - 1) + 1;
+    if (p >= m) from = 0;
     wave_fill(guide, from, to, (int32_t)p);
     wave_fill(guide, to, end, (int32_t)m);
 }
 
 // What follows a T-order sort, in one pass over the positions of each
-// direction (blockIdx.y): by eid the edge's position (the inverse of leid), the
-// (neighbour, time) records of 32-bit lists, and the guide by time.
+// direction (blockIdx.y): the (neighbour, time) records of 32-bit lists, and by
+// eid the edge's position (the inverse of leid); each where it is asked for.
+//
+// The positions' scattered writes are its time.  Up to 2^26 edges everything
+// goes in one launch; above, where an array of positions no longer fits the
+// 256 MB cache behind the L2s, the records' stream and the other direction's
+// writes push it out, and the four parts go one after the other (1e8 edges 6.0
+// and 4.8 ms, 2e7 0.60 and 0.73 ms).
+constexpr int64_t kFinishTogether = (int64_t)1 << 26;
+
 template <typename TT>
 struct ListFinish {
-    const uint32_t* own;
     const int32_t* leid;
     const uint32_t* nbr;
     const TT* t;
-    const int32_t* off;
     int32_t* pos;
     uint2* nt;
-    int32_t* guide;
 };
 
 template <typename TT>
-__global__ void __launch_bounds__(kBlock)
-list_finish_kernel(ListFinish<TT> f0, ListFinish<TT> f1, int64_t m, int32_t n, int bt, uint32_t tmul) {
+__global__ void __launch_bounds__(kBlock) list_finish_kernel(ListFinish<TT> f0, ListFinish<TT> f1, int64_t m) {
     const int y = blockIdx.y;
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const TT* t = pick_arg(f0.t, f1.t, y);
-    if (p < m) {
-        const int32_t e = pick_arg(f0.leid, f1.leid, y)[p];
-        if ((uint32_t)e < (uint64_t)m) pick_arg(f0.pos, f1.pos, y)[e] = (int32_t)p;
-        uint2* nt = pick_arg(f0.nt, f1.nt, y);
-        if (nt) nt[p] = make_uint2(pick_arg(f0.nbr, f1.nbr, y)[p], (uint32_t)t[p]);
-    }
-    int32_t* guide = pick_arg(f0.guide, f1.guide, y);
-    if (guide)
-        guide_fill(pick_arg(f0.own, f1.own, y), pick_arg(f0.off, f1.off, y), m, n, p,
-                   [&](int64_t i) { return (u64)t[i]; }, bt, tmul, guide);
+    if (p >= m) return;
+    const int32_t e = pick_arg(f0.leid, f1.leid, y)[p];
+    uint2* nt = pick_arg(f0.nt, f1.nt, y);
+    if (nt) nt[p] = make_uint2(pick_arg(f0.nbr, f1.nbr, y)[p], (uint32_t)pick_arg(f0.t, f1.t, y)[p]);
+    int32_t* pos = pick_arg(f0.pos, f1.pos, y);
+    if (pos && (uint32_t)e < (uint64_t)m) pos[e] = (int32_t)p;
 }
 
 // N order (of one direction, or of both: blockIdx.y): the packed key from the
 // carried neighbour and time (time: the carried times, which may be nkey
-// itself), each entry's position in the direction's T order, and the guide by
-// neighbour.  own: the owners, the same sequence in both orders.
+// itself), each entry's position in the direction's T order, and the guides by
+// neighbour and by time.  own: the owners, the same sequence in both orders;
+// tt: the T order's times.
+//
+// The positions are random reads and the kernel's time; the guides' own reads
+// and stores pass beside them (2e7 edges, per direction: 419 us without guides,
+// 455 with both).  Beside the scattered position writes of list_finish_kernel
+// the guides by time cost it 100 us there, as a load after such a store waits for
+// it.
 template <typename TT>
 struct NOrderFix {
     const uint32_t* nbr;
@@ -362,14 +371,17 @@ struct NOrderFix {
     const int32_t* tpos;
     const uint32_t* own;
     const int32_t* off;
+    const TT* tt;
     u64* nkey;
     int32_t* nxref;
-    int32_t* guide;
+    int32_t* nguide;
+    int32_t* tguide;
 };
 
 template <typename TT>
 __global__ void __launch_bounds__(kBlock)
-n_order_fix_kernel(NOrderFix<TT> f0, NOrderFix<TT> f1, int64_t m, int32_t n, int bt, int bn, uint32_t nmul) {
+n_order_fix_kernel(NOrderFix<TT> f0, NOrderFix<TT> f1, int64_t m, int32_t n, int bt, int bn, uint32_t tmul,
+                   uint32_t nmul) {
     const int y = blockIdx.y;
     const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const uint32_t* nbr = pick_arg(f0.nbr, f1.nbr, y);
@@ -378,10 +390,13 @@ n_order_fix_kernel(NOrderFix<TT> f0, NOrderFix<TT> f1, int64_t m, int32_t n, int
         const int32_t e = pick_arg(f0.neid, f1.neid, y)[q];
         pick_arg(f0.nxref, f1.nxref, y)[q] = (uint32_t)e < (uint64_t)m ? pick_arg(f0.tpos, f1.tpos, y)[e] : -1;
     }
-    int32_t* guide = pick_arg(f0.guide, f1.guide, y);
-    if (guide)
-        guide_fill(pick_arg(f0.own, f1.own, y), pick_arg(f0.off, f1.off, y), m, n, q,
-                   [&](int64_t i) { return (u64)nbr[i]; }, bn, nmul, guide);
+    int32_t* nguide = pick_arg(f0.nguide, f1.nguide, y);
+    if (!nguide) return;
+    const uint32_t* own = pick_arg(f0.own, f1.own, y);
+    const int32_t* off = pick_arg(f0.off, f1.off, y);
+    const TT* tt = pick_arg(f0.tt, f1.tt, y);
+    guide_fill(own, off, m, n, q, [&](int64_t i) { return (u64)nbr[i]; }, bn, nmul, nguide);
+    guide_fill(own, off, m, n, q, [&](int64_t i) { return (u64)tt[i]; }, bt, tmul, pick_arg(f0.tguide, f1.tguide, y));
 }
 
 // The pair ranks of both lists (see DevGraph) of a finished graph, in one
@@ -817,7 +832,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         int32_t* tpos[2] = {nullptr, nullptr};
         TT* ltab[2] = {nullptr, nullptr};
         uint32_t* lnbr_of[2] = {nullptr, nullptr};  // each T order's neighbours (the N-order sorts' keys)
-        int32_t* off[2] = {nullptr, nullptr};
+        int32_t *off[2] = {nullptr, nullptr}, *tguide[2] = {nullptr, nullptr};
         // guides pay from lists of a few entries on; with fewer edges than
         // vertices the lists are shorter than that (1e6 edges, 9e5 and 1.1e6
         // vertices: a build 511 and 503 us, a 6-chain estimate 375 and 379)
@@ -854,9 +869,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             TM_TRY(arena_alloc(g->arena, &tpos[dir], (size_t)m));
             own[dir] = keep_own ? reinterpret_cast<uint32_t*>(lown) : reinterpret_cast<uint32_t*>(work[3]) + dir * m;
             uint2* nt = nullptr;
-            int32_t* tguide = nullptr;
             if constexpr (sizeof(TT) == 4) TM_TRY(arena_alloc(g->arena, &nt, m));
-            if (guides) TM_TRY(arena_alloc(g->arena, &tguide, guide_len));
+            if (guides) TM_TRY(arena_alloc(g->arena, &tguide[dir], guide_len));
             L in, out;
             in.k = reinterpret_cast<uint32_t*>(dir == 0 ? esrc : edst);
             in.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(t32e) : reinterpret_cast<V*>(et);
@@ -866,11 +880,10 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             out.v1 = reinterpret_cast<uint32_t*>(leid);
             out.v2 = reinterpret_cast<uint32_t*>(lnbr);
             tsort[dir] = sort_job(in, out, buf[dir].tmp, plan.npass, scratch_of(2 + dir, 2 + dir));
-            fin[dir] = ListFinish<TT>{own[dir], leid, reinterpret_cast<uint32_t*>(lnbr), lt, off[dir], tpos[dir], nt,
-                                      tguide};
+            fin[dir] = ListFinish<TT>{leid, reinterpret_cast<uint32_t*>(lnbr), lt, tpos[dir], nt};
             D.off[dir] = off[dir];
             D.tpos[dir] = tpos[dir];
-            D.tguide[dir] = tguide;
+            D.tguide[dir] = tguide[dir];
             ltab[dir] = lt;
             if constexpr (sizeof(TT) == 4) {
                 D.lt32[dir] = reinterpret_cast<const uint32_t*>(lt);
@@ -890,8 +903,20 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         TM_TRY(sort_lists(tsort, 2 /* eids: 0, 1, ... */));
         hipLaunchKernelGGL(offsets_kernel, dim3(grid_for(m), 2), dim3(kBlock), 0, st, (const uint32_t*)own[0],
                            (const uint32_t*)own[1], m, n, off[0], off[1]);
-        hipLaunchKernelGGL((list_finish_kernel<TT>), dim3(grid_for(m), 2), dim3(kBlock), 0, st, fin[0], fin[1], m, n,
-                           D.bt, D.tmul);
+        auto finish = [&](const ListFinish<TT>& f0, const ListFinish<TT>& f1, unsigned dirs) {
+            hipLaunchKernelGGL((list_finish_kernel<TT>), dim3(grid_for(m), dirs), dim3(kBlock), 0, st, f0, f1, m);
+        };
+        if (m <= kFinishTogether) {
+            finish(fin[0], fin[1], 2);
+        } else {
+            for (const ListFinish<TT>& f : fin) {
+                ListFinish<TT> pos = f, records = f;
+                pos.nt = nullptr;
+                records.pos = nullptr;
+                finish(pos, pos, 1);
+                if (records.nt) finish(records, records, 1);
+            }
+        }
         if (hipGetLastError() != hipSuccess) return tm_fail(TM_EDEVICE, "graph: list launch");
         // N order of dir d: the T order of the other direction (sorted by this
         // direction's neighbour, then time) stably re-sorted by this
@@ -916,7 +941,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             out.v1 = reinterpret_cast<uint32_t*>(neid);
             out.v2 = buf[dir].nbr;
             nsort[dir] = sort_job(in, out, buf[dir].tmp, plan.npass, scratch_of(4 + dir, 2 + dir));
-            fix[dir] = NOrderFix<V>{buf[dir].nbr, out.v0, neid, tpos[dir], own[dir], off[dir], nkey, nxref, nguide};
+            fix[dir] = NOrderFix<V>{buf[dir].nbr, out.v0, neid, tpos[dir], own[dir], off[dir],
+                                    reinterpret_cast<const V*>(ltab[dir]), nkey, nxref, nguide, tguide[dir]};
             D.nkey[dir] = nkey;
             D.nxref[dir] = nxref;
             D.neid[dir] = neid;
@@ -924,7 +950,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         }
         auto fix_lists = [&](int first, int count) -> int {
             hipLaunchKernelGGL((n_order_fix_kernel<V>), dim3(grid_for(m), (unsigned)count), dim3(kBlock), 0, st,
-                               fix[first], fix[1], m, n, D.bt, bn, D.nmul);
+                               fix[first], fix[1], m, n, D.bt, bn, D.tmul, D.nmul);
             return hipGetLastError() == hipSuccess ? TM_OK : tm_fail(TM_EDEVICE, "graph: list launch");
         };
         int res = 0;

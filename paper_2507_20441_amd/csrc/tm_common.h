@@ -36,8 +36,9 @@ constexpr int kWaves = kBlock / 64;
 // search of a list was one dependent probe per doubling of its length, and
 // the kernels that search are bound by those probes (the level kernel at 1e8
 // edges 10.5 -> 9.2 ms a launch, the sampler without kept windows at 1e6
-// edges 3.97 -> 3.20 ms per 2e7 samples; 0.75 ms per list order to build at
-// 1e8 edges, 0.5 B per edge and 4 B per vertex each).
+// edges 3.97 -> 3.20 ms per 2e7 samples; 0.1 ms per list order to build at 1e8
+// edges, beside the random reads of n_order_fix_kernel, 0.5 B per edge and 4 B
+// per vertex each).
 struct DevGraph {
     int64_t m;
     int32_t n;
