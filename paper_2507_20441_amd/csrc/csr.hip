@@ -71,6 +71,8 @@ validate_kernel(const int32_t* src, const int32_t* dst, const int64_t* t, int64_
 // where few of them would repeat.
 constexpr int kTieSamples = 4096;
 
+constexpr double kTieMean = 20;
+
 int tie_samples(int64_t m) { return m < ((int64_t)1 << 23) ? kTieSamples / 4 : kTieSamples; }
 
 __device__ __forceinline__ int repeated_times(const int64_t* t, int64_t m, int samples) {
@@ -718,9 +720,12 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     // edges 421 and 342 us, 4e6 1.94 and 1.57 ms, 2e7 9.32 and 7.26 ms.)  It pays
     // while fewer than half of the edges are in long runs (each then costs the
     // full sort's passes on top); past that the full sort starts over, so where
-    // the sampled times say that an edge shares its time with more than 64
-    // others on average, it is not tried (the passes in vain made a build of 4e6
-    // edges at whole days 2.2 instead of 1.5 ms).
+    // the sampled times say that an edge shares its time with more than kTieMean
+    // others on average, it is not tried: each edge reads that many to find its
+    // place.  Every time held by 16, 24 and 60 edges, the full sort and this way:
+    // 4e6 edges 1397 and 1378, 1391 and 1425, 1372 and 1636 us; 2e7 7.00 and
+    // 6.71, 6.97 and 6.95, 6.88 and 8.02 ms; 1e6 456 and 417, 458 and 432, 453
+    // and 490 us.
     auto order_by_time = [&](bool* done) -> int {
         u64 *key, *uv = nullptr;
         u64 *lk, *lv = nullptr, *lk1, *lv1 = nullptr;  // the listed edges' keys and their sort's other buffers
@@ -764,7 +769,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     };
     bool ordered = false;
     const double pairs = 0.5 * tie_samples(m) * (tie_samples(m) - 1);
-    if (rc == TM_OK && m / 8 <= g->T && (double)hb[2] * (double)m <= 64.0 * pairs) rc = order_by_time(&ordered);
+    if (rc == TM_OK && m / 8 <= g->T && (double)hb[2] * (double)m <= kTieMean * pairs) rc = order_by_time(&ordered);
     if (rc == TM_OK && !ordered) {
         u64 *key = nullptr, *uv = nullptr;
         rc = order_all(work[0], work[1], work[2], work[3], m, &key, &uv);
