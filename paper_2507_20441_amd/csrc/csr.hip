@@ -474,7 +474,7 @@ __global__ void offsets_kernel(const uint32_t* key0, const uint32_t* key1, int64
 // List sorts side by side up to this many edges (a pass of few tiles leaves the
 // chip idle: a build of 2^14 edges takes 167 us with pairs and 201 without,
 // 2^20 512 and 630, 2^21 862 and 1028, 2^22 1685 and 1760).  Larger builds
-// gain 3% and keep the memory of the second buffers (28 to 36 B per edge).
+// gain 3% and keep the memory of the second buffers (28 to 32 B per edge).
 constexpr int64_t kPairedSorts = (int64_t)1 << 22;
 
 int bits_for(u64 x) {
@@ -799,19 +799,62 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         using TT = decltype(time_tag);
         using V = typename std::conditional<sizeof(TT) == 4, uint32_t, u64>::type;
         using L = SortSet<uint32_t, V, uint32_t, uint32_t>;
-        // Graphs of few sort tiles sort both directions side by side, with
-        // buffers of their own; larger ones in turn, through the same ones.
-        const bool paired = m <= kPairedSorts;
-        struct Bufs {
-            L tmp;               // the other buffer of the list sorts
-            uint32_t* nkeys;      // N order: its sorted keys (unused)
-            uint32_t* ntime;      // N order: the carried 32-bit times (64-bit ones: the key array itself,
-                                  // packed in place afterwards)
-            uint32_t* nbr;        // N order: the carried neighbours
-        } buf[2];
+        // What every list needs, then what a build can go on without.
+        TT* lt[2] = {nullptr, nullptr};
+        int32_t *leid[2], *lnbr[2], *lown[2] = {nullptr, nullptr}, *off[2], *tpos[2], *nxref[2], *neid[2];
+        uint2* nt[2] = {nullptr, nullptr};
+        u64* nkey[2];
         const bool keep_own = m <= ((int64_t)1 << 28);
         if (!keep_own && dev_alloc((void**)&nbr_tmp, (size_t)m * sizeof(uint32_t), st) != hipSuccess)
             return tm_fail(TM_ENOMEM, "graph: work arrays");
+        for (int dir = 0; dir < 2; ++dir) {
+            TM_TRY(arena_alloc(g->arena, &lt[dir], (size_t)m));
+            TM_TRY(arena_alloc(g->arena, &leid[dir], (size_t)m));
+            if constexpr (sizeof(TT) == 4) {
+                // the neighbours end up in the (neighbour, time) records
+                if (dev_alloc((void**)&nbr32[dir], (size_t)m * sizeof(uint32_t), st) != hipSuccess)
+                    return tm_fail(TM_ENOMEM, "graph: work arrays");
+                lnbr[dir] = reinterpret_cast<int32_t*>(nbr32[dir]);
+                TM_TRY(arena_alloc(g->arena, &nt[dir], (size_t)m));
+            } else {
+                TM_TRY(arena_alloc(g->arena, &lnbr[dir], (size_t)m));
+            }
+            if (keep_own) TM_TRY(arena_alloc(g->arena, &lown[dir], (size_t)m));
+            TM_TRY(arena_alloc(g->arena, &off[dir], (size_t)n + 1));
+            TM_TRY(arena_alloc(g->arena, &tpos[dir], (size_t)m));
+            TM_TRY(arena_alloc(g->arena, &nkey[dir], (size_t)m));
+            TM_TRY(arena_alloc(g->arena, &nxref[dir], (size_t)m));
+            TM_TRY(arena_alloc(g->arena, &neid[dir], (size_t)m));
+        }
+        // guides pay from lists of a few entries on; with fewer edges than
+        // vertices the lists are shorter than that (1e6 edges, 9e5 and 1.1e6
+        // vertices: a build 511 and 503 us, a 6-chain estimate 375 and 379)
+        // and the guides' entry per vertex would outweigh the edges
+        int32_t *tguide[2] = {nullptr, nullptr}, *nguide[2] = {nullptr, nullptr};
+        if (n <= m) {
+            const size_t len = (size_t)guide_first(n, (int32_t)m) + 1;
+            int32_t* block = nullptr;
+            if (arena_alloc(g->arena, &block, 4 * len) == TM_OK)
+                for (int dir = 0; dir < 2; ++dir) {
+                    tguide[dir] = block + (2 * dir) * len;
+                    nguide[dir] = block + (2 * dir + 1) * len;
+                }
+        }
+        // Graphs of few sort tiles sort both directions side by side, with
+        // buffers of their own (six 4-byte arrays and the values of type V);
+        // larger ones in turn, through the same ones.
+        bool paired = m <= kPairedSorts;
+        if (paired && dev_alloc((void**)&second, (size_t)m * (6 * sizeof(uint32_t) + sizeof(V)), st) != hipSuccess) {
+            (void)hipGetLastError();
+            paired = false;
+        }
+        struct Bufs {
+            L tmp;           // the other buffer of the list sorts
+            uint32_t* nkeys;  // N order: its sorted keys (unused)
+            uint32_t* ntime;  // N order: the carried 32-bit times (64-bit ones: the key array itself,
+                              // packed in place afterwards)
+            uint32_t* nbr;    // N order: the carried neighbours
+        } buf[2];
         buf[0].tmp.k = reinterpret_cast<uint32_t*>(work[0]);
         buf[0].tmp.v1 = reinterpret_cast<uint32_t*>(work[0]) + m;
         buf[0].tmp.v0 = reinterpret_cast<V*>(work[1]);
@@ -821,9 +864,6 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         buf[0].nbr = keep_own ? reinterpret_cast<uint32_t*>(work[3]) : nbr_tmp;
         buf[1] = buf[0];
         if (paired) {
-            // six 4-byte arrays and the values of type V
-            if (dev_alloc((void**)&second, (size_t)m * (6 * sizeof(uint32_t) + sizeof(V)), st) != hipSuccess)
-                return tm_fail(TM_ENOMEM, "graph: work arrays");
             buf[1].tmp.v0 = reinterpret_cast<V*>(second);
             uint32_t* at = reinterpret_cast<uint32_t*>(buf[1].tmp.v0 + m);
             uint32_t** const arrays[6] = {&buf[1].tmp.k, &buf[1].tmp.v1, &buf[1].tmp.v2, &buf[1].nkeys, &buf[1].ntime,
@@ -833,17 +873,10 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
                 at += m;
             }
         }
-        uint32_t* own[2] = {nullptr, nullptr};
-        int32_t* tpos[2] = {nullptr, nullptr};
-        TT* ltab[2] = {nullptr, nullptr};
-        uint32_t* lnbr_of[2] = {nullptr, nullptr};  // each T order's neighbours (the N-order sorts' keys)
-        int32_t *off[2] = {nullptr, nullptr}, *tguide[2] = {nullptr, nullptr};
-        // guides pay from lists of a few entries on; with fewer edges than
-        // vertices the lists are shorter than that (1e6 edges, 9e5 and 1.1e6
-        // vertices: a build 511 and 503 us, a 6-chain estimate 375 and 379)
-        // and the guides' entry per vertex would outweigh the edges
-        const bool guides = n <= m;
-        const size_t guide_len = (size_t)guide_first(n, (int32_t)m) + 1;
+        uint32_t* own[2];
+        for (int dir = 0; dir < 2; ++dir)
+            own[dir] = keep_own ? reinterpret_cast<uint32_t*>(lown[dir])
+                                : reinterpret_cast<uint32_t*>(work[3]) + dir * m;
         const SortPlan plan = sort_plan_copy(0, bn);
         // two sorts side by side, or one after the other
         auto sort_lists = [&](auto* jobs, int iota) -> int {
@@ -857,53 +890,32 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         SortJob<L> tsort[2];
         ListFinish<TT> fin[2];
         for (int dir = 0; dir < 2; ++dir) {
-            TT* lt = nullptr;
-            int32_t *leid = nullptr, *lnbr = nullptr, *lown = nullptr;
-            TM_TRY(arena_alloc(g->arena, &lt, m));
-            TM_TRY(arena_alloc(g->arena, &leid, m));
-            if constexpr (sizeof(TT) == 4) {
-                // the neighbours end up in the (neighbour, time) records
-                if (dev_alloc((void**)&nbr32[dir], (size_t)m * sizeof(uint32_t), st) != hipSuccess)
-                    return tm_fail(TM_ENOMEM, "graph: work arrays");
-                lnbr = reinterpret_cast<int32_t*>(nbr32[dir]);
-            } else {
-                TM_TRY(arena_alloc(g->arena, &lnbr, m));
-            }
-            if (keep_own) TM_TRY(arena_alloc(g->arena, &lown, m));
-            TM_TRY(arena_alloc(g->arena, &off[dir], (size_t)n + 1));
-            TM_TRY(arena_alloc(g->arena, &tpos[dir], (size_t)m));
-            own[dir] = keep_own ? reinterpret_cast<uint32_t*>(lown) : reinterpret_cast<uint32_t*>(work[3]) + dir * m;
-            uint2* nt = nullptr;
-            if constexpr (sizeof(TT) == 4) TM_TRY(arena_alloc(g->arena, &nt, m));
-            if (guides) TM_TRY(arena_alloc(g->arena, &tguide[dir], guide_len));
             L in, out;
             in.k = reinterpret_cast<uint32_t*>(dir == 0 ? esrc : edst);
             in.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(t32e) : reinterpret_cast<V*>(et);
             in.v2 = reinterpret_cast<uint32_t*>(dir == 0 ? edst : esrc);
             out.k = own[dir];
-            out.v0 = reinterpret_cast<V*>(lt);
-            out.v1 = reinterpret_cast<uint32_t*>(leid);
-            out.v2 = reinterpret_cast<uint32_t*>(lnbr);
+            out.v0 = reinterpret_cast<V*>(lt[dir]);
+            out.v1 = reinterpret_cast<uint32_t*>(leid[dir]);
+            out.v2 = reinterpret_cast<uint32_t*>(lnbr[dir]);
             tsort[dir] = sort_job(in, out, buf[dir].tmp, plan.npass, scratch_of(2 + dir, 2 + dir));
-            fin[dir] = ListFinish<TT>{leid, reinterpret_cast<uint32_t*>(lnbr), lt, tpos[dir], nt};
+            fin[dir] = ListFinish<TT>{leid[dir], reinterpret_cast<uint32_t*>(lnbr[dir]), lt[dir], tpos[dir], nt[dir]};
             D.off[dir] = off[dir];
             D.tpos[dir] = tpos[dir];
             D.tguide[dir] = tguide[dir];
-            ltab[dir] = lt;
             if constexpr (sizeof(TT) == 4) {
-                D.lt32[dir] = reinterpret_cast<const uint32_t*>(lt);
+                D.lt32[dir] = reinterpret_cast<const uint32_t*>(lt[dir]);
                 D.lt[dir] = nullptr;
-                D.lnt[dir] = nt;
+                D.lnt[dir] = nt[dir];
                 D.lnbr[dir] = nullptr;
             } else {
-                D.lt[dir] = reinterpret_cast<const int64_t*>(lt);
+                D.lt[dir] = reinterpret_cast<const int64_t*>(lt[dir]);
                 D.lt32[dir] = nullptr;
                 D.lnt[dir] = nullptr;
-                D.lnbr[dir] = lnbr;
+                D.lnbr[dir] = lnbr[dir];
             }
-            lnbr_of[dir] = reinterpret_cast<uint32_t*>(lnbr);
-            D.leid[dir] = leid;
-            D.lown[dir] = lown;
+            D.leid[dir] = leid[dir];
+            D.lown[dir] = lown[dir];
         }
         TM_TRY(sort_lists(tsort, 2 /* eids: 0, 1, ... */));
         hipLaunchKernelGGL(offsets_kernel, dim3(grid_for(m), 2), dim3(kBlock), 0, st, (const uint32_t*)own[0],
@@ -930,28 +942,23 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         NOrderFix<V> fix[2];
         for (int dir = 0; dir < 2; ++dir) {
             const int other = 1 - dir;
-            u64* nkey = nullptr;
-            int32_t *nxref = nullptr, *neid = nullptr, *nguide = nullptr;
-            TM_TRY(arena_alloc(g->arena, &nkey, m));
-            TM_TRY(arena_alloc(g->arena, &nxref, m));
-            TM_TRY(arena_alloc(g->arena, &neid, m));
-            if (guides) TM_TRY(arena_alloc(g->arena, &nguide, guide_len));
             L in, out;
-            in.k = lnbr_of[other];
-            in.v0 = reinterpret_cast<V*>(ltab[other]);
-            in.v1 = reinterpret_cast<uint32_t*>(const_cast<int32_t*>(D.leid[other]));
+            in.k = reinterpret_cast<uint32_t*>(lnbr[other]);
+            in.v0 = reinterpret_cast<V*>(lt[other]);
+            in.v1 = reinterpret_cast<uint32_t*>(leid[other]);
             in.v2 = own[other];
             out.k = buf[dir].nkeys;
-            out.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(buf[dir].ntime) : reinterpret_cast<V*>(nkey);
-            out.v1 = reinterpret_cast<uint32_t*>(neid);
+            out.v0 = sizeof(TT) == 4 ? reinterpret_cast<V*>(buf[dir].ntime) : reinterpret_cast<V*>(nkey[dir]);
+            out.v1 = reinterpret_cast<uint32_t*>(neid[dir]);
             out.v2 = buf[dir].nbr;
             nsort[dir] = sort_job(in, out, buf[dir].tmp, plan.npass, scratch_of(4 + dir, 2 + dir));
-            fix[dir] = NOrderFix<V>{buf[dir].nbr, out.v0, neid, tpos[dir], own[dir], off[dir],
-                                    reinterpret_cast<const V*>(ltab[dir]), nkey, nxref, nguide, tguide[dir]};
-            D.nkey[dir] = nkey;
-            D.nxref[dir] = nxref;
-            D.neid[dir] = neid;
-            D.nguide[dir] = nguide;
+            fix[dir] = NOrderFix<V>{buf[dir].nbr, out.v0, neid[dir], tpos[dir], own[dir], off[dir],
+                                    reinterpret_cast<const V*>(lt[dir]), nkey[dir], nxref[dir], nguide[dir],
+                                    tguide[dir]};
+            D.nkey[dir] = nkey[dir];
+            D.nxref[dir] = nxref[dir];
+            D.neid[dir] = neid[dir];
+            D.nguide[dir] = nguide[dir];
         }
         auto fix_lists = [&](int first, int count) -> int {
             hipLaunchKernelGGL((n_order_fix_kernel<V>), dim3(grid_for(m), (unsigned)count), dim3(kBlock), 0, st,
