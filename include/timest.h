@@ -349,17 +349,20 @@ int tm_batch_plan_create(tm_graph* const* g, const tm_motif* mo, const tm_tree* 
 int tm_batch_plan_run(tm_batch_plan* p, void* stream, tm_result* out);
 void tm_batch_plan_destroy(tm_batch_plan* p);
 
-/* Schedule of the batched kernels: samples per tile (>= 256) and the grid of
- * the persistent kernels (0 = 8 workgroups per compute unit).  Process-wide;
+/* Schedule of the batched kernels: samples per tile (>= 256; 8192, the
+ * default, is fitted to the pass, see tm_batch_opts) and the grid of the
+ * persistent kernels (0 = 8 workgroups per compute unit).  Process-wide;
  * the autotuner in the Python package searches these.  Returns the previous
  * values through prev_tile / prev_blocks when not NULL. */
 int tm_batch_config(int tile, int blocks, int* prev_tile, int* prev_blocks);
 
 /* The full schedule of the batched kernels (tm_batch_config sets the first
  * two fields only).  Process-wide; the autotuner searches these.
- *   tile: samples per tile, >= 256 (fewer in a pass of few samples); each lane
- *     of a 256-lane workgroup takes tile / 256 of a tile's samples (the
- *     samples per lane);
+ *   tile: samples per tile, >= 256; each lane of a 256-lane workgroup takes
+ *     tile / 256 of a tile's samples (the samples per lane).  The default,
+ *     8192, is the most a tile then holds: a pass of fewer than 2^26 samples
+ *     is split into about 8192 tiles of 512 samples or more.  Any other value
+ *     is used as it is;
  *   blocks: workgroups of the persistent kernels (0 = 8 per compute unit);
  *   root_lds: LDS bytes per workgroup that stage a job's interval prefix W_i
  *     for its root draws when it fits (jobs with a root guide read one or

@@ -2,14 +2,15 @@
 
 The batched persistent kernels take four knobs (tm_batch_options): samples
 per tile -- the unit of work pulled from the device counter, so also the
-samples each of a workgroup's 256 lanes takes (tile / 256) -- the grid size
-(how many workgroups, hence wavefronts, share the jobs at once), the LDS
-bytes that stage a job's interval prefix for its root draws, and the pass
-limit (left at its default: it only splits a batch).  Results never depend
-on them -- every sample is keyed by (seed, sample id) -- so the tuner times
-the real batch under each candidate, checks that every result is unchanged,
-and keeps the fastest: a grid over (tile, grid), then the LDS staging at the
-best pair.
+samples each of a workgroup's 256 lanes takes (tile / 256); 8192, the default,
+is fitted to the pass by the library, any other value is used as it is -- the
+grid size (how many workgroups, hence wavefronts, share the jobs at once), the
+LDS bytes that stage a job's interval prefix for its root draws, and the pass
+limit (left at its default: it only splits a batch).  Results never depend on
+them -- every sample is keyed by (seed, sample id) -- so the tuner times the
+real batch under each candidate, checks that every result is unchanged, and
+keeps the fastest: a grid over (tile, grid), then the LDS staging at the best
+pair.
 """
 import time
 

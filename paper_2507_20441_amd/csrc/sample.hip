@@ -1503,7 +1503,7 @@ void launch_batch_sample(int mode, dim3 grid, hipStream_t st, const SampleArgs* 
                            counter, tile_parts);
 }
 
-constexpr u64 kBatchTiles = 8192;  // tiles a pass is split into where the configured ones are larger
+constexpr u64 kBatchTiles = 8192;  // tiles a pass is split into where the default ones are larger
 
 // The kernel groups of a batched pass, by width and completion counter.  (A
 // group of their own for the plans that kSmall holds, with five or six waves a
@@ -1803,7 +1803,7 @@ int sample_run(tm_weights* w, u64 seed, u64 j0, u64 count, u64 k_total, hipStrea
 // ---------------------------------------------------------------------------
 // Host side of batched sampling.
 // ---------------------------------------------------------------------------
-BatchConfig g_batch_config = {8192, 0, 0, kCumLdsBytes};
+BatchConfig g_batch_config = {kDefaultTile, 0, 0, kCumLdsBytes};
 
 void sums_merge(JobSums& into, const JobSums& x) {
     if (!add_ok(into.acc2, x.acc2, &into.acc2)) into.flags |= 1;
@@ -1874,14 +1874,18 @@ void group_prepare(tm_weights* const* ws, const std::vector<int>& act, const u64
     }
     G.key_bits = std::max(1, bits_of(key_space - 1));
     G.passes = radix_passes(G.key_bits - root_sort_lo_bit(G.key_bits));
-    // at most the configured tile: a lane takes its samples of a tile one after
-    // the other, so a pass is never shorter than that, and a few large tiles
-    // leave most of the chip waiting for them (16 jobs of 1e4 to 1e6 edges,
-    // 1e7 samples, whole call: 3.1 ms with tiles of 8192 samples, 2.63 with
-    // this; 24 warm queries at a server 4.3 and 3.55; split into half or twice
-    // as many tiles within 3%)
-    const u64 fair = (G.total / kBatchTiles + kBlock - 1) / kBlock * kBlock;
-    const int tile = (int)std::min<u64>(cfg.tile > 0 ? cfg.tile : 8192, std::max<u64>(fair, 2 * kBlock));
+    // a tile that the caller chose is taken as it is; the default is fitted to
+    // the pass: a lane takes its samples of a tile one after the other, so a
+    // pass is never shorter than that, and a few large tiles leave most of the
+    // chip waiting for them (16 jobs of 1e4 to 1e6 edges, 1e7 samples, whole
+    // call: 3.1 ms with tiles of 8192 samples, 2.63 with this; 24 warm queries
+    // at a server 4.3 and 3.55; split into half or twice as many tiles within
+    // 3%)
+    int tile = cfg.tile > 0 ? cfg.tile : kDefaultTile;
+    if (tile == kDefaultTile) {
+        const u64 fair = (G.total / kBatchTiles + kBlock - 1) / kBlock * kBlock;
+        tile = (int)std::min<u64>(tile, std::max<u64>(fair, 2 * kBlock));
+    }
     int cus = 256;
     {
         int dev = 0;

@@ -356,8 +356,10 @@ void sums_to_result(const JobSums& s, tm_result* out);
 
 // Batched sampling of several weight sets in one pass (tile: samples per work
 // item of the persistent kernels; blocks: their grid, 0 = 8 per CU).
+constexpr int kDefaultTile = 8192;
 struct BatchConfig {
-    int tile;          // samples per tile (each of a workgroup's lanes takes tile / kBlock)
+    int tile;          // samples per tile (each of a workgroup's lanes takes tile / kBlock);
+                       // kDefaultTile: at most that, fewer in a pass of few samples
     int blocks;        // persistent grid (0: 8 workgroups per CU)
     u64 group_limit;   // root keys and samples per batched pass (0: 2^32)
     int root_lds;      // LDS bytes staging a job's interval prefix in the root draws
