@@ -50,3 +50,15 @@ def test_edge_counts(T, m):
     print("[intervals] edges", m, flush=True)
     g = W.small_graph(m, 52, n=max(2, m // 30), span=5000)
     check(T, g.src, g.dst, g.t, g.n, 300, int(g.t.max() - g.t.min()) // 300 + 1)
+
+
+@pytest.mark.parametrize("delta", [2**31, 2**61 + 12345, 2**62 - 1])
+def test_delta_near_the_largest(T, delta):
+    # one or two intervals whose ends lie far past every time
+    print("[intervals] delta", delta, flush=True)
+    g = W.small_graph(2000, 53, n=60, span=5000)
+    check(T, g.src, g.dst, g.t, g.n, delta, 1)
+    if delta < 2**61:
+        t = g.t - g.t.min()
+        t = np.where(t > 2500, t + delta, t)
+        check(T, g.src, g.dst, t, g.n, delta, 2)

@@ -77,3 +77,29 @@ def test_weights_and_samples_match_oracle(T, kind):
             ro, reco = P.sample(3, k, records=True)
             rg, recg = Wt.sample(3, k, records=True)
             assert (reco == recg).all() and rg.estimate == ro.estimate
+
+
+@pytest.mark.parametrize("kind", ["as_many_vertices", "one_vertex_more", "many_idle_vertices", "one_time",
+                                  "times_at_both_ends", "near_ids", "span_31_bits", "span_32_bits", "span_33_bits",
+                                  "span_40_bits"])
+def test_served_samples_match_oracle(T, kind):
+    """A server's sets keep no windows: each of their samples searches the
+    lists, below and above the count that sorts roots."""
+    u, v, t, n = make(kind)
+    print("[guides] served", kind, len(u), n, flush=True)
+    og, tg = O.Graph(u, v, t, n), T.Graph(u, v, t, n)
+    delta = max(1, int(t.max() - t.min()) // 20)
+    with T.Server(4 << 30) as server:
+        gid = server.add_graph(tg)
+        for name in ("3cycle", "scatter_gather", "6chain"):
+            P = O.Prep(og, O.make_motif(W.MOTIFS[name], delta))
+            for k in (500, 70_000):
+                r, _ = server.wait(server.submit(gid, T.make_motif(W.MOTIFS[name], delta), k, 3))
+                assert r.W.value == P.W
+                if P.W == 0:
+                    continue
+                o, _ = P.sample(3, k)
+                assert (r.acc2.value, r.acc2_sq.value, r.n_valid, r.n_bad_vertex, r.n_bad_delta, r.n_bad_order,
+                        r.n_nonzero, r.estimate) == \
+                       (o.acc2.value, o.acc2_sq.value, o.n_valid, o.n_bad_vertex, o.n_bad_delta, o.n_bad_order,
+                        o.n_nonzero, o.estimate), (name, k)
