@@ -13,7 +13,8 @@ Workload: 2,000,000 vertices, 100,000,000 edges (90M Chung-Lu gamma 2.0 +
 The same JSON line carries: the roofline of the dominant kernel (the
 sampler: its access-model bytes per launch over the average launch from HIP
 events in the timed region) and of the level kernels of the weight builds,
-the graph build and the root draws; the oracle's single-thread CPU throughput on
+the graph build and the root draws (the bytes each cannot do without, over its
+stage); the oracle's single-thread CPU throughput on
 a bounded slice of the same workload; the batched-queue against one job per
 launch (64 jobs); the serving loop's p50/p99 latency on a short Poisson
 stream; and the medium workload's rate and sampler roofline.
@@ -211,7 +212,7 @@ def medium_run(args, steps, warmup, cpu_samples):
     # Access-model bytes of the sampling kernel's launches in one step
     # (counting pass, outside the timed region: same draws).
     Gm = T.Graph(src, dst, tt, g.n)
-    model_bytes = 0
+    model_bytes = level_bytes = 0
     per_motif = []
     for (name, mo), r in zip(motifs, results):
         Wt = T.Weights(Gm, mo)
@@ -223,9 +224,9 @@ def medium_run(args, steps, warmup, cpu_samples):
         per_motif.append(dict(motif=name, estimate=est, std_error=se,
                               rel_ci95=(1.96 * se / est) if est else None, valid=nvalid, W=Wv,
                               model_bytes=b.value))
+        # ... and what its level launches cannot do without
+        level_bytes += level_bytes_of(Wt, g.m, Gm.info()["t_span"])
         Wt.close()
-    # ... and of the level kernels of one step's weight builds
-    level_bytes = sum(T.weights_model_bytes(Gm, mo) for _, mo in motifs)
     Gm.close()
     # counter-measured bytes, valid only for the kernel source they were taken on
     traffic = load_traffic(args.traffic, "sample_kernel")
@@ -589,6 +590,46 @@ def roofline_of(kernel, bytes_per_launch, avg_ms, traffic):
     return out
 
 
+def level_plan(edges, tree, center):
+    """The level launches of a weight build, as (kept windows, children with
+    tables of their own, whether it reads an earlier launch's products) each:
+    one per tree edge with children and endpoint they attach at.  Leaf children
+    that attach at the same endpoint, in the same direction and on the same side
+    in time share a window."""
+    rest = set(tree) - {center}
+    launches = []
+
+    def visit(e, at):
+        mine = [(c, x) for c in sorted(rest) for x in set(edges[c]) & set(edges[e]) if x != at]
+        mine = list(dict(mine).items())
+        rest.difference_update(c for c, _ in mine)
+        inner = {c: visit(c, x) for c, x in mine}
+        first = True
+        for end in edges[e]:
+            kids = [c for c, x in mine if x == end]
+            if kids:
+                windows = {(edges[c][0] == end, c < e, c if inner[c] else None) for c in kids}
+                launches.append((len(windows), sum(inner[c] for c in kids), not first))
+                first = False
+        return bool(mine)
+
+    visit(center, None)
+    return launches
+
+
+def level_bytes_of(w, m, t_span):
+    """Bytes that the level launches of weight set w cannot do without: per
+    launch and edge the walked list entry (owner, neighbour, time), the windows
+    kept (32 B per child) and the products written, read again by a second
+    launch of the same tree edge; and the prefix table of every child that has
+    one, once.  Products and tables hold two interval parities."""
+    mo, tr = w.mo, w.info()["tree"]
+    edges = [(mo.src[p], mo.dst[p]) for p in range(mo.l)]
+    launches = level_plan(edges, list(tr.edge[:tr.n_edges]), tr.center)
+    entry = 12 if t_span < 2**32 - 1 else 16
+    return m * sum(entry + 32 * windows + 16 + 16 * again + 16 * inner for windows, inner, again in launches)
+
+
 def large(args):
     """The large workload: 2e6 vertices, 1e8 edges (drawn on the device),
     scatter-gather and 6-chain at delta 86400, 1e8 samples each; a step is
@@ -664,14 +705,14 @@ def large(args):
     stage_ms = {T.STAGES[i]: bd["ms"][i] / nb for i in range(len(T.STAGES))}
     stage_n = {T.STAGES[i]: bd["launches"][i] / nb for i in range(len(T.STAGES))}
     log("stage ms per step", {a: round(b, 3) for a, b in stage_ms.items()})
-    # access-model bytes of one step's level kernels and sampling kernels
-    # (counting variants, outside the timed region)
+    # access-model bytes of one step's sampling kernels (counting variants,
+    # outside the timed region), and what its level launches cannot do without
     g = T.Graph(u, v, t, n)
-    level_bytes = sum(T.weights_model_bytes(g, mo) for _, mo in motifs)
-    sample_bytes = 0
+    level_bytes = sample_bytes = 0
     for _, mo in motifs:
         w = T.Weights(g, mo)
         sample_bytes += T.sample_model_bytes(w, seed, k)
+        level_bytes += level_bytes_of(w, m, g.info()["t_span"])
         w.close()
     g.close()
     traffic = args.large_traffic
@@ -1279,7 +1320,22 @@ TRAFFIC_KERNELS = {
                       "sample.hip"),
     "root_kernel": (lambda nm: "root_kernel<" in nm and "batch_" not in nm, "sample.hip"),
     "level_kernel": (lambda nm: "level_kernel<" in nm and _targs(nm)[1:2] == ["false"], "weights.hip"),
+    "pair_rank_kernel": (lambda nm: "pair_rank_kernel(" in nm, "csr.hip"),
 }
+
+
+# The kernels that only graph builds launch.  The digit counts, the fills and
+# the copies of a few words to the host, shared by name with other calls, are
+# left out (a few percent).
+GRAPH_KERNELS = ("validate_kernel", "validate_reduce_kernel", "canon_keys_kernel", "decode_packed_kernel",
+                 "decode_split_kernel", "decode_ties_kernel", "decode_long_kernel", "list_finish_kernel",
+                 "n_order_fix_kernel", "offsets_kernel")
+
+
+def graph_kernel(nm):
+    nm = nm.replace("(anonymous namespace)::", "")
+    return any(k + "(" in nm or k + "<" in nm for k in GRAPH_KERNELS) or \
+        ("sort_pass_kernel<" in nm and "sort_pass_kernel<unsigned int, unsigned int, SortNone" not in nm)
 
 
 def summarize_traffic(fetch_dir, write_dir, out_path, calib_bytes, workload):
@@ -1326,20 +1382,13 @@ def summarize_traffic(fetch_dir, write_dir, out_path, calib_bytes, workload):
                             fetch_bytes_per_launch=round(fb), write_bytes_per_launch=round(wb),
                             hbm_bytes_per_launch=round(fb + wb))
     # the graph build as a whole: every kernel only it launches, summed over
-    # a build (builds counted by the validation kernel); the digit counts,
-    # shared with the root sorts by name, are left out (a few percent)
-    def graph_test(nm):
-        nm = nm.replace("(anonymous namespace)::", "")
-        return any(k in nm for k in ("validate_kernel(", "validate_reduce_kernel(", "canon_keys_kernel(",
-                                     "decode_packed_kernel(", "decode_split_kernel(", "list_finish_kernel<",
-                                     "n_order_fix_kernel<", "offsets_kernel(")) or \
-            ("sort_pass_kernel<" in nm and "sort_pass_kernel<unsigned int, unsigned int, SortNone" not in nm)
+    # a build (builds counted by the validation kernel)
     builds = sum(len(vs) for nm, vs in fk.items() if "validate_kernel(" in nm.replace("(anonymous namespace)::", ""))
     if builds:
-        fb = sum(x for nm, vs in fk.items() if graph_test(nm) for x in vs) * 1024 * f_scale / builds
-        wb = sum(x for nm, vs in wk.items() if graph_test(nm) for x in vs) * 1024 * w_scale / builds
+        fb = sum(x for nm, vs in fk.items() if graph_kernel(nm) for x in vs) * 1024 * f_scale / builds
+        wb = sum(x for nm, vs in wk.items() if graph_kernel(nm) for x in vs) * 1024 * w_scale / builds
         kernels["graph_build"] = dict(names=sorted({nm.replace("(anonymous namespace)::", "").replace("void ", "")
-                                                    .split("(")[0] for nm in fk if graph_test(nm)}),
+                                                    .split("(")[0] for nm in fk if graph_kernel(nm)}),
                                       source="csr.hip", source_sha=kernel_source_sha("csr.hip"), launches=builds,
                                       per="build", fetch_bytes_per_launch=round(fb), write_bytes_per_launch=round(wb),
                                       hbm_bytes_per_launch=round(fb + wb))

@@ -344,11 +344,13 @@ __device__ __forceinline__ W window_mass(int32_t p0, int32_t p1, int32_t q0, int
 // blk L), min(t + delta, (blk + 2) L - 1)] and B = [max(t - delta,
 // (blk - 1) L), min(t + delta, (blk + 1) L - 1)], four distinct bounds.
 //
-// The counting variant returns the bytes the edge's work reads and writes
-// under the access model: each read or write its element size; a list search
-// of L entries ceil(log2 L) + 1 probes of each of its six bounds (three in
-// the T order, of the list's time size, and three 8 B keys in the N order;
-// eight bounds for an unordered child).
+// The counting variant returns the edge's work as the bytes of an access model
+// with plain searches: each read or write its element size; a list search of
+// L entries ceil(log2 L) + 1 probes of each of its six bounds (three in the T
+// order, of the list's time size, and three 8 B keys in the N order; eight
+// bounds for an unordered child).  The kernel makes a few of those probes
+// (guides, pair ranks); the model is kept as a measure that does not change
+// with them.
 template <typename W, bool kCount, bool kPO>
 __device__ __forceinline__ u64 level_edge(const LevelArgs& a, int64_t p) {
     const DevGraph& G = a.G;

@@ -59,3 +59,57 @@ def test_committed_traffic_matches_the_kernels(name):
     for key, k in tr["kernels"].items():
         assert k["source_sha"] == bench.kernel_source_sha(k.get("source", "sample.hip")), key
         assert bench.load_traffic(path, key) == k["hbm_bytes_per_launch"]
+
+
+def test_graph_traffic_covers_every_kernel_of_its_source():
+    """Every kernel of the graph build's source file is counted as the graph
+    build's, or on its own."""
+    import re
+    src = open(os.path.join(ROOT, "paper_2507_20441_amd", "csrc", "csr.hip")).read()
+    names = set(re.findall(r"__global__\s+void\s+(?:__launch_bounds__\(\w+\)\s+)?(\w+)\(", src))
+    assert {"validate_kernel", "decode_ties_kernel", "n_order_fix_kernel", "pair_rank_kernel"} <= names
+    for name in names:
+        for form in (f"(anonymous namespace)::{name}(long)", f"void (anonymous namespace)::{name}<unsigned int>(long)"):
+            own = any(test(form.replace("(anonymous namespace)::", "")) for test, _ in bench.TRAFFIC_KERNELS.values())
+            if bench.graph_kernel(form) != own:
+                break
+        else:
+            assert False, name
+    sort = "void sort_pass_kernel<unsigned int, unsigned int, {}, SortNone, 16>(SortPass)"
+    assert bench.graph_kernel(sort.format("unsigned int")) and not bench.graph_kernel(sort.format("SortNone"))
+
+
+@pytest.mark.parametrize("edges,tree,center,plan", [
+    # a 4-cycle's path tree from its middle edge: a leaf at either end
+    (((0, 1), (1, 2), (2, 3), (3, 0)), [0, 1, 2], 1, [(1, 0, False), (1, 0, True)]),
+    # an out-star: three leaves that share one window
+    (((0, 1), (0, 2), (0, 3), (0, 4)), [0, 1, 2, 3], 0, [(1, 0, False)]),
+    # a 6-chain from its middle edge: two children with a leaf each
+    (((0, 1), (1, 2), (2, 3), (3, 4), (4, 5)), [0, 1, 2, 3, 4], 2,
+     [(1, 0, False), (1, 0, False), (1, 1, False), (1, 1, True)]),
+    # scatter-gather from its second edge: a leaf at one end, a child with a leaf at the other
+    (((0, 1), (0, 2), (0, 3), (1, 4), (2, 4), (3, 4)), [0, 1, 4, 5], 1,
+     [(1, 0, False), (1, 0, False), (1, 1, True)]),
+])
+def test_level_bytes(edges, tree, center, plan):
+    got = bench.level_plan(edges, tree, center)
+    assert sorted(got) == sorted(plan)
+
+    class Tree:
+        edge, n_edges = tree + [-1], len(tree)
+
+    Tree.center = center
+
+    class Set:
+        class mo:
+            l = len(edges)
+            src = [a for a, _ in edges]
+            dst = [b for _, b in edges]
+
+        @staticmethod
+        def info():
+            return {"tree": Tree}
+
+    for span, entry in ((2**32 - 2, 12), (2**32 - 1, 16)):
+        want = sum(entry + 32 * windows + 16 + 16 * again + 16 * inner for windows, inner, again in plan)
+        assert bench.level_bytes_of(Set, 1000, span) == 1000 * want
