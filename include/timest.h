@@ -560,16 +560,16 @@ int tm_sample_model_bytes(tm_weights* w, uint64_t seed, uint64_t j0, uint64_t co
  * plain list searches.  The kernels themselves read less -- a search stays
  * inside a slice of its list, and a graph's pair ranks give the N-order bounds
  * with no probe in most cases -- so this is a measure of the task, and no
- * numerator of a share of the memory's rate.  The model: a search over a list of L entries is charged ceil(log2 L) + 1 probes of
- * each of its six bounds (three over the T order, of the lists' time size:
- * 4 B when every shifted time is below 2^32 - 1, else 8 B; three 8 B keys
- * over the N order), every other read and write its element size (the edge, the
- * first pass's products, the children's prefix entries, the kept windows,
- * the products written).  The set is built as tm_weights_create_ex with
- * constraints TM_C_ALL builds it (a counting variant of the same kernels,
- * not timed) and then freed; a 64-bit build that overflows counts both
- * attempts, as the TM_STAGE_LEVELS timing does.  Errors: as
- * tm_weights_create. */
+ * numerator of a share of the memory's rate.  The model: a search over a list
+ * of L entries is charged ceil(log2 L) + 1 probes of each of its six bounds
+ * (three over the T order, of the lists' time size: 4 B when every shifted
+ * time is below 2^32 - 1, else 8 B; three 8 B keys over the N order), every
+ * other read and write its element size (the edge, the first pass's products,
+ * the children's prefix entries, the kept windows, the products written).
+ * The set is built as tm_weights_create_ex with constraints TM_C_ALL builds it
+ * (a counting variant of the same kernels, not timed) and then freed; a 64-bit
+ * build that overflows counts both attempts, as the TM_STAGE_LEVELS timing
+ * does.  Errors: as tm_weights_create. */
 int tm_weights_model_bytes(tm_graph* g, const tm_motif* mo, const tm_tree* tr, void* stream,
                            uint64_t* bytes);
 
