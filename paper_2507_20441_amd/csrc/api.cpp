@@ -623,6 +623,18 @@ extern "C" int tm_choose_tree(tm_graph* g, const tm_motif* mo, int n_c, void* st
     std::vector<TreeCand> c;
     TM_TRY(tree_cands(mo, c));
     const int n = std::min<int>(n_c, (int)c.size());
+    // the candidates' level launches are one call's
+    int launches = 0;
+    for (int x = 0; x < n; ++x) {
+        const tm_tree tr = to_tree(c[x]);
+        HostPlan P;
+        TM_TRY(plan_build(mo, &tr, &P));
+        launches += level_launches(P);
+        if (x + 1 == n && launches >= kRankAllLaunches && g->m > 0)
+            graph_pair_ranks(g, launches,
+                             weights_footprint(P, g->m, g->T / mo->delta + 1, false) + weights_build_extra(g->m, false),
+                             as_stream(stream));
+    }
     int arg = -1;
     u128 bestW = 0;
     for (int x = 0; x < n; ++x) {
@@ -1279,7 +1291,7 @@ extern "C" int tm_batch_plan_create(tm_graph* const* g, const tm_motif* mo, cons
     for (int i = 0; i < n_jobs; ++i) {
         HostPlan& p = raw->ws[i]->plan;
         const int64_t q = raw->g[i]->m > 0 ? raw->g[i]->T / p.mo.delta + 1 : 0;
-        graph_pair_ranks(raw->g[i], kRankLaunches,
+        graph_pair_ranks(raw->g[i], kRankAllLaunches,
                          weights_footprint(p, raw->g[i]->m, q, false) + weights_build_extra(raw->g[i]->m, false),
                          raw->cs);
     }

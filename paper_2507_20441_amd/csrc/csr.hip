@@ -492,7 +492,9 @@ void graph_pair_ranks(tm_graph* g, int launches, u64 need, hipStream_t st) {
     if (g->m < kRanksFrom || g->m > kRanksTo || R.state.load(std::memory_order_acquire) != PairRanks::kNone ||
         dev_deferring())
         return;
-    if (R.launches.fetch_add(launches) + launches < kRankAllLaunches && launches < kRankLaunches) return;
+    const bool pays = R.launches.fetch_add(launches) + launches >= kRankAllLaunches ||
+                      (launches >= kRankLaunches && g->m >= kRanksAtOnce);
+    if (!pays) return;
     int none = PairRanks::kNone;
     if (!R.state.compare_exchange_strong(none, PairRanks::kBusy)) return;  // another thread makes them
     AllocScope scope_(alloc_of(g));

@@ -286,21 +286,25 @@ struct tm_weights {
 int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64_t* t,
                 hipStream_t st);
 // Makes g's pair ranks (32 B per edge), on st and waited for, in the first
-// weight build that they pay for: one with at least kRankLaunches level
-// launches, or that brings the graph's to kRankAllLaunches; `launches` are this
-// build's, and `need` its tables' bytes, which come first.  A graph that cannot
-// have them, or not while work is recorded, goes on without.
+// call that they pay for: one with kRankLaunches level launches on a graph of
+// 2^22 edges or more, or that brings a graph's to kRankAllLaunches; `launches`
+// are this call's, and `need` its tables' bytes, which come first.  A graph that
+// cannot have them, or not while work is recorded, goes on without.
 //   Making them takes 40 us at 5e5 edges, 60 at 1e6, 240 at 4e6, 1.2 ms at 2e7
-// and 6.8 ms at 1e8; a level launch then gains 3, 11, 70, 330 and 2000 us.
-// Made by every graph build they had one of 1e8 edges take 35.1 ms, which takes
-// 29.6 without (2e7: 7.2 and 6.1), whatever was asked of the graph afterwards.
-// Below 2^19 edges a graph would have to meet many motifs to earn them; above
-// 2^28 their memory goes to weight sets, as that of the owners.
-constexpr int64_t kRanksFrom = (int64_t)1 << 19, kRanksTo = (int64_t)1 << 28;
+// and 6.8 ms at 1e8; a level launch then gains 3, 11, 70, 330 and 2000 us: 3.5
+// launches' worth from 4e6 edges on, 5 and more below.  Made by every graph
+// build they had one of 1e8 edges take 35.1 ms, which takes 29.6 without (2e7:
+// 7.2 and 6.1), whatever was asked of the graph afterwards.  Below 2^19 edges a
+// graph would have to meet many motifs to earn them; above 2^28 their memory
+// goes to weight sets, as that of the owners.
+constexpr int64_t kRanksFrom = (int64_t)1 << 19, kRanksAtOnce = (int64_t)1 << 22, kRanksTo = (int64_t)1 << 28;
 constexpr int kRankLaunches = 3, kRankAllLaunches = 8;
 void graph_pair_ranks(tm_graph* g, int launches, u64 need, hipStream_t st);
 // The graph as kernels take it, with the pair ranks that are there.
 DevGraph graph_view(const tm_graph* g);
+// Level launches of a weight build: one per slot with children and endpoint
+// that children attach at.
+int level_launches(const HostPlan& P);
 // model_bytes (optional): the level kernels' access-model bytes (every
 // attempt, as the level stage timing counts every attempt).
 int weights_build(tm_weights* w, hipStream_t st, u64* model_bytes = nullptr);

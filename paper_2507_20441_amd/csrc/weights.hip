@@ -999,8 +999,6 @@ int64_t interval_unit(const tm_weights* w) {
     return (w->constraints & TM_C_WINDOWS) ? w->plan.mo.delta : w->g->T + 1;
 }
 
-// Level launches of a weight build: one per slot with children and endpoint
-// that children attach at.
 int level_launches(const HostPlan& P) {
     int n = 0;
     for (int s = 0; s < P.nt; ++s) {
