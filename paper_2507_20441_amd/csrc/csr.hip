@@ -472,9 +472,10 @@ __global__ void offsets_kernel(const uint32_t* key0, const uint32_t* key1, int64
 }
 
 // List sorts side by side up to this many edges (a pass of few tiles leaves the
-// chip idle: a build of 2^14 edges takes 167 us with pairs and 201 without,
-// 2^20 512 and 630, 2^21 862 and 1028, 2^22 1685 and 1760).  Larger builds
-// gain 3% and keep the memory of the second buffers (28 to 32 B per edge).
+// chip idle: a build of 2^14 edges takes 157 us with pairs and 206 without,
+// 2^20 395 and 518, 2^21 649 and 836, 2^22 1255 and 1350).  Larger builds
+// gain 3 to 5% (2^24 edges 4.48 and 4.65 ms) and keep the memory of the second
+// buffers (28 to 32 B per edge).
 constexpr int64_t kPairedSorts = (int64_t)1 << 22;
 
 int bits_for(u64 x) {
@@ -716,15 +717,14 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     // bits alone (2-4 passes instead of 5-10) leaves short runs of equal times
     // to put in order, and the edges of the few long ones are sorted apart; how
     // many those are costs a round trip to the host.  Builds with the full sort
-    // and this way: 2^14 edges 164 and 151 us, 2^18 285 and 232, 2^20 513 and
-    // 425, 2^22 1690 and 1515, 2^24 6.76 and 5.90 ms.  (With 300 edges at one
-    // time, which started the full sort over before there was the list, 2^18
-    // edges 421 and 342 us, 4e6 1.94 and 1.57 ms, 2e7 9.32 and 7.26 ms.)  It pays
-    // while fewer than half of the edges are in long runs (each then costs the
-    // full sort's passes on top); past that the full sort starts over, so where
-    // the sampled times say that an edge shares its time with more than kTieMean
-    // others on average, it is not tried: each edge reads that many to find its
-    // place.  Every time held by 16, 24 and 60 edges, the full sort and this way:
+    // and this way: 2^14 edges 162 and 157 us, 2^18 286 and 240, 2^20 480 and
+    // 395, 2^22 1416 and 1255, 2^24 5.46 and 4.65 ms.  (300 edges at one time,
+    // for which the full sort started over before there was the list, add 96 us
+    // at 2^18 edges and 97 at 4e6; they added 186 and 474.)  It pays while fewer
+    // than half of the edges are in long runs (each then costs the full sort's
+    // passes on top); past that the full sort starts over.  Where the sampled
+    // times say that an edge shares its time with more than kTieMean others on
+    // average, it is not tried: each edge reads that many to find its place.  Every time held by 16, 24 and 60 edges, the full sort and this way:
     // 4e6 edges 1397 and 1378, 1391 and 1425, 1372 and 1636 us; 2e7 7.00 and
     // 6.71, 6.97 and 6.95, 6.88 and 8.02 ms; 1e6 456 and 417, 458 and 432, 453
     // and 490 us.

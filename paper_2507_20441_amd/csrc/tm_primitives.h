@@ -17,9 +17,9 @@ constexpr int kSortDigits = 1 << kSortBits;        // 256
 // over few tiles is one tile's serial work -- ranking key by key, one array
 // after another through LDS -- and is left after a quarter of the keys (1024,
 // whose values also fit in registers from the start).  A graph build of 2^14
-// edges takes 198 us with the small tiles and 301 with the large, 2^18 edges
-// 351 and 412, 2^19 506 and 494, 2^21 1475 and 1020; sampling 2^16 roots 88
-// and 95 us, 2^18 112 and 116, 2^19 152 and 148.
+// edges takes 158 us with the small tiles and 222 with the large, 2^18 edges
+// 238 and 275, 2^19 324 and 309, 2^20 509 and 394; sampling 2^16 roots 80 and
+// 93 us, 2^18 104 and 111, 2^20 200 and 179.
 constexpr int kSortItems = 16;
 constexpr int kSortItemsSmall = 4;
 constexpr int64_t kSortSmall = (int64_t)1 << 18;
