@@ -189,7 +189,10 @@ int tm_graph_create(const int32_t* src, const int32_t* dst, const int64_t* t, in
  * first.  NULL is ignored. */
 void tm_graph_destroy(tm_graph* g);
 
-/* Sizes of a graph; any output pointer may be NULL. */
+/* Sizes of a graph; any output pointer may be NULL.  device_bytes grows once,
+ * by 32 B per edge, when a weight build on a graph of 2^19 to 2^28 edges makes
+ * lookup records that later builds and samples read (from the graph's
+ * allocator; without that memory the builds go on without them). */
 int tm_graph_info(const tm_graph* g, int64_t* m, int32_t* n, int64_t* t_shift,
                   int64_t* t_span, uint64_t* device_bytes);
 
