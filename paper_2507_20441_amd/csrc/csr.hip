@@ -707,8 +707,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
         *uv = r2.v0;
         return TM_OK;
     };
-    // What the flag words, once read, say of the edges.
-    auto verdict = [&]() -> int {
+    // The error that the flag words, once read, hold.
+    auto flags_error = [&]() -> int {
         if (hflags[kFlags] & kDup) return tm_fail(TM_EDUP, "graph: duplicate (u, v, t) tuple");
         if (hflags[kSortErr]) return tm_fail(TM_EDEVICE, "graph: internal sort error (look-back stalled)");
         return TM_OK;
@@ -724,10 +724,11 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     // than half of the edges are in long runs (each then costs the full sort's
     // passes on top); past that the full sort starts over.  Where the sampled
     // times say that an edge shares its time with more than kTieMean others on
-    // average, it is not tried: each edge reads that many to find its place.  Every time held by 16, 24 and 60 edges, the full sort and this way:
-    // 4e6 edges 1397 and 1378, 1391 and 1425, 1372 and 1636 us; 2e7 7.00 and
-    // 6.71, 6.97 and 6.95, 6.88 and 8.02 ms; 1e6 456 and 417, 458 and 432, 453
-    // and 490 us.
+    // average, it is not tried: each edge reads that many to find its place.
+    // Every time held by 16, 24 and 60 edges, the full sort and this way: 4e6
+    // edges 1397 and 1378, 1391 and 1425, 1372 and 1636 us; 2e7 7.00 and 6.71,
+    // 6.97 and 6.95, 6.88 and 8.02 ms; 1e6 456 and 417, 458 and 432, 453 and 490
+    // us.
     auto order_by_time = [&](bool* done) -> int {
         u64 *key, *uv = nullptr;
         u64 *lk, *lv = nullptr, *lk1, *lv1 = nullptr;  // the listed edges' keys and their sort's other buffers
@@ -752,7 +753,7 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
                            (const u64*)uv, m, bn, esrc, edst, et, t32e, flags, lk, lv, cap);
         TM_HIP(hipGetLastError());
         TM_HIP(read_back({{hflags, flags, sizeof hflags}}, st));
-        TM_TRY(verdict());  // (what this refuses, no list is built for)
+        TM_TRY(flags_error());  // (what this refuses, no list is built for)
         const int64_t c = (int64_t)(uint32_t)hflags[kLongEdges];
         *done = c <= cap;
         if (c == 0) return TM_OK;
@@ -763,7 +764,8 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
             return TM_OK;
         }
         u64 *sk, *suv;
-        TM_TRY(one_key ? order_all(lk, nullptr, lk1, nullptr, c, &sk, &suv) : order_all(lv, lk, lv1, lk1, c, &sk, &suv));
+        TM_TRY(one_key ? order_all(lk, nullptr, lk1, nullptr, c, &sk, &suv)
+                       : order_all(lv, lk, lv1, lk1, c, &sk, &suv));
         hipLaunchKernelGGL(decode_long_kernel, dim3(grid_for(c)), dim3(kBlock), 0, st, (const u64*)sk,
                            (const u64*)suv, c, (const u64*)key, m, bn, esrc, edst, et, t32e, flags);
         TM_HIP(hipGetLastError());
@@ -986,5 +988,5 @@ int graph_build(tm_graph* g, const int32_t* src, const int32_t* dst, const int64
     TM_HIP(dev_free(flags, st));
     TM_HIP(dev_free(tbounds, st));
     timer.finish();
-    return verdict();
+    return flags_error();
 }
